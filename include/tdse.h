@@ -267,14 +267,14 @@ int tdse_far_eval_noalloc(tdse_plan_t plan, const double* xs, int32_t nx, const 
 int tdse_query(tdse_plan_t plan, int32_t key, double* value);
 
 /* Plan options.  TDSE_CFG_PERSISTENT (default 1): a square 2D periodic FP64
- * plan (M = 32..512, a power of two, stored potential fields) marches its
+ * plan (M = 32..512, 2^a or 3*2^a, stored potential fields) marches its
  * implicit Adams steps in one launch of a co-resident grid (one workgroup per
- * two lines; the multistep state stays in registers and LDS, the grid
- * synchronizes between the two transform directions of each step), falling
+ * two lines; the multistep state stays in registers and LDS, the workgroups
+ * exchange the tile between the two transform directions of each step), falling
  * back to two kernel passes per step when the device cannot hold the grid;
  * 0 always takes the passes.  Not while a run is under way (ESTATE).  The
- * persistent launch synchronizes the stream once, to check that no grid
- * barrier timed out (TDSE_EDEVICE if one did). */
+ * persistent launch synchronizes the stream once, to check that no exchange
+ * timed out (TDSE_EDEVICE if one did). */
 #define TDSE_CFG_PERSISTENT 0
 /* TDSE_CFG_GUARD (default 0, off): with value K >= 1, tdse_step marches in
  * pieces of at most K steps and after each piece, and tdse_run after the

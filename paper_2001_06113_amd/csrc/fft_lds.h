@@ -273,4 +273,116 @@ __device__ __forceinline__ void fft_regs(C* v, int t, C* line, const TW& tw) {
   if constexpr (N > 1) fft_regs_rec<N, TL, 1, INV>(v, t, line, tw);
 }
 
+// ------------------------------------------- held twiddles, alternating lines
+//
+// For kernels that transform many lines of one length N = 2^a or 3 * 2^a:
+// each thread's twiddles (the same in every transform) stay in registers, and
+// the exchanges alternate between two LDS lines.  A pass then costs one
+// barrier and no table reads: a line is written again only two exchanges
+// later, behind the barrier of the exchange between, which every thread
+// reaches after its reads of the line.
+//
+// Two element layouts: A, thread t < N/4 holds t + (N/4) m, m < 4; B, the
+// same for 2^a, and thread t < N/3 holds t + (N/3) m, m < 3, for 3 * 2^a.  A
+// transform goes A -> B with the radices 4 .. 4 (2) (3), or B -> A with the
+// radix 3 first, so that a factor 3 costs one pass (with four elements per
+// thread throughout, it would not divide, and with six every pass but one
+// would be of radix 2).  Threads past a layout's count idle through its passes.
+template <int N, int Ns, bool BA>
+__host__ __device__ constexpr int held_radix() {
+  if (N % 3 == 0 && (BA ? Ns == 1 : N / Ns == 3)) return 3;
+  return (N / Ns) % 4 == 0 ? 4 : 2;
+}
+// elements of a thread in a pass of radix R
+__host__ __device__ constexpr int held_ept(int R) { return R == 3 ? 3 : 4; }
+
+// twiddles a thread holds, and exchanges of a transform
+template <int N, bool BA, int Ns = 1>
+__host__ __device__ constexpr int held_count() {
+  if constexpr (Ns >= N) return 0;
+  else {
+    constexpr int R = held_radix<N, Ns, BA>();
+    return (Ns > 1 ? held_ept(R) / R * (R - 1) : 0) + held_count<N, BA, Ns * R>();
+  }
+}
+template <int N, bool BA, int Ns = 1>
+__host__ __device__ constexpr int exchange_count() {
+  if constexpr (Ns * held_radix<N, Ns, BA>() >= N) return 0;
+  else return 1 + exchange_count<N, BA, Ns * held_radix<N, Ns, BA>()>();
+}
+
+// held[0 .. held_count) of thread t from the full table
+template <int N, bool BA, int Ns = 1, int AT = 0, typename C>
+__device__ __forceinline__ void hold_twiddles(C* held, int t, const C* tw) {
+  if constexpr (Ns < N) {
+    constexpr int R = held_radix<N, Ns, BA>(), E = held_ept(R), T = N / E, B = E / R;
+    if constexpr (Ns > 1) {
+#pragma unroll
+      for (int b = 0; b < B; ++b)
+#pragma unroll
+        for (int r = 1; r < R; ++r) held[AT + b * (R - 1) + r - 1] = tw[N % 3 != 0 || t < T ? r * ((t + b * T) % Ns) * (N / (Ns * R)) : 0];
+    }
+    hold_twiddles<N, BA, Ns * R, AT + (Ns > 1 ? B * (R - 1) : 0)>(held, t, tw);
+  }
+}
+
+template <int N, bool BA, bool INV, int Ns, int AT, typename C>
+__device__ __forceinline__ void fft_held_rec(C* v, int t, C* la, C* lb, const C* held) {
+  constexpr int R = held_radix<N, Ns, BA>(), E = held_ept(R), T = N / E, B = E / R;
+  constexpr bool LAST = (Ns * R == N);
+  if (N % 3 != 0 || t < T) {
+    C x[B][R];
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) x[b][r] = v[b + r * B];
+      if constexpr (Ns > 1) {
+#pragma unroll
+        for (int r = 1; r < R; ++r) {
+          C w = held[AT + b * (R - 1) + r - 1];
+          if (INV) w.y = -w.y;
+          x[b][r] = cmul(x[b][r], w);
+        }
+      }
+      dft_small<R, INV>(x[b]);
+    }
+    if constexpr (LAST) {
+#pragma unroll
+      for (int b = 0; b < B; ++b)
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[b + r * B] = x[b][r];
+    } else {
+#pragma unroll
+      for (int b = 0; b < B; ++b) {
+        const int j = t + b * T;
+        const int k = (Ns == 1) ? 0 : (j % Ns);
+        const int base = (j / Ns) * Ns * R + k;
+#pragma unroll
+        for (int r = 0; r < R; ++r) la[lds_slot(base + r * Ns)] = x[b][r];
+      }
+    }
+  }
+  if constexpr (!LAST) {
+    __syncthreads();
+    constexpr int EN = held_ept(held_radix<N, Ns * R, BA>()), TN = N / EN;
+    if (N % 3 != 0 || t < TN) {
+#pragma unroll
+      for (int m = 0; m < EN; ++m) v[m] = la[lds_slot(t + TN * m)];
+    }
+    fft_held_rec<N, BA, INV, Ns * R, AT + (Ns > 1 ? B * (R - 1) : 0)>(v, t, lb, la, held);
+  }
+}
+// FFT of one line from layout A to B (BA: from B to A) through the exchange
+// lines la and lb (la first); swaps the two after an odd number of exchanges,
+// so that the caller's next transform may use them as they are.
+template <int N, bool BA, bool INV, typename C>
+__device__ __forceinline__ void fft_held(C* v, int t, C*& la, C*& lb, const C* held) {
+  fft_held_rec<N, BA, INV, 1, 0>(v, t, la, lb, held);
+  if constexpr (exchange_count<N, BA>() % 2 == 1) {
+    C* x = la;
+    la = lb;
+    lb = x;
+  }
+}
+
 }  // namespace tdse

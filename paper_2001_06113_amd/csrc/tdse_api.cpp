@@ -381,13 +381,13 @@ struct tdse_plan_s {
 
   // persistent Adams steps of a square 2D periodic FP64 plan
   // (persist2d_kernels.hip): per-step scalars, static column factors and the
-  // barrier words, at the end of the workspace
+  // timeout flag, at the end of the workspace
   bool persist = false;       // the plan qualifies
   bool persist_on = true;     // tdse_configure(TDSE_CFG_PERSISTENT)
   int persist_cap = -1;       // co-resident workgroups of the device (-1: not asked yet)
   std::vector<double> p2tab;
   std::vector<double2> p2S2;
-  size_t o_p2tab = 0, o_p2S2 = 0, o_p2bar = 0;
+  size_t o_p2tab = 0, o_p2S2 = 0, o_p2flag = 0;
   int64_t p2_oD2 = 0;
   bool p2_ph2 = false;
   static constexpr int P2_OSTEP = 16;
@@ -1732,14 +1732,14 @@ int persist2d_step(tdse_plan_s* p, int end, bool write_u) {
   a.tab = (const double*)(p->ws + p->o_p2tab);
   a.oD2 = p->p2_oD2;
   a.tile = (double2*)p->tmp(0);
-  a.xbuf = p->u(1 - p->ucur);   // the start-up's second physical buffer, free in the Adams phase
+  a.xrow = p->u(1 - p->ucur);   // the start-up's second physical buffer, free in the Adams phase
+  a.xcol = (double2*)(p->ws + p->o_dbuf);   // the diagnostics' mode array, used by a residual query only
   a.B = p->B();
   a.ring = (double2*)p->ring(0);
   a.S2 = (const double2*)(p->ws + p->o_p2S2);
   a.tw = (const double2*)p->tw(0, 1);
   a.uout = p->u(p->ucur);
-  a.bar = (unsigned*)(p->ws + p->o_p2bar);
-  a.flag = a.bar + 32 * 9;
+  a.flag = (unsigned*)(p->ws + p->o_p2flag);
   hipEvent_t e0 = nullptr, e1 = nullptr;
   const size_t first = p->ev_used;
   if (p->prof) {
@@ -1759,11 +1759,11 @@ int persist2d_step(tdse_plan_s* p, int end, bool write_u) {
     HIP_TRY(hipEventRecord(e1, p->stream));
     p->prof_marks.push_back({first, 4});
   }
-  // a grid barrier that timed out leaves the run unusable: report it now
+  // an exchange that timed out leaves the run unusable: report it now
   unsigned flag = 0;
   HIP_TRY(hipMemcpyAsync(&flag, a.flag, sizeof(flag), hipMemcpyDeviceToHost, p->stream));
   HIP_TRY(hipStreamSynchronize(p->stream));
-  if (flag) return fail(TDSE_EDEVICE, "persistent 2D kernel: a grid barrier timed out (co-resident grid not scheduled)");
+  if (flag) return fail(TDSE_EDEVICE, "persistent 2D kernel: an exchange timed out (co-resident grid not scheduled)");
   p->cur = end;
   return TDSE_OK;
 }
@@ -2960,7 +2960,7 @@ int tdse_plan(const tdse_problem_t* prob, tdse_plan_t* out) {
     build_persist2d(p);
     p->o_p2tab = off; off = align256(off + p->p2tab.size() * sizeof(double));
     p->o_p2S2 = off; off = align256(off + p->p2S2.size() * sizeof(double2));
-    p->o_p2bar = off; off = align256(off + P2_BAR_WORDS * sizeof(unsigned));
+    p->o_p2flag = off; off = align256(off + sizeof(unsigned));
   }
   if (p->dim == 1 && !split && run1d_supported(p->M2) && p->vkind != TDSE_V_SAMPLED) {
     p->run1d = true;
@@ -3073,11 +3073,18 @@ int tdse_step(tdse_plan_t p, int32_t k) {
 }
 
 namespace {
+// a stream under capture records kernel passes: a cooperative launch, and the
+// read of its timeout flag, cannot be captured
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return s && hipStreamIsCapturing(s, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
+}
+
 int step_range(tdse_plan_s* p, int k) {
   if (p->is_batch()) return batch_step(p, k);
   const int end = p->cur + k;
   if (p->run1d) return k > 0 ? run1d_step(p, end) : TDSE_OK;
-  if (p->persist && p->persist_on && end > p->ns + 1) {
+  if (p->persist && p->persist_on && end > p->ns + 1 && !capturing(p->stream)) {
     // start-up and the Adams start by the passes, the rest in one persistent launch
     for (int m = p->cur + 1; m <= p->ns + 1; ++m) {
       const int s = do_step(p, m, m == end);

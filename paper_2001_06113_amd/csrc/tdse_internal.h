@@ -297,9 +297,8 @@ hipError_t launch_run1d(const Run1DArgs& a, hipStream_t s, hipEvent_t e0 = nullp
 // phi_1(t_{m+1-j}), j = 1..7; tab[oD2 + i - 1] = phi_2(t_i) - phi_2(t_{i-1}).
 // S2 holds exp(-i k2^2 j dt), j = 1..n-1.  tile: the row-major tile of the
 // two-pass path (read by the first step, written by a launch that ends
-// before T); xbuf: an N x N complex128 exchange buffer (blocked layout).
-// bar: P2_BAR_WORDS words of barrier counters, flag: the timeout flag (both
-// reset by the launch).
+// before T); xrow, xcol: N x N complex128 exchange buffers (blocked layout),
+// filled with marks by the launch; flag: the timeout flag (reset by the launch).
 struct Persist2DArgs {
   int N, order, nsteps, m0, m1, mbase, ostep, nV, write_u, ph2, spin_limit;
   double dt, c0, scale;
@@ -309,16 +308,15 @@ struct Persist2DArgs {
   const double* tab;
   int64_t oD2;
   double2* tile;
-  double2* xbuf;
+  double2* xrow;
+  double2* xcol;
   double2* B;
   double2* ring;
   const double2* S2;
   const double2* tw;
   double2* uout;
-  unsigned* bar;
   unsigned* flag;
 };
-constexpr int P2_BAR_WORDS = 32 * 9 + 32;   // grid counter, eight XCD counters (128 bytes apart), flag
 bool persist2d_supported(int N);
 size_t persist2d_lds_bytes(int N, int order);
 int persist2d_capacity(int N, int order, bool ph2);   // co-resident workgroups the device holds
