@@ -14,8 +14,15 @@
 //                factors of step n+1;
 //   k_adj_sub    the phase factor of an order-2 sub-step (forward, or adjoint
 //                with its dJ/d(dphi) partial sums);
-//   k_adj_point  diagonal factors (alpha + beta V) or 1/(alpha + beta V) on the grid;
-//   k_adj_axpy, k_adj_copy2, k_adj_phase, k_adj_reduce, k_adj_to_A  (helpers).
+//   k_adj_axpy, k_adj_phase, k_adj_phases, k_adj_reduce, k_adj_to_A  (helpers);
+// and fused with the line FFTs on either side of them, as in the forward
+// passes (periodic_body.h), for the many steps of the sweeps:
+//   k_adj_row_am   forward FFT, an implicit Adams step, inverse FFT along axis 1;
+//   k_adj_row_sub  forward FFT, a sub-step's phase factor, inverse FFT along axis 1;
+//   k_adj_col      inverse FFT, a diagonal factor on the grid, forward FFT along axis 0.
+// A reverse step is one column and one row pass (it was five launches, with
+// Z, omega and the per-step phase table going through memory, and a gradient's
+// time was the host's launch rate: 8 instances of 200 steps 90 ms).
 #include <hip/hip_runtime.h>
 
 #include "periodic_body.h"
@@ -48,6 +55,21 @@ __global__ __launch_bounds__(256) void k_adj_phase(AdjPhase q) {
     }
     double s, c;
     sincos(-(k * k) * q.tau[e] + k * dphi, &s, &c);
+    q.ph[idx] = double2{c, s};
+  }
+}
+
+__global__ __launch_bounds__(256) void k_adj_phases(AdjPhases q) {
+  const int per = q.M1 + q.M2;
+  const int64_t total = (int64_t)q.ne * per;
+  for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (int64_t)gridDim.x * 256) {
+    const int e = (int)(idx / per);
+    const int kk = (int)(idx - (int64_t)e * per);
+    const double* l = q.list + 3 * (int64_t)e;
+    const bool row = kk < q.M1;
+    const double k = (double)(row ? signed_mode(kk, q.M1) : signed_mode(kk - q.M1, q.M2));
+    double s, c;
+    sincos(-(k * k) * l[0] + k * l[row ? 1 : 2], &s, &c);
     q.ph[idx] = double2{c, s};
   }
 }
@@ -149,44 +171,12 @@ __global__ __launch_bounds__(256) void k_adj_sub(AdjSub a) {
   if (a.mode == 0) block_partials<2>(val, a.part, a.nblk);
 }
 
-// out = s (alpha + beta V(t)) in   or   out = s in / (alpha + beta V(t));  optionally out +=
-__global__ __launch_bounds__(256) void k_adj_point(AdjPoint a) {
-  const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (g >= a.P) return;
-  double Vs = 0.0;
-  for (int r = 0; r < a.nV; ++r) Vs += a.fV[r] * a.V[r * a.vstride + g];
-  const double2 f = double2{a.ar + a.br * Vs, a.ai + a.bi * Vs};
-  const double2 x = a.in[g];
-  double2 y;
-  if (a.divide) {
-    const double den = f.x * f.x + f.y * f.y;
-    y = double2{(x.x * f.x + x.y * f.y) / den, (x.y * f.x - x.x * f.y) / den};
-  } else {
-    y = cmul(f, x);
-  }
-  y.x *= a.s;
-  y.y *= a.s;
-  if (a.accumulate) y = cadd(y, a.out[g]);
-  a.out[g] = y;
-}
-
 // out = x + c y (complex c)
 __global__ __launch_bounds__(256) void k_adj_axpy(int64_t P, const double2* x, const double2* y, double cr, double ci,
                                                   double2* out) {
   const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (g >= P) return;
   out[g] = cadd(x[g], cmul(double2{cr, ci}, y[g]));
-}
-
-// two copies of P entries in one launch: workgroups [0, nb) copy src0 into
-// dst0, the next nb copy src1 into dst1
-__global__ __launch_bounds__(256) void k_adj_copy2(int64_t P, int nblk, double2* dst0, const double2* src0,
-                                                   double2* dst1, const double2* src1) {
-  const bool second = (int)blockIdx.x >= nblk;
-  const int64_t g = (int64_t)(second ? blockIdx.x - nblk : blockIdx.x) * 256 + threadIdx.x;
-  if (g >= P) return;
-  if (second) dst1[g] = src1[g];
-  else dst0[g] = src0[g];
 }
 
 // red[r] = sum_b part[r * nblk + b], one workgroup per row
@@ -214,6 +204,263 @@ __global__ __launch_bounds__(256) void k_adj_to_A(const double* red, const int* 
   out[o] = s;
 }
 
+// ------------------------------------------------------------ fused passes
+
+// Block sums of NV values per thread (NT threads, a power of two) into
+// part[v * nblk + blockIdx.x], through LDS that holds NV * NT doubles.
+template <int NV, int NT>
+__device__ __forceinline__ void row_partials(const double (&val)[NV], double* buf, double* part, int nblk) {
+  const int t = threadIdx.x;
+  __syncthreads();   // the buffer held a transform's line
+#pragma unroll
+  for (int v = 0; v < NV; ++v) buf[v * NT + t] = val[v];
+  __syncthreads();
+  for (int s = NT / 2; s > 0; s >>= 1) {
+    if (t < s) {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) buf[v * NT + t] += buf[v * NT + t + s];
+    }
+    __syncthreads();
+  }
+  for (int v = t; v < NV; v += NT) part[(int64_t)v * nblk + blockIdx.x] = buf[v * NT];
+  __syncthreads();
+}
+
+// LDS of a fused row pass: the lines and twiddles of row_lds, or NV sums
+template <int N, int L, int NT, int NV>
+constexpr int adj_row_lds() {
+  const int a = row_lds<double2, N, L>::elems, b = (NV * NT + 1) / 2;
+  return a > b ? a : b;
+}
+
+// A row pass moves 18 entries of 16 bytes per mode (tile in and out, seven
+// adjoint states and a new one, seven history entries, B_n) and is bound by
+// that traffic on large grids, by latency on small ones.  PF: everything is
+// loaded before the forward FFT, 15 entries per element in registers, which
+// leaves one wave per SIMD; else term by term after it (four waves).
+template <int N, int L, int TL, bool PF>
+__global__ __launch_bounds__(L * TL) void k_adj_row_am(AdjRowAm a) {
+  constexpr int NT = L * TL, EPT = N / TL, NH = MAXH - 1, PITCH = row_lds<double2, N, L>::PITCH;
+  constexpr bool TWL = row_lds<double2, N, L>::TWL;
+  __shared__ double2 lds[adj_row_lds<N, L, NT, 2 * NH>()];
+  double2* twl = lds + L * PITCH;
+  const int tid = threadIdx.x, i = tid / TL, t = tid % TL;
+  const int i1 = blockIdx.x * L + i;
+  const bool active = i1 < a.M1;
+  const int per = a.M1 + a.M2, H = a.H;
+  const int64_t g0 = (int64_t)(active ? i1 : 0) * N + t;
+  const double2* __restrict__ prow = a.ph + (active ? i1 : 0);
+  const double2* __restrict__ pcol = a.ph + a.M1 + t;
+  if constexpr (TWL) {
+    for (int q = tid; q < N; q += NT) twl[q] = a.tw[q];
+  }
+  double2 v[EPT], b1[EPT], om[EPT];
+  double2 Bn[PF ? EPT : 1], Wr[PF ? NH : 1][EPT], br[PF ? NH - 1 : 1][EPT];
+#pragma unroll
+  for (int m = 0; m < EPT; ++m) {
+    v[m] = active ? a.src[g0 + TL * m] : double2{0.0, 0.0};
+    b1[m] = active && a.slot_b1 >= 0 ? a.beta[a.slot_b1 * a.P + g0 + TL * m] : double2{0.0, 0.0};
+  }
+  if constexpr (PF) {
+    if (active && a.has_grad) {
+#pragma unroll
+      for (int m = 0; m < EPT; ++m) Bn[m] = a.Bn[g0 + TL * m];
+#pragma unroll
+      for (int j = 1; j <= NH; ++j) {
+        if (j <= H) {
+#pragma unroll
+          for (int m = 0; m < EPT; ++m) Wr[j - 1][m] = a.Wx[j][g0 + TL * m];
+        }
+      }
+    }
+#pragma unroll
+    for (int j = 2; j <= NH; ++j) {
+      if (active && j <= H && a.slot_bj[j] >= 0) {
+#pragma unroll
+        for (int m = 0; m < EPT; ++m) br[j - 2][m] = a.beta[a.slot_bj[j] * a.P + g0 + TL * m];
+      }
+    }
+  }
+  if constexpr (TWL) __syncthreads();
+  const double2* tw = TWL ? twl : a.tw;
+  double2* myline = &lds[i * PITCH];
+  fft_regs<N, TL, false>(v, t, myline, tw);
+  double val[2 * NH];
+#pragma unroll
+  for (int j = 0; j < 2 * NH; ++j) val[j] = 0.0;
+#pragma unroll
+  for (int m = 0; m < EPT; ++m) om[m] = double2{0.0, 0.0};
+  if (active) {
+    const double k1 = (double)signed_mode(i1, a.M1);
+    // beta_n = conj(E^(1)_{n+1}) beta_{n+1} + Z
+    {
+      const double2 R = prow[0];
+#pragma unroll
+      for (int m = 0; m < EPT; ++m) {
+        v[m] = cadd(cmul(conjd(cmul(R, pcol[TL * m])), b1[m]), v[m]);
+        a.beta[a.slot_bn * a.P + g0 + TL * m] = v[m];
+      }
+    }
+    if (a.has_grad) {
+      // B_{n+1} = sum_j E^(j)_{n+1} x_j, x_1 = B_n - i c_1 What_n, x_j = -i c_j What_{n+1-j};
+      // dJ/dtheta = Re(conj(beta_{n+1}) i E x), weighted by k_a
+#pragma unroll
+      for (int j = 1; j <= NH; ++j) {
+        if (j <= H) {
+          const double2 R = prow[(j - 1) * per];
+          const double2* __restrict__ W = a.Wx[j];
+          double s1 = 0.0, s2 = 0.0;
+#pragma unroll
+          for (int m = 0; m < EPT; ++m) {
+            const double2 w = PF ? Wr[PF ? j - 1 : 0][m] : W[g0 + TL * m];
+            double2 x = double2{a.cx[j] * w.y, -a.cx[j] * w.x};
+            if (j == 1) x = cadd(x, PF ? Bn[PF ? m : 0] : a.Bn[g0 + TL * m]);
+            const double2 Ex = cmul(cmul(R, pcol[(j - 1) * per + TL * m]), x);
+            const double term = b1[m].y * Ex.x - b1[m].x * Ex.y;
+            s1 += term;
+            s2 += (double)signed_mode(t + TL * m, N) * term;
+          }
+          val[2 * (j - 1)] = k1 * s1;
+          val[2 * (j - 1) + 1] = s2;
+        }
+      }
+    }
+    // omega_{n-1} = sum_j i w_j conj(E^(j)_{n-1+j}) beta_{n-1+j}
+#pragma unroll
+    for (int j = 1; j <= NH; ++j) {
+      if (j <= H && a.wj[j] != 0.0 && (j == 1 || a.slot_bj[j] >= 0)) {
+        const double2 R = prow[(H + j - 1) * per];
+        const double2* __restrict__ b = a.beta + (int64_t)(j == 1 ? 0 : a.slot_bj[j]) * a.P;
+#pragma unroll
+        for (int m = 0; m < EPT; ++m) {
+          const double2 bb = j == 1 ? v[m] : PF ? br[PF ? j - 2 : 0][m] : b[g0 + TL * m];
+          const double2 z = cmul(conjd(cmul(R, pcol[(H + j - 1) * per + TL * m])), bb);
+          om[m] = cadd(om[m], double2{-a.wj[j] * z.y, a.wj[j] * z.x});
+        }
+      }
+    }
+    if (a.omega) {
+#pragma unroll
+      for (int m = 0; m < EPT; ++m) a.omega[g0 + TL * m] = om[m];
+    }
+  }
+  if (a.has_grad) {
+    row_partials<2 * NH, NT>(val, (double*)lds, a.part, a.nblk);
+    if constexpr (TWL) {   // the sums took the twiddles' place
+      for (int q = tid; q < N; q += NT) twl[q] = a.tw[q];
+      __syncthreads();
+    }
+  }
+  fft_regs<N, TL, true>(om, t, myline, tw);
+  if (active) {
+#pragma unroll
+    for (int m = 0; m < EPT; ++m) a.dst[g0 + TL * m] = om[m];
+  }
+}
+
+template <int N, int L, int TL>
+__global__ __launch_bounds__(L * TL) void k_adj_row_sub(AdjRowSub a) {
+  constexpr int NT = L * TL, EPT = N / TL, PITCH = row_lds<double2, N, L>::PITCH;
+  constexpr bool TWL = row_lds<double2, N, L>::TWL;
+  __shared__ double2 lds[row_lds<double2, N, L>::elems];
+  __shared__ double sums[2 * NT];
+  double2* twl = lds + L * PITCH;
+  const int tid = threadIdx.x, i = tid / TL, t = tid % TL;
+  const int i1 = blockIdx.x * L + i;
+  const bool active = i1 < a.M1;
+  const int64_t g0 = (int64_t)(active ? i1 : 0) * N + t;
+  const double2 R = a.ph[active ? i1 : 0];
+  const double2* __restrict__ pcol = a.ph + a.M1 + t;
+  if constexpr (TWL) {
+    for (int q = tid; q < N; q += NT) twl[q] = a.tw[q];
+  }
+  double2 v[EPT], G[EPT];
+#pragma unroll
+  for (int m = 0; m < EPT; ++m) {
+    v[m] = active ? a.src[g0 + TL * m] : double2{0.0, 0.0};
+    G[m] = active && a.rev ? a.G[g0 + TL * m] : double2{0.0, 0.0};
+  }
+  if constexpr (TWL) __syncthreads();
+  const double2* tw = TWL ? twl : a.tw;
+  double2* myline = &lds[i * PITCH];
+  fft_regs<N, TL, false>(v, t, myline, tw);
+  if (a.rev) {
+    double val[2] = {0.0, 0.0};
+#pragma unroll
+    for (int m = 0; m < EPT; ++m) {
+      const double2 E = cmul(R, pcol[TL * m]);
+      const double2 Ex = cmul(E, G[m]);
+      const double term = v[m].y * Ex.x - v[m].x * Ex.y;   // Re(conj(y) i E g)
+      val[0] += term;
+      val[1] += (double)signed_mode(t + TL * m, N) * term;
+      v[m] = cmul(conjd(E), v[m]);
+    }
+    val[0] *= (double)signed_mode(active ? i1 : 0, a.M1);
+    row_partials<2, NT>(val, sums, a.part, a.nblk);
+  } else {
+#pragma unroll
+    for (int m = 0; m < EPT; ++m) {
+      if (active) a.G[g0 + TL * m] = v[m];
+      v[m] = cmul(cmul(R, pcol[TL * m]), v[m]);
+    }
+    if (!a.inv) return;
+  }
+  fft_regs<N, TL, true>(v, t, myline, tw);
+  if (active) {
+#pragma unroll
+    for (int m = 0; m < EPT; ++m) a.dst[g0 + TL * m] = v[m];
+  }
+}
+
+template <int N, int LPW, int TL>
+__global__ __launch_bounds__(LPW * TL) void k_adj_col(AdjCol a) {
+  constexpr int NT = LPW * TL, EPT = N / TL, PITCH = col_lds<double2, N, LPW>::PITCH;
+  constexpr bool TWL = col_lds<double2, N, LPW>::TWL;
+  __shared__ double2 lds[col_lds<double2, N, LPW>::elems];
+  double2* twl = lds + LPW * PITCH;
+  const int tid = threadIdx.x, i = tid % LPW, t = tid / LPW;
+  const int tile = xcd_tile<(16 / LPW > 1 ? 16 / LPW : 1)>(blockIdx.x, gridDim.x);
+  const int line = tile * LPW + i;
+  const bool active = line < a.M2;
+  const int64_t g0 = active ? (int64_t)t * a.M2 + line : 0, gs = active ? (int64_t)TL * a.M2 : 0;
+  if constexpr (TWL) {
+    for (int q = tid; q < N; q += NT) twl[q] = a.tw[q];
+  }
+  double2 v[EPT];
+  const double2* __restrict__ x = a.src ? a.src : a.xin;
+#pragma unroll
+  for (int m = 0; m < EPT; ++m) v[m] = x[g0 + m * gs];
+  double Vs[EPT];
+#pragma unroll
+  for (int m = 0; m < EPT; ++m) Vs[m] = 0.0;
+  for (int r = 0; r < a.nV; ++r) {
+#pragma unroll
+    for (int m = 0; m < EPT; ++m) Vs[m] += a.fV[r] * a.V[r * a.vstride + g0 + m * gs];
+  }
+  if constexpr (TWL) __syncthreads();
+  const double2* tw = TWL ? twl : a.tw;
+  double2* myline = &lds[i * PITCH];
+  if (a.src) fft_regs<N, TL, true>(v, t, myline, tw);
+#pragma unroll
+  for (int m = 0; m < EPT; ++m) {
+    const double q = a.di * Vs[m], iv = a.s / (1.0 + q * q);
+    // s (a + b V) / (1 + i q) = s (a + b V) (1 - i q) / (1 + q^2)
+    const double2 f = cmul(double2{a.ar + a.br * Vs[m], a.ai + a.bi * Vs[m]}, double2{iv, -q * iv});
+    v[m] = cmul(f, v[m]);
+    if (a.yout && active) {
+      double2 y = v[m];
+      if (a.accumulate) y = cadd(y, a.yout[g0 + m * gs]);
+      a.yout[g0 + m * gs] = y;
+    }
+  }
+  if (!a.dst) return;
+  fft_regs<N, TL, false>(v, t, myline, tw);
+  if (active) {
+#pragma unroll
+    for (int m = 0; m < EPT; ++m) a.dst[g0 + m * gs] = v[m];
+  }
+}
+
 static int nb(int64_t n) { return (int)((n + 255) / 256); }
 
 hipError_t launch_adj_phase(const AdjPhase& q, hipStream_t s) {
@@ -224,24 +471,72 @@ hipError_t launch_adj_am(const AdjAm& a, hipStream_t s) {
   hipLaunchKernelGGL(k_adj_am, dim3(a.nblk), dim3(256), 0, s, a);
   return hipGetLastError();
 }
-hipError_t launch_adj_sub(const AdjSub& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_adj_sub, dim3(a.nblk), dim3(256), 0, s, a);
+hipError_t launch_adj_phases(const AdjPhases& q, hipStream_t s) {
+  const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(((int64_t)q.ne * (q.M1 + q.M2) + 255) / 256, 4096));
+  hipLaunchKernelGGL(k_adj_phases, dim3((unsigned)blocks), dim3(256), 0, s, q);
   return hipGetLastError();
 }
-hipError_t launch_adj_point(const AdjPoint& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_adj_point, dim3(nb(a.P)), dim3(256), 0, s, a);
+int adj_row_blocks(int M1, int M2) {
+  switch (M2) {
+#define X(n) case n: return (M1 + row_lpw(n) - 1) / row_lpw(n);
+    TDSE_LINE_SIZES(X)
+#undef X
+    default:
+      return 0;
+  }
+}
+hipError_t launch_adj_row_am(const AdjRowAm& a, hipStream_t s) {
+  // one wave per SIMD is all there is up to 2^18 modes (1024 waves of four
+  // elements a lane): whole adjoints of 193 steps 13.95 -> 13.1 ms at 256^2,
+  // 13.2 -> 12.3 at 1 x 1024, no difference at 512^2; beyond, the lost
+  // occupancy costs (30.6 -> 34.4 ms at 512 x 1024, 49.7 -> 60.8 at 1024^2)
+  const bool few = a.P < (1 << 18);
+  const dim3 grid((unsigned)adj_row_blocks(a.M1, a.M2));
+  switch (a.M2) {
+#define X(n)                                                                                              \
+  case n: {                                                                                               \
+    constexpr bool PF = row_ept(n) <= 4;                                                                  \
+    const dim3 block(row_lpw(n) * row_tl(n));                                                             \
+    if (PF && few) hipLaunchKernelGGL((k_adj_row_am<n, row_lpw(n), row_tl(n), PF>), grid, block, 0, s, a); \
+    else hipLaunchKernelGGL((k_adj_row_am<n, row_lpw(n), row_tl(n), false>), grid, block, 0, s, a);        \
+    break;                                                                                                \
+  }
+    TDSE_LINE_SIZES(X)
+#undef X
+    default:
+      return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+hipError_t launch_adj_row_sub(const AdjRowSub& a, hipStream_t s) {
+  const dim3 grid((unsigned)adj_row_blocks(a.M1, a.M2));
+  switch (a.M2) {
+#define X(n)   case n: hipLaunchKernelGGL((k_adj_row_sub<n, row_lpw(n), row_tl(n)>), grid, dim3(row_lpw(n) * row_tl(n)), 0, s, a); break;
+    TDSE_LINE_SIZES(X)
+#undef X
+    default:
+      return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+hipError_t launch_adj_col(const AdjCol& a, hipStream_t s) {
+  switch (a.M1) {
+#define X(n)                                                                                                         case n:                                                                                                              hipLaunchKernelGGL((k_adj_col<n, col_lpw(n), col_tl(n)>), dim3((unsigned)((a.M2 + col_lpw(n) - 1) / col_lpw(n))),                        dim3(col_lpw(n) * col_tl(n)), 0, s, a);                                                         break;
+    X(1)
+    TDSE_LINE_SIZES(X)
+#undef X
+    default:
+      return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+hipError_t launch_adj_sub(const AdjSub& a, hipStream_t s) {
+  hipLaunchKernelGGL(k_adj_sub, dim3(a.nblk), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 hipError_t launch_adj_axpy(int64_t P, const double2* x, const double2* y, double cr, double ci, double2* out,
                            hipStream_t s) {
   hipLaunchKernelGGL(k_adj_axpy, dim3(nb(P)), dim3(256), 0, s, P, x, y, cr, ci, out);
-  return hipGetLastError();
-}
-hipError_t launch_adj_copy2(int64_t P, double2* dst0, const double2* src0, double2* dst1, const double2* src1,
-                            hipStream_t s) {
-  if (P <= 0) return hipSuccess;
-  const int n = nb(P);
-  hipLaunchKernelGGL(k_adj_copy2, dim3(2 * n), dim3(256), 0, s, P, n, dst0, src0, dst1, src1);
   return hipGetLastError();
 }
 hipError_t launch_adj_reduce(const double* part, double* red, int nrows, int nblk, hipStream_t s) {

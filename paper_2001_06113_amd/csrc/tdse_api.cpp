@@ -525,6 +525,7 @@ LineArgs base_args(const tdse_plan_s* p, int g) {
   a.ring = p->ring(g);
   a.ring_stride = p->P;
   a.Bm = p->B();
+  a.Bw = p->B();
   a.ph = p->ph();
   a.ph32 = p->ph32();
   a.slot_w = -1;
@@ -807,6 +808,8 @@ int op_fp64_output(tdse_plan_s* p, int m) {
   return launch(p, g, true, c);
 }
 
+int am_passes(tdse_plan_s* p, int m, bool write_u, void* ring, int sw, int slots, double2* Br, double2* Bw);
+
 // Implicit Adams step m (eq. (uadamsk)), stage 1.
 int op_am_step(tdse_plan_s* p, int m, bool write_u) {
   const int n = p->order, g = p->split() ? 1 : 0;
@@ -816,6 +819,13 @@ int op_am_step(tdse_plan_s* p, int m, bool write_u) {
     write_u = false;
   }
   if (m == p->nsteps && !write_u && p->split()) return TDSE_OK;
+  return am_passes(p, m, write_u, p->ring(g), m % (n - 1), n - 1, p->B(), p->B());
+}
+
+// The two passes of an Adams step: history entries in `ring` (What_m into
+// slot sw, What_{m-i} in slot sw - i modulo `slots`), the state from Br into Bw.
+int am_passes(tdse_plan_s* p, int m, bool write_u, void* ring, int sw, int slots, double2* Br, double2* Bw) {
+  const int n = p->order, g = p->split() ? 1 : 0;
   LineArgs c = base_args(p, g);
   col_geom(p, g, c);
   c.mode = C_SOLVE;
@@ -835,10 +845,13 @@ int op_am_step(tdse_plan_s* p, int m, bool write_u) {
   r.dst = p->tmp(g);
   r.nh = n - 1;
   r.c0 = p->mu[0] * p->dt;
-  r.slot_w = m % (n - 1);
+  r.ring = ring;
+  r.Bm = Br;
+  r.Bw = Bw;
+  r.slot_w = sw;
   for (int j = 1; j <= n - 1; ++j) {
     r.ch[j] = p->dt * p->mu[j];
-    r.slot_r[j] = ((m + 1 - j) % (n - 1) + (n - 1)) % (n - 1);
+    r.slot_r[j] = ((sw + 1 - j) % slots + slots) % slots;
   }
   // no field component along the last axis: its factors of E^(j) are the
   // j-th powers of E^(1)'s
@@ -2290,7 +2303,9 @@ struct AdjLayout {
   int K = 1, C = 0, H = 1, nblk = 1, L = 1, nsub_max = 1;
   int64_t P = 1, rows = 0;
   size_t o_ustore = 0, o_ck = 0, o_bseg = 0, o_wwin = 0, o_beta = 0, o_omega = 0, o_omsu = 0, o_Z = 0;
-  size_t o_phys[3] = {0, 0, 0}, o_modes[2] = {0, 0}, o_bvirt = 0, o_subv = 0, o_subg = 0, o_ph = 0;
+  size_t o_phys[3] = {0, 0, 0}, o_modes[2] = {0, 0}, o_bvirt = 0, o_subg = 0, o_ph = 0, o_plist = 0, o_ptab = 0;
+  int64_t entries = 0;   // phase entries of the fused passes: Adams steps, then start-up sub-steps
+  int chunk = 1;         // reverse steps whose phase table is built at once
   size_t o_part = 0, o_red = 0, o_csr = 0, o_gA = 0, csr_bytes = 0, total = 0;
   size_t ck_bytes = 0;
 };
@@ -2327,9 +2342,13 @@ AdjLayout adj_layout(const tdse_plan_s* p, int K) {
   for (int i = 0; i < 3; ++i) L.o_phys[i] = take(a);
   for (int i = 0; i < 2; ++i) L.o_modes[i] = take(a);
   L.o_bvirt = take(a);
-  L.o_subv = take((size_t)L.nsub_max * a);
   L.o_subg = take((size_t)L.nsub_max * a);
   L.o_ph = take((size_t)ADJ_PH * (p->M1 + p->M2) * sizeof(double2));
+  const int64_t nsub_all = (1 << L.L) - 1;
+  L.entries = (int64_t)(N - ns) * 2 * L.H + (int64_t)ns * nsub_all;
+  L.chunk = std::max(1, std::min(N - ns, 32));
+  L.o_plist = take((size_t)L.entries * 3 * sizeof(double));
+  L.o_ptab = take((size_t)std::max<int64_t>((int64_t)L.chunk * 2 * L.H, nsub_all) * (p->M1 + p->M2) * sizeof(double2));
   L.o_part = take((size_t)L.rows * L.nblk * sizeof(double));
   L.o_red = take((size_t)L.rows * sizeof(double));
   // field-gradient map: per sample (m, component) the rows that overlap it
@@ -2380,52 +2399,6 @@ int adj_fft2(tdse_plan_s* p, const double2* src, double2* dst, double scale, dou
   r.src = p->tmp(0);
   r.fdst = dst;
   return launch(p, 0, false, r);
-}
-
-// unnormalized inverse FFT of modes src, then / (1 + i csolve V(t)) into dst (physical);
-// with zdst, the column pass's forward transform of V u / P lands in tmp and a
-// row FFT of it in zdst (G^H when csolve = -mu_0 dt)
-int adj_ifft2(tdse_plan_s* p, const double2* src, double2* dst, double csolve, double t, double2* zdst = nullptr) {
-  LineArgs r = base_args(p, 0);
-  row_geom(p, 0, r);
-  r.mode = R_INV;
-  r.Bm = (double2*)src;
-  r.dst = p->tmp(0);
-  int s = launch(p, 0, false, r);
-  if (s) return s;
-  LineArgs c = base_args(p, 0);
-  col_geom(p, 0, c);
-  c.mode = C_SOLVE;
-  c.src = p->tmp(0);
-  c.dst = p->tmp(0);
-  c.csolve = csolve;
-  p->fV_at(t, c.fV);
-  c.uout = dst;   // may be null
-  s = launch(p, 0, true, c);
-  if (s || !zdst) return s;
-  LineArgs f = base_args(p, 0);
-  row_geom(p, 0, f);
-  f.mode = R_FWD;
-  f.src = p->tmp(0);
-  f.fdst = zdst;
-  return launch(p, 0, false, f);
-}
-
-int adj_point(tdse_plan_s* p, const double2* in, double2* out, double t, double ar, double ai, double br, double bi,
-              double sc, bool divide, bool acc) {
-  AdjPoint a;
-  std::memset(&a, 0, sizeof(a));
-  a.P = p->P;
-  a.in = in;
-  a.out = out;
-  a.V = (const double*)p->V(0);
-  a.nV = p->nV;
-  a.vstride = p->P;
-  p->fV_at(t, a.fV);
-  a.ar = ar; a.ai = ai; a.br = br; a.bi = bi; a.s = sc;
-  a.divide = divide;
-  a.accumulate = acc;
-  return adj_err(launch_adj_point(a, p->stream), "adjoint pointwise");
 }
 
 // phase entries e: E over [tb - tau, tb]
@@ -2502,20 +2475,42 @@ int adjoint_single(tdse_plan_s* p, char* w, size_t wbytes, int K, const void* u0
     if (!s) s = adj_copy(p, R.at(L.o_ustore, m), p->u(p->ucur), a);
   }
   if (s) return done(s);
+  // a checkpoint: B, then What_{sc-H} .. What_{sc-1} in that order
   auto ck = [&](int c) { return w + L.o_ck + (size_t)c * L.ck_bytes; };
+  // (oldest first: the ring's H slots from slot sc mod H on, and round)
+  auto save_state = [&](int sc, double2* B, double2* W) {
+    int e = adj_copy(p, B, p->B(), a);
+    const int k = sc % H;
+    if (!e) e = adj_copy(p, W, (char*)p->ring(0) + (size_t)k * a, (size_t)(H - k) * a);
+    if (!e && k) e = adj_copy(p, W + (int64_t)(H - k) * p->P, p->ring(0), (size_t)k * a);
+    return e;
+  };
+  // Adams step n of the segment that starts at sc, B_n and What_n left in the
+  // segment's store (bseg, wwin: window slot 0 holds What_{sc-H}).  The last
+  // B of a segment goes to the plan's own array.
+  double2* const bseg = R.at(L.o_bseg);
+  double2* const wwin = R.at(L.o_wwin);
+  auto seg_step = [&](int n, int sc, int ec) {
+    const int i = n - sc;
+    return am_passes(p, n, false, wwin, i + H, L.K + H, bseg + (int64_t)i * p->P,
+                     n < ec ? bseg + (int64_t)(i + 1) * p->P : p->B());
+  };
+  const int sc_last = ns + 1 + (L.C - 1) * L.K;
   if (N > ns) {
     if (ns == 0) s = op_history(p, 0);
     if (!s) s = op_am_init(p);
-    if (!s) s = adj_copy(p, ck(0), p->B(), a);
-    if (!s) s = adj_copy(p, ck(0) + a, p->ring(0), (size_t)H * a);
     for (int m = ns + 1; m <= N - 1 && !s; ++m) {
-      s = op_am_step(p, m, false);
-      const int sidx = m + 1 - (ns + 1);
-      if (!s && sidx % L.K == 0 && sidx / L.K < L.C) {
-        s = adj_copy(p, ck(sidx / L.K), p->B(), a);
-        if (!s) s = adj_copy(p, ck(sidx / L.K) + a, p->ring(0), (size_t)H * a);
+      const int sidx = m - (ns + 1);
+      // the newest segment needs no checkpoint: its steps go to the store at once
+      if (m >= sc_last) {
+        if (m == sc_last) s = save_state(m, bseg, wwin);
+        if (!s) s = seg_step(m, sc_last, N - 1);
+        continue;
       }
+      if (sidx % L.K == 0) s = save_state(m, (double2*)ck(sidx / L.K), (double2*)(ck(sidx / L.K) + a));
+      if (!s) s = op_am_step(p, m, false);
     }
+    if (!s && N - 1 < sc_last) s = save_state(sc_last, bseg, wwin);   // no Adams step before T
   }
   if (s) return done(s);
   // ---- reverse sweep
@@ -2571,45 +2566,146 @@ int adjoint_single(tdse_plan_s* p, char* w, size_t wbytes, int K, const void* u0
     return adj_err(launch_adj_am(A, st), "adjoint Adams step");
   };
   auto omsu = [&](int m) { return R.at(L.o_omsu, m - (ns + 1 - H)); };
+  // ---- phase entries of the fused passes, uploaded once: reverse step n =
+  // ns+1..N at (n - ns - 1) 2H: E^(j) over [t_{n+1-j}, t_{n+1}], then over
+  // [t_{n-1}, t_{n-1+j}]; sub-step k of level l of start-up step m after them
+  std::vector<double> list;
+  list.reserve((size_t)L.entries * 3);
+  auto entry = [&](double tb, double tau) {
+    double pb[3], pa[3];
+    p->tf.phi(tb, pb);
+    p->tf.phi(tb - tau, pa);
+    list.push_back(tau);
+    list.push_back(p->dim == 2 ? pb[0] - pa[0] : 0.0);
+    list.push_back(p->dim == 2 ? pb[1] - pa[1] : pb[0] - pa[0]);
+  };
+  for (int n = ns + 1; n <= N; ++n) {
+    for (int j = 1; j <= H; ++j) entry((n + 1) * dt, j * dt);
+    for (int j = 1; j <= H; ++j) entry((n - 1 + j) * dt, j * dt);
+  }
+  for (int m = 1; m <= ns; ++m)
+    for (int l = 0; l < L.L; ++l)
+      for (int k = 0; k < (1 << l); ++k) {
+        const double d = dt / (1 << l);
+        entry((m - 1) * dt + k * d + d, d);
+      }
+  s = adj_err(hipMemcpyAsync(w + L.o_plist, list.data(), list.size() * sizeof(double), hipMemcpyHostToDevice, st),
+              "adjoint phases");
+  if (!s) s = adj_err(hipStreamSynchronize(st), "adjoint sync");   // list is host memory of this call
+  if (s) return done(s);
+  const int per = p->M1 + p->M2;
+  double2* const ptab = R.at(0) + (int64_t)(L.o_ptab / sizeof(double2));
+  auto build_phases = [&](int64_t first, int count) {
+    AdjPhases q;
+    q.M1 = p->M1;
+    q.M2 = p->M2;
+    q.ne = count;
+    q.list = (const double*)(w + L.o_plist) + 3 * first;
+    q.ph = ptab;
+    return adj_err(launch_adj_phases(q, st), "adjoint phases");
+  };
+  double2* const rtile = R.at(L.o_Z);   // the reverse sweep's tile
+  // a fused column pass at time t: x from the tile or from xin, times
+  // s (ar + (br + i bi) V) / (1 + i di V), into yout and (fwd) transformed into the tile
+  auto col_op = [&](const double2* xin, double2* yout, bool accumulate, bool fwd, double t, double ar, double br,
+                    double bi, double di, double sc) {
+    AdjCol q;
+    std::memset(&q, 0, sizeof(q));
+    q.M1 = p->M1;
+    q.M2 = p->M2;
+    q.src = xin ? nullptr : rtile;
+    q.xin = xin;
+    q.dst = fwd ? rtile : nullptr;
+    q.yout = yout;
+    q.accumulate = accumulate;
+    q.tw = (const double2*)p->tw(0, 0);
+    q.V = (const double*)p->V(0);
+    q.nV = p->nV;
+    q.vstride = p->P;
+    p->fV_at(t, q.fV);
+    q.ar = ar;
+    q.br = br;
+    q.bi = bi;
+    q.di = di;
+    q.s = sc;
+    return adj_err(launch_adj_col(q, st), "adjoint column pass");
+  };
+  // inverse FFT along axis 1 of modes into the reverse tile
+  auto row_inverse = [&](const double2* modes) {
+    LineArgs r = base_args(p, 0);
+    row_geom(p, 0, r);
+    r.mode = R_INV;
+    r.Bm = (double2*)modes;
+    r.dst = rtile;
+    return launch(p, 0, false, r);
+  };
+  int tab_lo = 1, tab_hi = 0;   // reverse steps whose phase table is built
+  // the fused row pass of reverse step n: Z from the tile, beta_n, the partials
+  // of step n+1 (grad), omega_{n-1} into the tile (and out)
+  auto rev_row = [&](int n, bool grad, const double2* Bn, const double2* const* Wx, double2* out) -> int {
+    if (n < tab_lo || n > tab_hi) {
+      tab_hi = n;
+      tab_lo = std::max(ns + 1, n - L.chunk + 1);
+      const int e = build_phases((int64_t)(tab_lo - ns - 1) * 2 * H, (tab_hi - tab_lo + 1) * 2 * H);
+      if (e) return e;
+    }
+    AdjRowAm q;
+    std::memset(&q, 0, sizeof(q));
+    q.M1 = p->M1;
+    q.M2 = p->M2;
+    q.H = H;
+    q.P = p->P;
+    q.src = rtile;
+    q.dst = rtile;
+    q.tw = (const double2*)p->tw(0, 1);
+    q.ph = ptab + (int64_t)(n - tab_lo) * 2 * H * per;
+    q.beta = beta;
+    q.slot_b1 = bslot(n + 1);
+    q.slot_bn = n % 8;
+    q.omega = out;
+    for (int j = 2; j <= H; ++j) q.slot_bj[j] = bslot(n - 1 + j);
+    for (int j = 1; j <= H; ++j) q.wj[j] = n - 1 + j <= N ? dt * cfac(n - 1, j) : 0.0;
+    q.has_grad = grad;
+    q.nblk = L.nblk;
+    if (grad) {
+      const int64_t g0 = (int64_t)(n - ns) * 2 * MAXH;
+      q.part = (double*)(w + L.o_part) + g0 * L.nblk;
+      q.Bn = Bn;
+      for (int j = 1; j <= H; ++j) {
+        q.Wx[j] = Wx[j];
+        q.cx[j] = j == 1 ? dt * (mu[0] + mu[1]) : dt * mu[j];
+        for (int ax = 0; ax < 2; ++ax) R.rows[g0 + 2 * (j - 1) + ax] = AdjRun::Row{(n + 1 - j) * dt, (n + 1) * dt, ax};
+      }
+    }
+    return adj_err(launch_adj_row_am(q, st), "adjoint Adams step");
+  };
   if (N > ns) {
-    // beta_N = F^-H conj(S_N) lam = fft2(lam / (1 - i mu_0 dt V(t_N)))
-    s = adj_point(p, R.at(L.o_phys[2]), R.at(L.o_phys[0]), N * dt, 1.0, 0.0, 0.0, -mu[0] * dt, 1.0, true, false);
-    if (!s) s = adj_fft2(p, R.at(L.o_phys[0]), beta + (int64_t)(N % 8) * p->P, 1.0, 1.0, 0.0, 0.0, 0.0, N * dt);
-    if (!s) s = am_iter(N, 2, false, nullptr, nullptr, R.at(L.o_omega));
-    if (!s && N - 1 <= ns) s = adj_copy(p, omsu(N - 1), R.at(L.o_omega), a);
+    // beta_N = F^-H conj(S_N) lam = fft2(lam / (1 - i mu_0 dt V(t_N))), and omega_{N-1}
+    s = col_op(R.at(L.o_phys[2]), nullptr, false, true, N * dt, 1.0, 0.0, 0.0, -mu[0] * dt, 1.0);
+    if (!s) s = rev_row(N, false, nullptr, nullptr, N - 1 <= ns ? omsu(N - 1) : nullptr);
     for (int c = L.C - 1; c >= 0 && !s; --c) {
       const int sc = ns + 1 + c * L.K;
       const int ec = std::min(sc + L.K - 1, N - 1);
       const int w0 = sc - H;   // window slot 0 holds What_{sc-H}
-      s = adj_copy(p, p->B(), ck(c), a);
-      if (!s) s = adj_copy(p, p->ring(0), ck(c) + a, (size_t)H * a);
-      if (!s) {
-        LineArgs r = base_args(p, 0);
-        row_geom(p, 0, r);
-        r.mode = R_INV;
-        r.dst = p->tmp(0);
-        s = launch(p, 0, false, r);
+      if (c < L.C - 1) {
+        s = adj_copy(p, bseg, ck(c), a);
+        if (!s) s = adj_copy(p, wwin, ck(c) + a, (size_t)H * a);
+        if (!s) {
+          LineArgs r = base_args(p, 0);
+          row_geom(p, 0, r);
+          r.mode = R_INV;
+          r.Bm = bseg;
+          r.dst = p->tmp(0);
+          s = launch(p, 0, false, r);
+        }
+        for (int n = sc; n <= ec && !s; ++n) s = seg_step(n, sc, ec);
       }
-      for (int i = std::max(w0, 0); i < sc && !s; ++i) s = adj_copy(p, R.at(L.o_wwin, i - w0), (char*)p->ring(0) + (size_t)(i % H) * a, a);
-      // B_n into its segment slot before step n; What_{n-1}, which step n-1
-      // left in the ring, into the window in the same launch
-      auto ring_slot = [&](int m) { return (const double2*)((char*)p->ring(0) + (size_t)(m % H) * a); };
-      for (int n = sc; n <= ec && !s; ++n) {
-        if (n == sc) s = adj_copy(p, R.at(L.o_bseg, 0), p->B(), a);
-        else
-          s = adj_err(launch_adj_copy2(p->P, R.at(L.o_bseg, n - sc), p->B(), R.at(L.o_wwin, n - 1 - w0),
-                                       ring_slot(n - 1), p->stream),
-                      "adjoint copy");
-        if (!s) s = op_am_step(p, n, false);
-      }
-      if (!s && ec >= sc) s = adj_copy(p, R.at(L.o_wwin, ec - w0), ring_slot(ec), a);
       for (int n = ec; n >= sc && !s; --n) {
-        // Z = G_n^H omega_n = F conj(S_n) V_n F^-1 omega_n
-        s = adj_ifft2(p, R.at(L.o_omega), nullptr, -mu[0] * dt, n * dt, R.at(L.o_Z));
+        // Z = G_n^H omega_n = F conj(S_n) V_n F^-1 omega_n, then step n
+        s = col_op(nullptr, nullptr, false, true, n * dt, 0.0, 1.0, 0.0, -mu[0] * dt, invP);
         const double2* Wx[MAXH + 1] = {nullptr};
-        for (int j = 1; j <= H; ++j) Wx[j] = R.at(L.o_wwin, (j == 1 ? n : n + 1 - j) - w0);
-        if (!s) s = am_iter(n, 1, true, R.at(L.o_bseg, n - sc), Wx, R.at(L.o_omega));
-        if (!s && n - 1 <= ns) s = adj_copy(p, omsu(n - 1), R.at(L.o_omega), a);
+        for (int j = 1; j <= H; ++j) Wx[j] = R.at(L.o_wwin, n + 1 - j - w0);
+        if (!s) s = rev_row(n, true, R.at(L.o_bseg, n - sc), Wx, n - 1 <= ns ? omsu(n - 1) : nullptr);
       }
     }
     if (s) return done(s);
@@ -2641,69 +2737,70 @@ int adjoint_single(tdse_plan_s* p, char* w, size_t wbytes, int K, const void* u0
       S.nblk = L.nblk;
       s = adj_err(launch_adj_sub(S, st), "adjoint phase");
     }
-    if (!s) s = adj_ifft2(p, R.at(L.o_modes[0]), R.at(L.o_phys[0]), 0.0, ns * dt);
-    if (!s) s = adj_point(p, R.at(L.o_phys[0]), R.at(L.o_phys[1]), ns * dt, invP, 0.0, 0.0, 0.0, 1.0, false, false);
-    if (!s) s = adj_ifft2(p, omsu(ns), R.at(L.o_phys[0]), 0.0, ns * dt);
-    if (!s) s = adj_point(p, R.at(L.o_phys[0]), R.at(L.o_phys[1]), ns * dt, 0.0, 0.0, invP, 0.0, 1.0, false, true);
+    if (!s) s = row_inverse(R.at(L.o_modes[0]));
+    if (!s) s = col_op(nullptr, R.at(L.o_phys[1]), false, false, ns * dt, 1.0, 0.0, 0.0, 0.0, invP);
+    if (!s) s = row_inverse(omsu(ns));
+    if (!s) s = col_op(nullptr, R.at(L.o_phys[1]), true, false, ns * dt, 0.0, 1.0, 0.0, 0.0, invP);
   } else {
     s = adj_copy(p, R.at(L.o_phys[1]), R.at(L.o_phys[2]), a);
   }
   if (s) return done(s);
-  // ---- start-up sub-steps, newest first; g_u in phys[1], g_u_{m-1} built in phys[2]
+  // ---- start-up sub-steps, newest first; g_u in gu, g_u_{m-1} built in gn
   int64_t row = (N > ns ? (int64_t)(N - ns) * 2 * MAXH : 0);
+  double2 *gu = R.at(L.o_phys[1]), *gn = R.at(L.o_phys[2]);
+  const int nsub_all = (1 << L.L) - 1;
   for (int m = ns; m >= 1 && !s; --m) {
     const double t0 = (m - 1) * dt;
+    s = build_phases((int64_t)(N - ns) * 2 * H + (int64_t)(m - 1) * nsub_all, nsub_all);
+    if (s) break;
     if (N > ns && m - 1 >= ns + 1 - H) {
-      s = adj_ifft2(p, omsu(m - 1), R.at(L.o_phys[0]), 0.0, t0);
-      if (!s) s = adj_point(p, R.at(L.o_phys[0]), R.at(L.o_phys[2]), t0, 0.0, 0.0, invP, 0.0, 1.0, false, false);
+      s = row_inverse(omsu(m - 1));
+      if (!s) s = col_op(nullptr, gn, false, false, t0, 0.0, 1.0, 0.0, 0.0, invP);
     } else {
-      s = adj_err(hipMemsetAsync(R.at(L.o_phys[2]), 0, a, st), "adjoint clear");
+      s = adj_err(hipMemsetAsync(gn, 0, a, st), "adjoint clear");
     }
     for (int l = 0; l < L.L && !s; ++l) {
       const int nsub = 1 << l;
       const double d = dt / nsub;
-      // recompute the level's sub-step inputs v_s and g_s = F((1 - i d/2 V) v_s)
-      s = adj_copy(p, R.at(L.o_subv, 0), R.at(L.o_ustore, m - 1), a);
+      // the fused row pass of sub-step k
+      auto sub_row = [&](int k, bool rev, bool inv) {
+        AdjRowSub q;
+        std::memset(&q, 0, sizeof(q));
+        q.M1 = p->M1;
+        q.M2 = p->M2;
+        q.rev = rev;
+        q.inv = inv;
+        q.src = rtile;
+        q.dst = rtile;
+        q.tw = (const double2*)p->tw(0, 1);
+        q.ph = ptab + (int64_t)(nsub - 1 + k) * per;
+        q.G = R.at(L.o_subg, k);
+        q.nblk = L.nblk;
+        if (rev) {
+          q.part = (double*)(w + L.o_part) + row * L.nblk;
+          for (int ax = 0; ax < 2; ++ax) R.rows[row + ax] = AdjRun::Row{t0 + k * d, t0 + k * d + d, ax};
+          row += 2;
+        }
+        return adj_err(launch_adj_row_sub(q, st), "adjoint sub-step");
+      };
+      // recompute the level's g_k = F((1 - i d/2 V(tau_k)) v_k), v_{k+1} = F^-1(E_k g_k) / (1 + i d/2 V(tau_{k+1}))
+      s = col_op(R.at(L.o_ustore, m - 1), nullptr, false, true, t0, 1.0, 0.0, -0.5 * d, 0.0, invP);
       for (int k = 0; k < nsub && !s; ++k) {
-        const double tau = t0 + k * d;
-        s = adj_fft2(p, R.at(L.o_subv, k), R.at(L.o_subg, k), invP, 1.0, 0.0, 0.0, -0.5 * d, tau);
-        if (s || k == nsub - 1) continue;
-        PH.q.nj = 0;
-        PH.set(p, 0, tau + d, d);
-        s = adj_err(launch_adj_phase(PH.q, st), "adjoint phases");
-        if (s) break;
-        AdjSub S;
-        std::memset(&S, 0, sizeof(S));
-        S.M1 = p->M1; S.M2 = p->M2; S.mode = 1; S.P = p->P; S.ph = PH.q.ph; S.y = R.at(L.o_modes[1]);
-        S.g = R.at(L.o_subg, k); S.nblk = L.nblk;
-        s = adj_err(launch_adj_sub(S, st), "adjoint phase");
-        if (!s) s = adj_ifft2(p, R.at(L.o_modes[1]), R.at(L.o_subv, k + 1), 0.5 * d, tau + d);
+        s = sub_row(k, false, k < nsub - 1);
+        if (!s && k < nsub - 1)
+          s = col_op(nullptr, nullptr, false, true, t0 + k * d + d, 1.0, 0.0, -0.5 * d, 0.5 * d, invP);
       }
-      // reverse the level: g_v = r_l g_u_m
-      if (!s) s = adj_point(p, R.at(L.o_phys[1]), R.at(L.o_phys[0]), t0, p->rich[l], 0.0, 0.0, 0.0, 1.0, false, false);
+      // reverse the level from g_v = r_l g_u_m: per sub-step the conjugated
+      // solve at its end, F^-H, conj(E), F^H and the factor 1 + i d/2 V at its
+      // start; the last of these and the next sub-step's solve are at one time
+      if (!s) s = col_op(gu, nullptr, false, true, t0 + nsub * d, p->rich[l], 0.0, 0.0, -0.5 * d, 1.0);
       for (int k = nsub - 1; k >= 0 && !s; --k) {
-        const double tau = t0 + k * d;
-        s = adj_point(p, R.at(L.o_phys[0]), R.at(L.o_phys[0]), tau + d, 1.0, 0.0, 0.0, -0.5 * d, 1.0, true, false);
-        if (!s) s = adj_fft2(p, R.at(L.o_phys[0]), R.at(L.o_modes[1]), 1.0, 1.0, 0.0, 0.0, 0.0, tau);
-        if (s) break;
-        PH.q.nj = 0;
-        PH.set(p, 0, tau + d, d);
-        s = adj_err(launch_adj_phase(PH.q, st), "adjoint phases");
-        if (s) break;
-        AdjSub S;
-        std::memset(&S, 0, sizeof(S));
-        S.M1 = p->M1; S.M2 = p->M2; S.mode = 0; S.P = p->P; S.ph = PH.q.ph; S.y = R.at(L.o_modes[1]);
-        S.g = R.at(L.o_subg, k); S.nblk = L.nblk;
-        S.part = (double*)(w + L.o_part) + row * L.nblk;
-        for (int ax = 0; ax < 2; ++ax) R.rows[row + ax] = AdjRun::Row{tau, tau + d, ax};
-        row += 2;
-        s = adj_err(launch_adj_sub(S, st), "adjoint phase");
-        if (!s) s = adj_ifft2(p, R.at(L.o_modes[1]), R.at(L.o_phys[0]), 0.0, tau);
-        if (!s) s = adj_point(p, R.at(L.o_phys[0]), R.at(L.o_phys[0]), tau, 1.0, 0.0, 0.0, 0.5 * d, invP, false, false);
+        s = sub_row(k, true, true);
+        if (!s && k > 0) s = col_op(nullptr, nullptr, false, true, t0 + k * d, 1.0, 0.0, 0.5 * d, -0.5 * d, invP);
+        else if (!s) s = col_op(nullptr, gn, true, false, t0, 1.0, 0.0, 0.5 * d, 0.0, invP);
       }
-      if (!s) s = adj_point(p, R.at(L.o_phys[0]), R.at(L.o_phys[2]), t0, 1.0, 0.0, 0.0, 0.0, 1.0, false, true);
     }
-    if (!s) s = adj_copy(p, R.at(L.o_phys[1]), R.at(L.o_phys[2]), a);
+    std::swap(gu, gn);
   }
   if (s) return done(s);
   // ---- dJ/dA: reduce the partials, then map rows to samples
@@ -2750,7 +2847,7 @@ int adjoint_single(tdse_plan_s* p, char* w, size_t wbytes, int K, const void* u0
   }
   if (!s && dF_dA) s = adj_err(hipMemcpyAsync(dF_dA, w + L.o_gA, nA * sizeof(double), hipMemcpyDeviceToHost, st), "copy");
   if (!s && dF_du0)
-    s = adj_err(hipMemcpyAsync(dF_du0, R.at(L.o_phys[1]), a, on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, st),
+    s = adj_err(hipMemcpyAsync(dF_du0, gu, a, on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, st),
                 "copy");
   if (!s) s = adj_err(hipStreamSynchronize(st), "adjoint sync");
   return done(s);

@@ -75,6 +75,7 @@ struct LineArgs {
   int acc_first;
   // row pass
   double2* Bm;
+  double2* Bw;         // where R_AM leaves the new state (Bm, or a slot of the adjoint's store)
   void* ring;          // history ring (transform precision)
   int64_t ring_stride;
   int nh;
@@ -175,6 +176,13 @@ hipError_t launch_batch_pass(int prec, bool col, int family, const LineArgs* arg
 
 // Adjoint of the periodic scheme (adjoint_kernels.hip), FP64.
 constexpr int ADJ_PH = 2 * MAXH;   // phase entries of one adjoint Adams step
+// per-axis table ph[e (M1+M2) + k] of ne entries listed on the device as
+// (tau, dphi_1, dphi_2)
+struct AdjPhases {
+  int M1, M2, ne;
+  const double* list;
+  double2* ph;
+};
 struct AdjPhase {                  // per-axis table ph[e (M1+M2) + k], e < nj
   int M1, M2, nj;
   double tau[ADJ_PH], dphi1[ADJ_PH], dphi2[ADJ_PH];
@@ -208,25 +216,68 @@ struct AdjSub {                    // phase factor of an order-2 sub-step (entry
   double* part;                    // partial sums [axis][nblk]
   int nblk;
 };
-struct AdjPoint {                  // out (+)= s (alpha + beta V) in, or s in / (alpha + beta V)
+// Fused row pass of the reverse sweep (entries as for AdjAm): forward FFT of
+// a tile row (Z), beta_n = conj(E^(1)_{n+1}) beta_{n+1} + Z, the partials of
+// step n+1, omega_{n-1}, and the inverse FFT of omega_{n-1} into the tile.
+struct AdjRowAm {
+  int M1, M2, H;
   int64_t P;
-  const double2* in;
-  double2* out;
+  const double2* src;              // tile
+  double2* dst;                    // tile
+  const double2* tw;
+  const double2* ph;
+  double2* beta;
+  int slot_b1, slot_bn;
+  double2* omega;                  // optional copy of omega_{n-1} (null: none)
+  int slot_bj[MAXH + 1];
+  double wj[MAXH + 1];
+  int has_grad;
+  const double2* Bn;
+  const double2* Wx[MAXH + 1];
+  double cx[MAXH + 1];
+  double* part;                    // partial sums [2 (j-1) + axis][nblk], one per workgroup
+  int nblk;
+};
+// Fused row pass of a start-up sub-step, phase factor E (entry 0 of ph):
+//   rev 0: g = forward FFT of a tile row into G; with inv, the inverse FFT of E g;
+//   rev 1: y = forward FFT; partials of Re(conj(y) i E g); the inverse FFT of conj(E) y.
+struct AdjRowSub {
+  int M1, M2, rev, inv;
+  const double2* src;              // tile
+  double2* dst;                    // tile
+  const double2* tw;
+  const double2* ph;
+  double2* G;
+  double* part;                    // partial sums [axis][nblk]
+  int nblk;
+};
+// Fused column pass: x from the tile (inverse FFT along axis 0) or from the
+// grid array xin, y = s x (ar + i ai + (br + i bi) V) / (1 + i di V), y into (or
+// added to) the grid array yout, and the forward FFT of y into the tile.
+struct AdjCol {
+  int M1, M2;
+  const double2* src;              // tile (null: xin)
+  double2* dst;                    // tile (null: none)
+  const double2* xin;
+  double2* yout;                   // null: none
+  int accumulate;
+  const double2* tw;
   const double* V;
   int nV;
   int64_t vstride;
   double fV[MAXV];
-  double ar, ai, br, bi, s;
-  int divide, accumulate;
+  double ar, ai, br, bi, di, s;
 };
 hipError_t launch_adj_phase(const AdjPhase& q, hipStream_t s);
 hipError_t launch_adj_am(const AdjAm& a, hipStream_t s);
+hipError_t launch_adj_phases(const AdjPhases& q, hipStream_t s);
+hipError_t launch_adj_row_am(const AdjRowAm& a, hipStream_t s);
+hipError_t launch_adj_row_sub(const AdjRowSub& a, hipStream_t s);
+hipError_t launch_adj_col(const AdjCol& a, hipStream_t s);
+int adj_row_blocks(int M1, int M2);   // workgroups of the fused row passes
 hipError_t launch_adj_sub(const AdjSub& a, hipStream_t s);
-hipError_t launch_adj_point(const AdjPoint& a, hipStream_t s);
 hipError_t launch_adj_axpy(int64_t P, const double2* x, const double2* y, double cr, double ci, double2* out,
                            hipStream_t s);
-hipError_t launch_adj_copy2(int64_t P, double2* dst0, const double2* src0, double2* dst1, const double2* src1,
-                            hipStream_t s);
 hipError_t launch_adj_reduce(const double* part, double* red, int nrows, int nblk, hipStream_t s);
 hipError_t launch_adj_to_A(const double* red, const int* rowptr, const int* src, const double* wt, double* out,
                            int nout, hipStream_t s);
