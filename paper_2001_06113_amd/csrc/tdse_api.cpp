@@ -274,6 +274,9 @@ struct RecLaunch {
 };
 
 constexpr int NFAM = 6;   // batched pass families (schedule families 0..2, phase-power rows 3..5)
+// Lanes of a batch: sets of instances that march on streams of their own for
+// a whole run (1D instances; 2D with both lengths 2^a, both 3 * 2^a, mixed)
+constexpr int NLANE = 4;
 
 struct tdse_plan_s {
   // grid: M1 x M2 (1D: M1 = 1).  A 3D grid M0 x Mmid x M2 is held as M1 =
@@ -361,8 +364,8 @@ struct tdse_plan_s {
     int64_t off = 0;                            // element offset in the tile region
     // schedule families 0..2, and for row passes 3..5: the same schedules
     // for instances whose last axis carries no field (phase powers)
-    int first[NFAM] = {}, cnt[NFAM] = {};
-    size_t lds[NFAM] = {};
+    int first[NLANE][NFAM] = {}, cnt[NLANE][NFAM] = {};
+    size_t lds[NLANE][NFAM] = {};
   };
   TileSet tiles[2][2];                          // [column/row][stage]
   std::vector<int> ept[2];                      // [column/row][instance]: schedule of the Adams stage
@@ -411,19 +414,22 @@ struct tdse_plan_s {
     gexec = nullptr;
     graph = nullptr;
   }
-  // batch: the schedule families of one pass run concurrently, families 1
-  // and 2 on side streams forked from and joined back to the bound stream
-  hipStream_t fam_st[NFAM - 1] = {};
-  hipEvent_t fam_fork = nullptr, fam_join[NFAM - 1] = {};
+  // batch: the lanes' streams, the first lane present on the bound stream and
+  // the others on side streams forked from it and joined back to it once per
+  // tdse_step or run (an instance's passes depend on its own only)
+  std::vector<int> lane;                        // [instance]
+  hipStream_t side_st[NLANE - 1] = {};
+  hipEvent_t lane_fork = nullptr, lane_join[NLANE - 1] = {};
+  hipStream_t lane_st[NLANE] = {};              // while forked; null: the bound stream
 
   ~tdse_plan_s() {
     drop_graph();
     for (hipEvent_t e : ev_pool) (void)hipEventDestroy(e);
-    for (int i = 0; i < NFAM - 1; ++i) {
-      if (fam_join[i]) (void)hipEventDestroy(fam_join[i]);
-      if (fam_st[i]) (void)hipStreamDestroy(fam_st[i]);
+    for (int i = 0; i < NLANE - 1; ++i) {
+      if (lane_join[i]) (void)hipEventDestroy(lane_join[i]);
+      if (side_st[i]) (void)hipStreamDestroy(side_st[i]);
     }
-    if (fam_fork) (void)hipEventDestroy(fam_fork);
+    if (lane_fork) (void)hipEventDestroy(lane_fork);
     for (tdse_plan_s* q : sub) delete q;
   }
 
@@ -1919,13 +1925,14 @@ bool last_axis_field_free(const tdse_plan_s* q) {
 }
 
 // Tile table of one pass kind and buffer stage from per-instance schedules,
-// ordered by schedule family; uploaded synchronously.
+// ordered by lane and schedule family; uploaded synchronously.
 int batch_tiles(tdse_plan_s* p, int kind, int g, const std::vector<int>& ept) {
   const int prec = p->sub[0]->st[g].prec;
-  std::vector<BatchTile> fam[NFAM];
+  std::vector<BatchTile> fam[NLANE][NFAM];
   tdse_plan_s::TileSet& ts = p->tiles[kind][g];
   ts.off = tile_base(p, kind, g);
-  for (int f = 0; f < NFAM; ++f) ts.lds[f] = 0;
+  for (int l = 0; l < NLANE; ++l)
+    for (int f = 0; f < NFAM; ++f) ts.lds[l][f] = 0;
   for (size_t i = 0; i < p->sub.size(); ++i) {
     const tdse_plan_s* q = p->sub[i];
     const int N = batch_len(q, kind), e = ept[i];
@@ -1935,16 +1942,18 @@ int batch_tiles(tdse_plan_s* p, int kind, int g, const std::vector<int>& ept) {
     const int LPW = BATCH_THREADS / (N / e);
     const int nl = batch_lines(q, kind);
     const int nt = (nl + LPW - 1) / LPW;
-    for (int b = 0; b < nt; ++b) fam[f].push_back(BatchTile{(int32_t)i, b * LPW, b, nt, N * 64 + e, 0});
-    ts.lds[f] = std::max(ts.lds[f], batch_lds_bytes(prec, kind == 0, N, e));
+    const int l = p->lane[i];
+    for (int b = 0; b < nt; ++b) fam[l][f].push_back(BatchTile{(int32_t)i, b * LPW, b, nt, N * 64 + e, 0});
+    ts.lds[l][f] = std::max(ts.lds[l][f], batch_lds_bytes(prec, kind == 0, N, e));
   }
   std::vector<BatchTile> all;
-  for (int f = 0; f < NFAM; ++f) {
-    ts.first[f] = (int)all.size();
-    ts.cnt[f] = (int)fam[f].size();
-    if (ts.lds[f] > p->lds_max) return fail(TDSE_EINVAL, "batched schedule exceeds the LDS of a workgroup");
-    all.insert(all.end(), fam[f].begin(), fam[f].end());
-  }
+  for (int l = 0; l < NLANE; ++l)
+    for (int f = 0; f < NFAM; ++f) {
+      ts.first[l][f] = (int)all.size();
+      ts.cnt[l][f] = (int)fam[l][f].size();
+      if (ts.lds[l][f] > p->lds_max) return fail(TDSE_EINVAL, "batched schedule exceeds the LDS of a workgroup");
+      all.insert(all.end(), fam[l][f].begin(), fam[l][f].end());
+    }
   if ((int64_t)all.size() > p->cap_tiles[kind]) return fail(TDSE_EINVAL, "tile table overflow");
   HIP_TRY(hipStreamSynchronize(p->stream));
   HIP_TRY(hipMemcpy(p->ws + p->o_tiles + ts.off * sizeof(BatchTile), all.data(), all.size() * sizeof(BatchTile),
@@ -2016,6 +2025,43 @@ int batch_record(tdse_plan_s* p) {
   return TDSE_OK;
 }
 
+// The lanes that hold instances go to streams of their own, ordered after the
+// work on the bound stream; batch_join orders the bound stream after them.
+// Instances of different lanes share no data, so no pass of a run waits for
+// another lane's.  (With a fork and a join around every pass, a step of 64
+// uneven instances spent 25 us of 190 in event waits, and every pass lasted as
+// long as its slowest family.)  Not while launches are being timed.
+int batch_fork(tdse_plan_s* p) {
+  bool any[NLANE] = {};
+  for (int l : p->lane) any[l] = true;
+  int side = 0;
+  bool on_main = false;
+  for (int l = 0; l < NLANE; ++l) {
+    p->lane_st[l] = p->stream;
+    if (!any[l] || p->prof) continue;
+    if (on_main) {
+      if (side == 0) HIP_TRY(hipEventRecord(p->lane_fork, p->stream));
+      p->lane_st[l] = p->side_st[side++];
+      HIP_TRY(hipStreamWaitEvent(p->lane_st[l], p->lane_fork, 0));
+    }
+    on_main = true;
+  }
+  return TDSE_OK;
+}
+int batch_join(tdse_plan_s* p) {
+  for (int l = 0; l < NLANE; ++l) {
+    if (p->lane_st[l] != p->stream && p->lane_st[l]) {
+      int i = 0;
+      while (p->side_st[i] != p->lane_st[l]) ++i;
+      HIP_TRY(hipEventRecord(p->lane_join[i], p->lane_st[l]));
+      HIP_TRY(hipStreamWaitEvent(p->stream, p->lane_join[i], 0));
+    }
+    p->lane_st[l] = nullptr;
+  }
+  return TDSE_OK;
+}
+
+// issue recorded launches on the lanes' streams (between batch_fork and batch_join)
 int batch_exec(tdse_plan_s* p, const std::vector<tdse_plan_s::GLaunch>& L, const char* args_dev,
                const std::vector<tdse_plan_s::Narrow>& nar) {
   const size_t n = p->sub.size();
@@ -2023,7 +2069,7 @@ int batch_exec(tdse_plan_s* p, const std::vector<tdse_plan_s::GLaunch>& L, const
     if (gl.kind == 2) {
       for (size_t i = 0; i < n; ++i) {
         const tdse_plan_s::Narrow& w = nar[gl.arg0 + i];
-        const hipError_t e = launch_narrow((const double2*)w.src, (float2*)w.dst, w.n, p->stream);
+        const hipError_t e = launch_narrow((const double2*)w.src, (float2*)w.dst, w.n, p->lane_st[p->lane[i]]);
         if (e != hipSuccess) return fail(TDSE_EDEVICE, std::string("narrow: ") + hipGetErrorString(e));
       }
       continue;
@@ -2033,38 +2079,21 @@ int batch_exec(tdse_plan_s* p, const std::vector<tdse_plan_s::GLaunch>& L, const
     const LineArgs* args = (const LineArgs*)args_dev + gl.arg0;
     const BatchTile* tiles = (const BatchTile*)(p->ws + p->o_tiles) + ts.off;
     const bool timed = p->prof && gl.timed;
-    // the families touch disjoint instances: with more than one, the later
-    // ones go to side streams (not when each launch is being timed)
-    int nfam = 0;
-    for (int f = 0; f < NFAM; ++f) nfam += ts.cnt[f] > 0;
-    const bool fork = nfam > 1 && !timed && p->fam_fork;
-    if (fork) HIP_TRY(hipEventRecord(p->fam_fork, p->stream));
-    int side = 0;
-    bool on_main = false;
-    for (int f = 0; f < NFAM; ++f) {
-      if (!ts.cnt[f]) continue;
-      hipStream_t s = p->stream;
-      if (fork && on_main) {
-        s = p->fam_st[side++];
-        HIP_TRY(hipStreamWaitEvent(s, p->fam_fork, 0));
+    for (int l = 0; l < NLANE; ++l)
+      for (int f = 0; f < NFAM; ++f) {
+        if (!ts.cnt[l][f]) continue;
+        hipEvent_t e0 = nullptr, e1 = nullptr;
+        const size_t first = p->ev_used;
+        if (timed) {
+          e0 = next_event(p);
+          e1 = next_event(p);
+          if (!e0 || !e1) return fail(TDSE_EDEVICE, "hipEventCreate failed");
+        }
+        const hipError_t e = launch_batch_pass(prec, gl.kind == 0, f, args, tiles + ts.first[l][f], ts.cnt[l][f],
+                                               ts.lds[l][f], p->lane_st[l], e0, e1);
+        if (e != hipSuccess) return fail(TDSE_EDEVICE, std::string("batched launch: ") + hipGetErrorString(e));
+        if (e0) p->prof_marks.push_back({first, gl.kind});
       }
-      on_main = true;
-      hipEvent_t e0 = nullptr, e1 = nullptr;
-      const size_t first = p->ev_used;
-      if (timed) {
-        e0 = next_event(p);
-        e1 = next_event(p);
-        if (!e0 || !e1) return fail(TDSE_EDEVICE, "hipEventCreate failed");
-      }
-      const hipError_t e = launch_batch_pass(prec, gl.kind == 0, f, args, tiles + ts.first[f], ts.cnt[f], ts.lds[f],
-                                             s, e0, e1);
-      if (e != hipSuccess) return fail(TDSE_EDEVICE, std::string("batched launch: ") + hipGetErrorString(e));
-      if (e0) p->prof_marks.push_back({first, gl.kind});
-    }
-    for (int i = 0; i < side; ++i) {
-      HIP_TRY(hipEventRecord(p->fam_join[i], p->fam_st[i]));
-      HIP_TRY(hipStreamWaitEvent(p->stream, p->fam_join[i], 0));
-    }
   }
   return TDSE_OK;
 }
@@ -2073,8 +2102,8 @@ int batch_step(tdse_plan_s* p, int k) {
   if (!p->batch_ready) return fail(TDSE_ESTATE, "tdse_bind must come first");
   const int end = p->cur + k;
   const char* args = p->ws + p->o_args;
-  for (int m = p->cur + 1; m <= end; ++m) {
-    int s;
+  int s = batch_fork(p);
+  for (int m = p->cur + 1; m <= end && !s; ++m) {
     if (m < end || m <= p->sub[0]->ns) {
       s = batch_exec(p, p->seg[m], args, p->narrows);
     } else if (m == p->nsteps) {
@@ -2087,15 +2116,19 @@ int batch_step(tdse_plan_s* p, int k) {
       std::vector<tdse_plan_s::Narrow> nar;
       for (tdse_plan_s* q : p->sub) q->ucur = p->ucur_after[m - 1];
       s = batch_record_step(p, m, true, L, a, nar);
-      if (s) return s;
-      if (a.size() > p->cap_targs) return fail(TDSE_EINVAL, "output step table overflow");
+      if (!s && a.size() > p->cap_targs) s = fail(TDSE_EINVAL, "output step table overflow");
+      // the table's last readers, on whichever lane, are done
+      if (!s) s = batch_join(p);
+      if (s) break;
       HIP_TRY(hipStreamSynchronize(p->stream));
       HIP_TRY(hipMemcpy(p->ws + p->o_targs, a.data(), a.size() * sizeof(LineArgs), hipMemcpyHostToDevice));
-      s = batch_exec(p, L, p->ws + p->o_targs, nar);
+      s = batch_fork(p);
+      if (!s) s = batch_exec(p, L, p->ws + p->o_targs, nar);
     }
-    if (s) return s;
-    p->cur = m;
+    if (!s) p->cur = m;
   }
+  const int j = batch_join(p);
+  if (s || j) return s ? s : j;
   for (tdse_plan_s* q : p->sub) {
     q->ucur = p->ucur_after[end];
     q->cur = end;
@@ -2163,6 +2196,10 @@ int plan_batch(const tdse_problem_t* probs, int count, tdse_plan_s** out) {
     q->ucur = 0;
   }
   p->cap_targs = tcap;
+  for (const tdse_plan_s* q : p->sub) {
+    const bool t1 = q->M1 % 3 == 0, t2 = q->M2 % 3 == 0;
+    p->lane.push_back(q->M1 == 1 ? 0 : t1 != t2 ? 3 : t1 ? 2 : 1);
+  }
   p->bargs.clear();
   p->bargs.shrink_to_fit();
   p->narrows.clear();
@@ -2190,11 +2227,11 @@ int plan_batch(const tdse_problem_t* probs, int count, tdse_plan_s** out) {
 int bind_batch(tdse_plan_s* p) {
   int dev = 0, v = 0;
   HIP_TRY(hipGetDevice(&dev));
-  if (!p->fam_fork) {   // default priority, non-blocking
-    HIP_TRY(hipEventCreateWithFlags(&p->fam_fork, hipEventDisableTiming));
-    for (int i = 0; i < NFAM - 1; ++i) {
-      HIP_TRY(hipStreamCreateWithFlags(&p->fam_st[i], hipStreamNonBlocking));
-      HIP_TRY(hipEventCreateWithFlags(&p->fam_join[i], hipEventDisableTiming));
+  if (!p->lane_fork) {   // default priority, non-blocking
+    HIP_TRY(hipEventCreateWithFlags(&p->lane_fork, hipEventDisableTiming));
+    for (int i = 0; i < NLANE - 1; ++i) {
+      HIP_TRY(hipStreamCreateWithFlags(&p->side_st[i], hipStreamNonBlocking));
+      HIP_TRY(hipEventCreateWithFlags(&p->lane_join[i], hipEventDisableTiming));
     }
   }
   HIP_TRY(hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
@@ -2252,10 +2289,16 @@ int autotune_batch(tdse_plan_s* p, int reps) {
         for (size_t i = 0; i < lens.size(); ++i)
           if (lens[i] == N) trial[i] = e;
         status = batch_tiles(p, kind, 1, trial);
-        if (!status) status = batch_exec(p, one, p->ws + p->o_args, p->narrows);   // warm-up
+        auto pass = [&]() {
+          int e = batch_fork(p);
+          if (!e) e = batch_exec(p, one, p->ws + p->o_args, p->narrows);
+          const int j = batch_join(p);
+          return e ? e : j;
+        };
+        if (!status) status = pass();   // warm-up
         if (status) break;
         if (hipEventRecord(t0, p->stream) != hipSuccess) { status = fail(TDSE_EDEVICE, "hipEventRecord"); break; }
-        for (int r = 0; r < reps && !status; ++r) status = batch_exec(p, one, p->ws + p->o_args, p->narrows);
+        for (int r = 0; r < reps && !status; ++r) status = pass();
         if (status) break;
         float ms = 0.f;
         if (hipEventRecord(t1, p->stream) != hipSuccess || hipEventSynchronize(t1) != hipSuccess ||
