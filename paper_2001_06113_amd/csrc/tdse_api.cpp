@@ -10,11 +10,13 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <memory>
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
+#include <numeric>
 #include <string>
 #include <thread>
 #include <vector>
@@ -3767,9 +3769,16 @@ int tdse_adjoint(tdse_plan_t p, void* ws, size_t bytes, int32_t checkpoint_every
     p->cur = -1;
     return TDSE_OK;
   }
-  // T workers, worker t takes instances t, t + T, ...: a stream each
-  // (non-blocking, default priority), ordered after the work already on the
-  // bound stream, and the bound stream ordered after all of them
+  // T workers: a stream each (non-blocking, default priority), ordered after
+  // the work already on the bound stream, and the bound stream ordered after
+  // all of them.  They take the instances one by one, the longest first (a
+  // step is a chain of latency-bound passes: a 1D instance costs what a 2D
+  // one of 2^16 modes does), so that the workers end together
+  std::vector<int> turn(nsub);
+  std::iota(turn.begin(), turn.end(), 0);
+  auto cost = [&](int i) { return (double)p->sub[i]->P + 65536.0 + 80.0 * std::max(p->sub[i]->M1, p->sub[i]->M2); };
+  std::stable_sort(turn.begin(), turn.end(), [&](int x, int y) { return cost(x) > cost(y); });
+  std::atomic<int> next{0};
   int dev = 0;
   HIP_TRY(hipGetDevice(&dev));
   std::vector<hipStream_t> streams(T, nullptr);
@@ -3800,7 +3809,8 @@ int tdse_adjoint(tdse_plan_t p, void* ws, size_t bytes, int32_t checkpoint_every
         return;
       }
       char* w = (char*)ws + (size_t)t * slice;
-      for (int i = t; i < nsub && st[t] == TDSE_OK; i += T) {
+      for (int k; st[t] == TDSE_OK && (k = next.fetch_add(1)) < nsub;) {
+        const int i = turn[k];
         tdse_plan_s* q = p->sub[i];
         hipStream_t keep = q->stream;
         q->stream = streams[t];
