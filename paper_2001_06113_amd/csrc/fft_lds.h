@@ -273,6 +273,152 @@ __device__ __forceinline__ void fft_regs(C* v, int t, C* line, const TW& tw) {
   if constexpr (N > 1) fft_regs_rec<N, TL, 1, INV>(v, t, line, tw);
 }
 
+// ------------------------------------------------------- short ends of a line
+//
+// A line of N = 8 TL values of which only the first TL can be nonzero going
+// in, or are wanted coming out (radix 8 first).  In: every output of the first
+// pass's butterfly j equals x[j], so the pass and its exchange are one shared
+// copy of x: the second pass reads x[p >> 3] for its element p.  Out: the last
+// pass is one sum per thread over one butterfly's inputs.
+
+// forward: x[t], t < TL, is this thread's; `line` as for fft_regs
+template <int N, int TL, bool INV, typename C, typename TW>
+__device__ __forceinline__ void fft_short_in(C x, C* v, int t, C* line, const TW& tw) {
+  static_assert(N == 8 * TL && TL % 8 == 0 && pick_radix(N, 8) == 8, "radix 8 first");
+  line[t] = x;
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < 8; ++m) v[m] = line[(t >> 3) + (TL / 8) * m];
+  __syncthreads();
+  fft_regs_rec<N, TL, 8, INV>(v, t, line, tw);
+}
+// two lines in their own directions, sharing the barriers (fft_regs_dual)
+template <int N, int TL, bool INVA, bool INVB, typename C, typename TW>
+__device__ __forceinline__ void fft_short_in_dual(C xa, C xb, C* va, C* vb, int t, C* la, C* lb, const TW& tw) {
+  static_assert(N == 8 * TL && TL % 8 == 0 && pick_radix(N, 8) == 8, "radix 8 first");
+  la[t] = xa;
+  lb[t] = xb;
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < 8; ++m) {
+    va[m] = la[(t >> 3) + (TL / 8) * m];
+    vb[m] = lb[(t >> 3) + (TL / 8) * m];
+  }
+  __syncthreads();
+  fft_regs_dual_rec<N, TL, 8, INVA, INVB>(va, vb, t, la, lb, tw);
+}
+
+template <int N, int TL, int Ns, bool INV, typename C, typename TW>
+__device__ __forceinline__ C fft_short_out_rec(C* v, int t, C* line, const TW& tw) {
+  constexpr int EPT = N / TL, R = pick_radix(N / Ns, EPT), B = EPT / R, TWS = N / (Ns * R);
+  constexpr int RL = pick_radix(N / (Ns * R), EPT), BL = EPT / RL;   // the next pass
+  constexpr bool NEXT_LAST = Ns * R * RL == N;
+  C x[B][R];
+#pragma unroll
+  for (int b = 0; b < B; ++b) {
+    const int k = (Ns == 1) ? 0 : ((t + b * TL) % Ns);
+#pragma unroll
+    for (int r = 0; r < R; ++r) x[b][r] = v[b + r * B];
+    if constexpr (Ns > 1) {
+#pragma unroll
+      for (int r = 1; r < R; ++r) x[b][r] = cmul(x[b][r], twiddle<INV>(tw, r * k * TWS));
+    }
+    dft_small<R, INV>(x[b]);
+  }
+#pragma unroll
+  for (int b = 0; b < B; ++b) {
+    const int j = t + b * TL;
+    const int k = (Ns == 1) ? 0 : (j % Ns);
+    const int base = (j / Ns) * Ns * R + k;
+#pragma unroll
+    for (int r = 0; r < R; ++r) line[lds_slot(base + r * Ns)] = x[b][r];
+  }
+  __syncthreads();
+  if constexpr (NEXT_LAST) {   // output t of the last pass: butterfly t, sum of its twiddled inputs
+    C s = line[lds_slot(t)];
+#pragma unroll
+    for (int r = 1; r < RL; ++r) s = cadd(s, cmul(line[lds_slot(t + TL * r * BL)], twiddle<INV>(tw, r * t)));
+    __syncthreads();
+    return s;
+  } else {
+#pragma unroll
+    for (int m = 0; m < EPT; ++m) v[m] = line[lds_slot(t + TL * m)];
+    __syncthreads();
+    return fft_short_out_rec<N, TL, Ns * R, INV>(v, t, line, tw);
+  }
+}
+// element t < TL of the transform of v; ends with a barrier
+template <int N, int TL, bool INV, typename C, typename TW>
+__device__ __forceinline__ C fft_short_out(C* v, int t, C* line, const TW& tw) {
+  static_assert(plan_ok(N, N / TL) && pick_radix(N, N / TL) < N, "at least two passes");
+  return fft_short_out_rec<N, TL, 1, INV>(v, t, line, tw);
+}
+
+template <int N, int TL, int Ns, bool INVA, bool INVB, typename C, typename TW>
+__device__ __forceinline__ void fft_short_out_dual_rec(C* va, C* vb, C& oa, C& ob, int t, C* la, C* lb, const TW& tw) {
+  constexpr int EPT = N / TL, R = pick_radix(N / Ns, EPT), B = EPT / R, TWS = N / (Ns * R);
+  constexpr int RL = pick_radix(N / (Ns * R), EPT), BL = EPT / RL;
+  constexpr bool NEXT_LAST = Ns * R * RL == N;
+  C xa[B][R], xb[B][R];
+#pragma unroll
+  for (int b = 0; b < B; ++b) {
+    const int k = (Ns == 1) ? 0 : ((t + b * TL) % Ns);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      xa[b][r] = va[b + r * B];
+      xb[b][r] = vb[b + r * B];
+    }
+    if constexpr (Ns > 1) {
+#pragma unroll
+      for (int r = 1; r < R; ++r) {
+        const C w = twiddle<false>(tw, r * k * TWS);
+        const C wa = INVA ? C{w.x, -w.y} : w, wb = INVB ? C{w.x, -w.y} : w;
+        xa[b][r] = cmul(xa[b][r], wa);
+        xb[b][r] = cmul(xb[b][r], wb);
+      }
+    }
+    dft_small<R, INVA>(xa[b]);
+    dft_small<R, INVB>(xb[b]);
+  }
+#pragma unroll
+  for (int b = 0; b < B; ++b) {
+    const int j = t + b * TL;
+    const int k = (Ns == 1) ? 0 : (j % Ns);
+    const int base = (j / Ns) * Ns * R + k;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      la[lds_slot(base + r * Ns)] = xa[b][r];
+      lb[lds_slot(base + r * Ns)] = xb[b][r];
+    }
+  }
+  __syncthreads();
+  if constexpr (NEXT_LAST) {
+    oa = la[lds_slot(t)];
+    ob = lb[lds_slot(t)];
+#pragma unroll
+    for (int r = 1; r < RL; ++r) {
+      const C w = twiddle<false>(tw, r * t);
+      const C wa = INVA ? C{w.x, -w.y} : w, wb = INVB ? C{w.x, -w.y} : w;
+      oa = cadd(oa, cmul(la[lds_slot(t + TL * r * BL)], wa));
+      ob = cadd(ob, cmul(lb[lds_slot(t + TL * r * BL)], wb));
+    }
+    __syncthreads();
+  } else {
+#pragma unroll
+    for (int m = 0; m < EPT; ++m) {
+      va[m] = la[lds_slot(t + TL * m)];
+      vb[m] = lb[lds_slot(t + TL * m)];
+    }
+    __syncthreads();
+    fft_short_out_dual_rec<N, TL, Ns * R, INVA, INVB>(va, vb, oa, ob, t, la, lb, tw);
+  }
+}
+template <int N, int TL, bool INVA, bool INVB, typename C, typename TW>
+__device__ __forceinline__ void fft_short_out_dual(C* va, C* vb, C& oa, C& ob, int t, C* la, C* lb, const TW& tw) {
+  static_assert(plan_ok(N, N / TL) && pick_radix(N, N / TL) < N, "at least two passes");
+  fft_short_out_dual_rec<N, TL, 1, INVA, INVB>(va, vb, oa, ob, t, la, lb, tw);
+}
+
 // ------------------------------------------- held twiddles, alternating lines
 //
 // For kernels that transform many lines of one length N = 2^a or 3 * 2^a:

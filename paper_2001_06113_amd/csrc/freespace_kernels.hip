@@ -98,10 +98,16 @@ __device__ __forceinline__ typename fs_tw<NU>::type stage_twiddles(const CFAxis&
   return typename fs_tw<NU>::type{tws, tws + NC};
 }
 
+// Grid points a thread can hold, of the eight FFT slots: one when M <= nu/8
+// (the short ends of fft_lds.h: the first pass going in and most of the last
+// pass coming out drop out), four when M <= nu/2 (the other slots are
+// compile-time zeros going in and unused coming out), else eight.
+__host__ __device__ constexpr int fs_points(int nu, int M) { return M <= nu / 8 ? 1 : M <= nu / 2 ? 4 : 8; }
+
 // forward transform of f[0..M) (LDS); ends with dm complete (a barrier).
 // dm may share f's LDS: it is written only after the last read of f.
-// CH: the C-type block through the interpolant (ax.NT > 0).
-template <int NU, bool CH>
+// CH: the C-type block through the interpolant (ax.NT > 0); MP = fs_points.
+template <int NU, bool CH, int MP>
 __device__ __forceinline__ void cf_forward(const double2* f, double2 (&v3)[RAY], double2 (&v1)[RAY], double2* dm,
                                            double2* part, double2* fline, double2* fline2, const CFAxis& ax,
                                            const typename fs_tw<NU>::type& tw, int t) {
@@ -113,12 +119,18 @@ __device__ __forceinline__ void cf_forward(const double2* f, double2 (&v3)[RAY],
   double2 w[EPT], w1[EPT];
 #pragma unroll
   for (int m = 0; m < EPT; ++m) {
-    const int e = t + TL * m, ec = min(e, M - 1);
-    const double2 x = cmul(ax.pre3[ec], f[ec]), y = cmul(ax.pre1[ec], f[ec]);
-    w[m] = e < M ? x : double2{0.0, 0.0};
-    w1[m] = e < M ? y : double2{0.0, 0.0};
+    if (m < MP) {
+      const int e = t + TL * m, ec = min(e, M - 1);
+      const double2 x = cmul(ax.pre3[ec], f[ec]), y = cmul(ax.pre1[ec], f[ec]);
+      w[m] = e < M ? x : double2{0.0, 0.0};
+      w1[m] = e < M ? y : double2{0.0, 0.0};
+    } else {
+      w[m] = double2{0.0, 0.0};
+      w1[m] = double2{0.0, 0.0};
+    }
   }
-  fft_regs_dual<NU, TL, false, true>(w, w1, t, fline, fline2, tw);
+  if constexpr (MP == 1) fft_short_in_dual<NU, TL, false, true>(w[0], w1[0], w, w1, t, fline, fline2, tw);
+  else fft_regs_dual<NU, TL, false, true>(w, w1, t, fline, fline2, tw);
 #pragma unroll
   for (int m = 0; m < RAY; ++m) {
     const int e = t + TL * m;
@@ -187,7 +199,7 @@ __device__ __forceinline__ void cf_forward(const double2* f, double2 (&v3)[RAY],
 // (LDS); thread t writes u[t + TL m] only, so it may read those entries back
 // without a barrier.  With the interpolant (CH) dm shares u's LDS: u is
 // written only after every read of dm.
-template <int NU, bool CH>
+template <int NU, bool CH, int MP>
 __device__ __forceinline__ void cf_inverse(const double2 (&v3)[RAY], const double2 (&v1)[RAY], const double2* dm,
                                            double2* fline, double2* fline2, const CFAxis& ax,
                                            const typename fs_tw<NU>::type& tw, int t, double2* u) {
@@ -208,17 +220,19 @@ __device__ __forceinline__ void cf_inverse(const double2 (&v3)[RAY], const doubl
       w1[m] = double2{0.0, 0.0};
     }
   }
-  fft_regs_dual<NU, TL, true, false>(w, w1, t, fline, fline2, tw);   // ends with a barrier: both lines free
+  // ends with a barrier: both lines free
+  if constexpr (MP == 1) fft_short_out_dual<NU, TL, true, false>(w, w1, w[0], w1[0], t, fline, fline2, tw);
+  else fft_regs_dual<NU, TL, true, false>(w, w1, t, fline, fline2, tw);
   constexpr int DB = 18;   // dense rows per batch of matrix entries
   if constexpr (!CH) {
     // dm has LDS of its own: E3 part into u, then E1 and the dense modes
 #pragma unroll
-    for (int m = 0; m < EPT; ++m) {
+    for (int m = 0; m < MP; ++m) {
       const int e = t + TL * m;
       if (e < M) u[e] = cmul(ax.ipost3[e], w[m]);
     }
 #pragma unroll
-    for (int m = 0; m < EPT; ++m) {
+    for (int m = 0; m < MP; ++m) {
       const int e = t + TL * m;
       if (e < M) {
         double2 s = cadd(u[e], cmul(ax.ipost1[e], w1[m]));
@@ -263,7 +277,7 @@ __device__ __forceinline__ void cf_inverse(const double2 (&v3)[RAY], const doubl
     }
     __syncthreads();   // dv complete, and every read of dm done: u may be written
 #pragma unroll
-    for (int m = 0; m < EPT; ++m) {
+    for (int m = 0; m < MP; ++m) {
       const int e = t + TL * m;
       if (e < M) {
         double2 s = cadd(cmul(ax.ipost3[e], w[m]), cmul(ax.ipost1[e], w1[m]));
@@ -300,7 +314,7 @@ __device__ __forceinline__ double2 conj_if(bool c, double2 z) { return c ? doubl
 
 // forward transform of f[0..M) (LDS) on the thread's ray; ends with dm
 // complete (a barrier).  dm may share f's LDS (CH), as in cf_forward.
-template <int NU, bool CH>
+template <int NU, bool CH, int MP>
 __device__ __forceinline__ void rs_forward(const double2* f, double2 (&v)[RAY], double2* dm, double2* part,
                                            double2* fline, double2* fline2, const CFAxis& ax,
                                            const typename fs_tw<NU>::type& tw, int tid) {
@@ -314,11 +328,16 @@ __device__ __forceinline__ void rs_forward(const double2* f, double2 (&v)[RAY], 
   double2 w[EPT];
 #pragma unroll
   for (int m = 0; m < EPT; ++m) {
-    const int e = t + TL * m, ec = min(e, M - 1);
-    const double2 x = conj_if(ray, cmul(pre[ec], f[ec]));
-    w[m] = e < M ? x : double2{0.0, 0.0};
+    if (m < MP) {
+      const int e = t + TL * m, ec = min(e, M - 1);
+      const double2 x = conj_if(ray, cmul(pre[ec], f[ec]));
+      w[m] = e < M ? x : double2{0.0, 0.0};
+    } else {
+      w[m] = double2{0.0, 0.0};
+    }
   }
-  fft_regs<NU, TL, false>(w, t, ray ? fline2 : fline, tw);
+  if constexpr (MP == 1) fft_short_in<NU, TL, false>(w[0], w, t, ray ? fline2 : fline, tw);
+  else fft_regs<NU, TL, false>(w, t, ray ? fline2 : fline, tw);
 #pragma unroll
   for (int m = 0; m < RAY; ++m) {
     const int e = t + TL * m;
@@ -379,7 +398,7 @@ __device__ __forceinline__ void rs_forward(const double2* f, double2 (&v)[RAY], 
 // its own entries back without a barrier.  The dense rows are split between
 // the halves.  With the interpolant (CH) dm shares u's LDS: u is written only
 // after every read of dm.
-template <int NU, bool CH>
+template <int NU, bool CH, int MP>
 __device__ __forceinline__ void rs_inverse(const double2 (&v)[RAY], const double2* dm, double2* fline,
                                            double2* fline2, const CFAxis& ax, const typename fs_tw<NU>::type& tw,
                                            int tid, double2* u) {
@@ -401,7 +420,9 @@ __device__ __forceinline__ void rs_inverse(const double2 (&v)[RAY], const double
       w[m] = double2{0.0, 0.0};
     }
   }
-  fft_regs<NU, TL, false>(w, t, ray ? fline2 : fline, tw);   // ends with a barrier: both lines free
+  // ends with a barrier: both lines free
+  if constexpr (MP == 1) w[0] = fft_short_out<NU, TL, false>(w, t, ray ? fline2 : fline, tw);
+  else fft_regs<NU, TL, false>(w, t, ray ? fline2 : fline, tw);
   const double2* drow = dm;   // the rows' values: the dense modes, or (CH) the node values
   if constexpr (CH) {
     const int P = ax.NP, NT = ax.NT, NC = ND - 2 * P;
@@ -439,7 +460,7 @@ __device__ __forceinline__ void rs_inverse(const double2 (&v)[RAY], const double
   const int q0 = ray ? h : 0, q1 = ray ? NR : h;
   double2* dst = ray ? u : fline;
 #pragma unroll
-  for (int m = 0; m < EPT; ++m) {
+  for (int m = 0; m < MP; ++m) {
     const int e = t + TL * m;
     if (e < M) {
       double2 acc = cmul(ipost[e], conj_if(!ray, w[m]));
@@ -458,7 +479,7 @@ __device__ __forceinline__ void rs_inverse(const double2 (&v)[RAY], const double
   __syncthreads();
   if (!ray) {
 #pragma unroll
-    for (int m = 0; m < EPT; ++m) {
+    for (int m = 0; m < MP; ++m) {
       const int e = t + TL * m;
       if (e < M) u[e] = cadd(u[e], fline[e]);
     }
@@ -528,7 +549,7 @@ __device__ __forceinline__ double2 fs_mode_update(const FSArgs& a, const double2
 // Two workgroups per CU with the full register budget: with the history
 // loads batched, spill traffic at a budget of 168 (three per CU) costs more
 // than the latency a third wave per SIMD hides.
-template <int NU, bool CH>
+template <int NU, bool CH, int MP>
 __global__ __launch_bounds__(NU / 8) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_fs_row(FSArgs a) {
   constexpr int TL = NU / 8;
   HIP_DYNAMIC_SHARED(double2, fs_lds)
@@ -571,7 +592,7 @@ __global__ __launch_bounds__(NU / 8) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   if (need_fwd) {
     for (int j = t; j < M2; j += TL) fin[j] = a.src[row_p + j];
     __syncthreads();
-    cf_forward<NU, CH>(fin, v3, v1, dm, part, fline, fline2, ax, tw, t);
+    cf_forward<NU, CH, MP>(fin, v3, v1, dm, part, fline, fline2, ax, tw, t);
   } else {
 #pragma unroll
     for (int m = 0; m < RAY; ++m) v3[m] = v1[m] = double2{0.0, 0.0};
@@ -755,7 +776,7 @@ __global__ __launch_bounds__(NU / 8) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   }
   if (mode == R_UHACC) return;
   __syncthreads();
-  cf_inverse<NU, CH>(v3, v1, dm, fline, fline2, ax, tw, t, fin);   // the forward input is no longer needed
+  cf_inverse<NU, CH, MP>(v3, v1, dm, fline, fline2, ax, tw, t, fin);   // the forward input is no longer needed
   for (int e = t; e < M2; e += TL) a.dst[row_p + e] = fin[e];
 }
 
@@ -774,7 +795,7 @@ __device__ __forceinline__ int fs_col_of(int b, int nb) {
 // The row pass with 2 TL threads per row: each thread carries RAY modes of
 // one ray (E3 for threads [0, TL), E1 for [TL, 2 TL)) through the forward
 // transform, the recurrence and the inverse transform.
-template <int NU, bool CH>
+template <int NU, bool CH, int MP>
 __global__ __launch_bounds__(NU / 4) void k_fs_row_rs(FSArgs a) {
   constexpr int TL = NU / 8, NTH = 2 * TL;
   HIP_DYNAMIC_SHARED(double2, fs_lds)
@@ -809,7 +830,7 @@ __global__ __launch_bounds__(NU / 4) void k_fs_row_rs(FSArgs a) {
   if (need_fwd) {
     for (int j = tid; j < M2; j += NTH) fin[j] = a.src[row_p + j];
     __syncthreads();
-    rs_forward<NU, CH>(fin, v, dm, part, fline, fline2, ax, tw, tid);
+    rs_forward<NU, CH, MP>(fin, v, dm, part, fline, fline2, ax, tw, tid);
   } else {
 #pragma unroll
     for (int m = 0; m < RAY; ++m) v[m] = double2{0.0, 0.0};
@@ -905,10 +926,10 @@ __global__ __launch_bounds__(NU / 4) void k_fs_row_rs(FSArgs a) {
   }
   if (mode == R_UHACC) return;
   __syncthreads();
-  rs_inverse<NU, CH>(v, dm, fline, fline2, ax, tw, tid, fin);
+  rs_inverse<NU, CH, MP>(v, dm, fline, fline2, ax, tw, tid, fin);
   if (!ray) {
 #pragma unroll
-    for (int m = 0; m < 8; ++m) {
+    for (int m = 0; m < MP; ++m) {
       const int e = t + TL * m;
       if (e < M2) a.dst[row_p + e] = fin[e];
     }
@@ -917,7 +938,7 @@ __global__ __launch_bounds__(NU / 4) void k_fs_row_rs(FSArgs a) {
 
 // The column pass with 2 TL threads per column (ray halves as in the row pass);
 // the columns are the ncol points of the other axes (x2, or (x1, x2) in 3D).
-template <int NU, bool CH>
+template <int NU, bool CH, int MP>
 __global__ __launch_bounds__(NU / 4) void k_fs_col_rs(FSArgs a) {
   constexpr int TL = NU / 8, NTH = 2 * TL;
   HIP_DYNAMIC_SHARED(double2, fs_lds)
@@ -948,10 +969,10 @@ __global__ __launch_bounds__(NU / 4) void k_fs_col_rs(FSArgs a) {
     }
     for (int q = tid; q < ND; q += NTH) dm[q] = a.src[(int64_t)(NE + q) * M2 + y];
     __syncthreads();
-    rs_inverse<NU, CH>(v, dm, fline, fline2, ax, tw, tid, fin);
+    rs_inverse<NU, CH, MP>(v, dm, fline, fline2, ax, tw, tid, fin);
     if (!ray) {
 #pragma unroll
-      for (int m = 0; m < 8; ++m) {
+      for (int m = 0; m < MP; ++m) {
         const int e = t + TL * m;
         if (e < M1) {
           const double2 wv = fin[e];
@@ -983,7 +1004,7 @@ __global__ __launch_bounds__(NU / 4) void k_fs_col_rs(FSArgs a) {
     }
   }
   __syncthreads();
-  rs_forward<NU, CH>(fin, v, dm, part, fline, fline2, ax, tw, tid);
+  rs_forward<NU, CH, MP>(fin, v, dm, part, fline, fline2, ax, tw, tid);
 #pragma unroll
   for (int m = 0; m < RAY; ++m) {
     const int e = t + TL * m;
@@ -996,7 +1017,7 @@ __global__ __launch_bounds__(NU / 4) void k_fs_col_rs(FSArgs a) {
 // (k0, x2) of the N0 x Nm x M2 mode array and of the N0 x Mm x M2 grid array,
 // stride M2.  INV: modes to grid points (before the column pass), else grid
 // points to modes (after it).
-template <int NU, bool CH, bool INV>
+template <int NU, bool CH, bool INV, int MP>
 __global__ __launch_bounds__(NU / 4) void k_fs_mid_rs(FSArgs a) {
   constexpr int TL = NU / 8, NTH = 2 * TL;
   HIP_DYNAMIC_SHARED(double2, fs_lds)
@@ -1028,10 +1049,10 @@ __global__ __launch_bounds__(NU / 4) void k_fs_mid_rs(FSArgs a) {
     }
     for (int q = tid; q < ND; q += NTH) dm[q] = a.src[mbase + (int64_t)(NE + q) * M2];
     __syncthreads();
-    rs_inverse<NU, CH>(v, dm, fline, fline2, ax, tw, tid, fin);
+    rs_inverse<NU, CH, MP>(v, dm, fline, fline2, ax, tw, tid, fin);
     if (!ray) {
 #pragma unroll
-      for (int m = 0; m < 8; ++m) {
+      for (int m = 0; m < MP; ++m) {
         const int e = t + TL * m;
         if (e < Mm) a.dst[gbase + (int64_t)e * M2] = fin[e];
       }
@@ -1039,7 +1060,7 @@ __global__ __launch_bounds__(NU / 4) void k_fs_mid_rs(FSArgs a) {
   } else {
     for (int e = tid; e < Mm; e += NTH) fin[e] = a.src[gbase + (int64_t)e * M2];
     __syncthreads();
-    rs_forward<NU, CH>(fin, v, dm, part, fline, fline2, ax, tw, tid);
+    rs_forward<NU, CH, MP>(fin, v, dm, part, fline, fline2, ax, tw, tid);
 #pragma unroll
     for (int m = 0; m < RAY; ++m) {
       const int e = t + TL * m;
@@ -1098,6 +1119,24 @@ __global__ __launch_bounds__(256) void k_fs_phase(FSArgs a) { build_phase_table_
     if (E0) hipExtLaunchKernelGGL(K, G, B, SH, S, E0, E1, 0, A);   \
     else hipLaunchKernelGGL(K, G, B, SH, S, A);                    \
   } while (0)
+// a line kernel K<nu, CH, ...> over the interpolant and the points per thread of axis AX
+#define TDSE_FS_LINE(K, n, AX, G, B, S, E0, E1, A, ...)                                                     \
+  do {                                                                                                      \
+    const size_t sh_ = fs_lds_bytes<n>(AX.M, AX.ND, AX.NT != 0);                                            \
+    switch (fs_points(n, AX.M)) {                                                                           \
+      case 1:                                                                                               \
+        if (AX.NT) TDSE_FS_LAUNCH_SH((K<n, true, ##__VA_ARGS__, 1>), G, B, sh_, S, E0, E1, A);              \
+        else TDSE_FS_LAUNCH_SH((K<n, false, ##__VA_ARGS__, 1>), G, B, sh_, S, E0, E1, A);                   \
+        break;                                                                                              \
+      case 4:                                                                                               \
+        if (AX.NT) TDSE_FS_LAUNCH_SH((K<n, true, ##__VA_ARGS__, 4>), G, B, sh_, S, E0, E1, A);              \
+        else TDSE_FS_LAUNCH_SH((K<n, false, ##__VA_ARGS__, 4>), G, B, sh_, S, E0, E1, A);                   \
+        break;                                                                                              \
+      default:                                                                                              \
+        if (AX.NT) TDSE_FS_LAUNCH_SH((K<n, true, ##__VA_ARGS__, 8>), G, B, sh_, S, E0, E1, A);              \
+        else TDSE_FS_LAUNCH_SH((K<n, false, ##__VA_ARGS__, 8>), G, B, sh_, S, E0, E1, A);                   \
+    }                                                                                                       \
+  } while (0)
 
 bool fs_nu_supported(int nu) {
   switch (nu) {
@@ -1128,12 +1167,9 @@ size_t fs_line_lds_bytes(int nu, int M, int ND, bool ch) {
 hipError_t launch_fs_row(int nu, const FSArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   if (a.N1 == 1 || nu <= 512) {
     switch (nu) {
-#define X(n)                                                                              \
-  case n:                                                                                 \
-    if (a.ax2.NT)                                                                         \
-      TDSE_FS_LAUNCH_SH((k_fs_row_rs<n, true>), dim3(a.N1), dim3(n / 4), fs_lds_bytes<n>(a.ax2.M, a.ax2.ND, a.ax2.NT != 0), s, e0, e1, a); \
-    else                                                                                  \
-      TDSE_FS_LAUNCH_SH((k_fs_row_rs<n, false>), dim3(a.N1), dim3(n / 4), fs_lds_bytes<n>(a.ax2.M, a.ax2.ND, a.ax2.NT != 0), s, e0, e1, a); \
+#define X(n) \
+  case n: \
+    TDSE_FS_LINE(k_fs_row_rs, n, a.ax2, dim3(a.N1), dim3(n / 4), s, e0, e1, a); \
     break;
       TDSE_FS_NU(X)
 #undef X
@@ -1143,14 +1179,12 @@ hipError_t launch_fs_row(int nu, const FSArgs& a, hipStream_t s, hipEvent_t e0, 
     return hipGetLastError();
   }
   switch (nu) {
-#define X(n)                                                                              \
-  case n:                                                                                 \
-    if (a.ax2.NT)                                                                         \
-      TDSE_FS_LAUNCH_SH((k_fs_row<n, true>), dim3(a.N1), dim3(n / 8), fs_lds_bytes<n>(a.ax2.M, a.ax2.ND, a.ax2.NT != 0), s, e0, e1, a); \
-    else                                                                                  \
-      TDSE_FS_LAUNCH_SH((k_fs_row<n, false>), dim3(a.N1), dim3(n / 8), fs_lds_bytes<n>(a.ax2.M, a.ax2.ND, a.ax2.NT != 0), s, e0, e1, a); \
+#define X(n) \
+  case n: \
+    TDSE_FS_LINE(k_fs_row, n, a.ax2, dim3(a.N1), dim3(n / 8), s, e0, e1, a); \
     break;
-    TDSE_FS_NU(X)
+      X(1024)
+      X(2048)
 #undef X
     default:
       return hipErrorInvalidValue;
@@ -1166,14 +1200,11 @@ hipError_t launch_fs_col(int nu, const FSArgs& a, hipStream_t s, hipEvent_t e0, 
     return hipGetLastError();
   }
   switch (nu) {
-#define X(n)                                                                              \
-  case n:                                                                                 \
-    if (a.ax1.NT)                                                                         \
-      TDSE_FS_LAUNCH_SH((k_fs_col_rs<n, true>), dim3((unsigned)a.ncol), dim3(n / 4), fs_lds_bytes<n>(a.ax1.M, a.ax1.ND, a.ax1.NT != 0), s, e0, e1, a); \
-    else                                                                                  \
-      TDSE_FS_LAUNCH_SH((k_fs_col_rs<n, false>), dim3((unsigned)a.ncol), dim3(n / 4), fs_lds_bytes<n>(a.ax1.M, a.ax1.ND, a.ax1.NT != 0), s, e0, e1, a); \
+#define X(n) \
+  case n: \
+    TDSE_FS_LINE(k_fs_col_rs, n, a.ax1, dim3((unsigned)a.ncol), dim3(n / 4), s, e0, e1, a); \
     break;
-    TDSE_FS_NU(X)
+      TDSE_FS_NU(X)
 #undef X
     default:
       return hipErrorInvalidValue;
@@ -1183,19 +1214,13 @@ hipError_t launch_fs_col(int nu, const FSArgs& a, hipStream_t s, hipEvent_t e0, 
 
 hipError_t launch_fs_mid(int nu, bool inverse, const FSArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   const dim3 g((unsigned)((int64_t)a.ax1.N * a.ax2.M));
-  const size_t lds_b = fs_line_lds_bytes(nu, a.axm.M, a.axm.ND, a.axm.NT != 0);
   switch (nu) {
-#define X(n)                                                                                                  \
-  case n:                                                                                                     \
-    if (a.axm.NT) {                                                                                           \
-      if (inverse) TDSE_FS_LAUNCH_SH((k_fs_mid_rs<n, true, true>), g, dim3(n / 4), lds_b, s, e0, e1, a);       \
-      else TDSE_FS_LAUNCH_SH((k_fs_mid_rs<n, true, false>), g, dim3(n / 4), lds_b, s, e0, e1, a);              \
-    } else {                                                                                                  \
-      if (inverse) TDSE_FS_LAUNCH_SH((k_fs_mid_rs<n, false, true>), g, dim3(n / 4), lds_b, s, e0, e1, a);      \
-      else TDSE_FS_LAUNCH_SH((k_fs_mid_rs<n, false, false>), g, dim3(n / 4), lds_b, s, e0, e1, a);             \
-    }                                                                                                         \
+#define X(n) \
+  case n: \
+    if (inverse) TDSE_FS_LINE(k_fs_mid_rs, n, a.axm, g, dim3(n / 4), s, e0, e1, a, true); \
+    else TDSE_FS_LINE(k_fs_mid_rs, n, a.axm, g, dim3(n / 4), s, e0, e1, a, false); \
     break;
-    TDSE_FS_NU(X)
+      TDSE_FS_NU(X)
 #undef X
     default:
       return hipErrorInvalidValue;
