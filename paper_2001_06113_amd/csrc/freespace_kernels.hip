@@ -104,6 +104,49 @@ __device__ __forceinline__ typename fs_tw<NU>::type stage_twiddles(const CFAxis&
 // compile-time zeros going in and unused coming out), else eight.
 __host__ __device__ constexpr int fs_points(int nu, int M) { return M <= nu / 8 ? 1 : M <= nu / 2 ? 4 : 8; }
 
+// sum_{j0 <= j < j1} r^(j - j0) f[j] (f in LDS): four interleaved Horner sums
+// in r^4, since one is a chain of dependent products (100 points of a row on
+// one thread: 4.6 us of a 20 us pass).
+__device__ __forceinline__ double2 geometric_sum(const double2* f, int j0, int j1, double2 r) {
+  const double2 r2 = cmul(r, r), r4 = cmul(r2, r2);
+  double2 s[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) s[k] = double2{0.0, 0.0};
+  for (int j = j0 + ((j1 - j0 + 3) / 4 - 1) * 4; j >= j0; j -= 4) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const double2 x = f[min(j + k, j1 - 1)];
+      s[k] = cadd(cmul(s[k], r4), j + k < j1 ? x : double2{0.0, 0.0});
+    }
+  }
+  return cadd(cadd(s[0], cmul(r, s[1])), cmul(r2, cadd(s[2], cmul(r, s[3]))));
+}
+
+// acc[m] += sum_{q0 <= q < q1} D[q][t + TL m] row[q] over the thread's MP grid
+// points (entries past M read the last one and go unused): the matrix entries,
+// L2 hits, are loaded DB rows at a time over all the points, so that a few
+// round trips are waited for and not one per point and eight rows.
+template <int TL, int MP>
+__device__ __forceinline__ void dense_inverse(double2 (&acc)[MP], const double2* __restrict__ D, const double2* row,
+                                              int q0, int q1, int M, int t) {
+  constexpr int DB = MP == 1 ? 18 : MP == 4 ? 6 : 3;
+  for (int qb = q0; qb < q1; qb += DB) {
+    double2 d[DB][MP];
+#pragma unroll
+    for (int k = 0; k < DB; ++k)
+#pragma unroll
+      for (int m = 0; m < MP; ++m) d[k][m] = D[(int64_t)min(qb + k, q1 - 1) * M + min(t + TL * m, M - 1)];
+#pragma unroll
+    for (int k = 0; k < DB; ++k) {
+      if (qb + k < q1) {
+        const double2 x = row[qb + k];
+#pragma unroll
+        for (int m = 0; m < MP; ++m) acc[m] = cadd(acc[m], cmul(d[k][m], x));
+      }
+    }
+  }
+}
+
 // forward transform of f[0..M) (LDS); ends with dm complete (a barrier).
 // dm may share f's LDS: it is written only after the last read of f.
 // CH: the C-type block through the interpolant (ax.NT > 0); MP = fs_points.
@@ -141,7 +184,7 @@ __device__ __forceinline__ void cf_forward(const double2* f, double2 (&v3)[RAY],
   }
   // dense rows: thread (q, c) sums the contiguous chunk j0 <= j < j0 + L of
   // the row q of Dfwd.  Entries along a row form a geometric sequence
-  // (equispaced x_j), so the chunk is Dfwd[q][j0] times a Horner sum in the
+  // (equispaced x_j), so the chunk is Dfwd[q][j0] times a geometric sum in the
   // ratio rfwd[q]: two table reads per chunk, L LDS reads.
   const int NR = CH ? ax.NR : ND;
   const int C = TL / NR > 1 ? TL / NR : 1;
@@ -154,10 +197,7 @@ __device__ __forceinline__ void cf_forward(const double2* f, double2 (&v3)[RAY],
     const int j0 = c * L, j1 = min(j0 + L, M);
     double2 acc = {0.0, 0.0};
     if (j0 < M) {
-      const double2 r = ax.rfwd[q];
-      const double2 d0 = ax.Dfwd[(int64_t)q * M + j0];
-      for (int j = j1 - 1; j >= j0; --j) acc = cadd(cmul(acc, r), f[j]);
-      acc = cmul(d0, acc);
+      acc = cmul(ax.Dfwd[(int64_t)q * M + j0], geometric_sum(f, j0, j1, ax.rfwd[q]));
     }
     part[i] = acc;
   }
@@ -223,31 +263,18 @@ __device__ __forceinline__ void cf_inverse(const double2 (&v3)[RAY], const doubl
   // ends with a barrier: both lines free
   if constexpr (MP == 1) fft_short_out_dual<NU, TL, true, false>(w, w1, w[0], w1[0], t, fline, fline2, tw);
   else fft_regs_dual<NU, TL, true, false>(w, w1, t, fline, fline2, tw);
-  constexpr int DB = 18;   // dense rows per batch of matrix entries
   if constexpr (!CH) {
-    // dm has LDS of its own: E3 part into u, then E1 and the dense modes
+    // dm has LDS of its own
+    double2 acc[MP];
 #pragma unroll
     for (int m = 0; m < MP; ++m) {
-      const int e = t + TL * m;
-      if (e < M) u[e] = cmul(ax.ipost3[e], w[m]);
+      const int ec = min(t + TL * m, M - 1);
+      acc[m] = cadd(cmul(ax.ipost3[ec], w[m]), cmul(ax.ipost1[ec], w1[m]));
     }
+    dense_inverse<TL, MP>(acc, ax.Dinv, dm, 0, ND, M, t);
 #pragma unroll
-    for (int m = 0; m < MP; ++m) {
-      const int e = t + TL * m;
-      if (e < M) {
-        double2 s = cadd(u[e], cmul(ax.ipost1[e], w1[m]));
-        for (int q0 = 0; q0 < ND; q0 += DB) {
-          double2 d[DB];
-#pragma unroll
-          for (int u8 = 0; u8 < DB; ++u8) d[u8] = ax.Dinv[(int64_t)min(q0 + u8, ND - 1) * M + e];
-#pragma unroll
-          for (int u8 = 0; u8 < DB; ++u8) {
-            if (q0 + u8 < ND) s = cadd(s, cmul(d[u8], dm[q0 + u8]));
-          }
-        }
-        u[e] = s;
-      }
-    }
+    for (int m = 0; m < MP; ++m)
+      if (t + TL * m < M) u[t + TL * m] = acc[m];
   } else {
     // dm shares u's LDS.  Contract the C-modes onto the interpolation nodes
     // (eq. (expintrpp) in the form of its values), split over (node, chunk)
@@ -276,23 +303,16 @@ __device__ __forceinline__ void cf_inverse(const double2 (&v3)[RAY], const doubl
       dv[r] = acc;
     }
     __syncthreads();   // dv complete, and every read of dm done: u may be written
+    double2 acc[MP];
 #pragma unroll
     for (int m = 0; m < MP; ++m) {
-      const int e = t + TL * m;
-      if (e < M) {
-        double2 s = cadd(cmul(ax.ipost3[e], w[m]), cmul(ax.ipost1[e], w1[m]));
-        for (int q0 = 0; q0 < NR; q0 += DB) {
-          double2 d[DB];
-#pragma unroll
-          for (int u8 = 0; u8 < DB; ++u8) d[u8] = ax.Dinv[(int64_t)min(q0 + u8, NR - 1) * M + e];
-#pragma unroll
-          for (int u8 = 0; u8 < DB; ++u8) {
-            if (q0 + u8 < NR) s = cadd(s, cmul(d[u8], dv[q0 + u8]));
-          }
-        }
-        u[e] = s;
-      }
+      const int ec = min(t + TL * m, M - 1);
+      acc[m] = cadd(cmul(ax.ipost3[ec], w[m]), cmul(ax.ipost1[ec], w1[m]));
     }
+    dense_inverse<TL, MP>(acc, ax.Dinv, dv, 0, NR, M, t);
+#pragma unroll
+    for (int m = 0; m < MP; ++m)
+      if (t + TL * m < M) u[t + TL * m] = acc[m];
   }
 }
 
@@ -354,10 +374,7 @@ __device__ __forceinline__ void rs_forward(const double2* f, double2 (&v)[RAY], 
     const int j0 = c * L, j1 = min(j0 + L, M);
     double2 acc = {0.0, 0.0};
     if (j0 < M) {
-      const double2 r = ax.rfwd[q];
-      const double2 d0 = ax.Dfwd[(int64_t)q * M + j0];
-      for (int j = j1 - 1; j >= j0; --j) acc = cadd(cmul(acc, r), f[j]);
-      acc = cmul(d0, acc);
+      acc = cmul(ax.Dfwd[(int64_t)q * M + j0], geometric_sum(f, j0, j1, ax.rfwd[q]));
     }
     part[i] = acc;
   }
@@ -455,27 +472,15 @@ __device__ __forceinline__ void rs_inverse(const double2 (&v)[RAY], const double
   // the FFT is done; u shares no LDS with it or with drow, and with the
   // interpolant every read of dm is behind the barrier above), then the E3
   // half adds the two
-  constexpr int DB = 8;
   const int h = NR / 2;
-  const int q0 = ray ? h : 0, q1 = ray ? NR : h;
   double2* dst = ray ? u : fline;
+  double2 acc[MP];
 #pragma unroll
-  for (int m = 0; m < MP; ++m) {
-    const int e = t + TL * m;
-    if (e < M) {
-      double2 acc = cmul(ipost[e], conj_if(!ray, w[m]));
-      for (int qb = q0; qb < q1; qb += DB) {
-        double2 d[DB];
+  for (int m = 0; m < MP; ++m) acc[m] = cmul(ipost[min(t + TL * m, M - 1)], conj_if(!ray, w[m]));
+  dense_inverse<TL, MP>(acc, ax.Dinv, drow, ray ? h : 0, ray ? NR : h, M, t);
 #pragma unroll
-        for (int k = 0; k < DB; ++k) d[k] = ax.Dinv[(int64_t)min(qb + k, q1 - 1) * M + e];
-#pragma unroll
-        for (int k = 0; k < DB; ++k) {
-          if (qb + k < q1) acc = cadd(acc, cmul(d[k], drow[qb + k]));
-        }
-      }
-      dst[e] = acc;
-    }
-  }
+  for (int m = 0; m < MP; ++m)
+    if (t + TL * m < M) dst[t + TL * m] = acc[m];
   __syncthreads();
   if (!ray) {
 #pragma unroll
