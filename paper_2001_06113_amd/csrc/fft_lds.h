@@ -275,22 +275,23 @@ __device__ __forceinline__ void fft_regs(C* v, int t, C* line, const TW& tw) {
 
 // ------------------------------------------------------- short ends of a line
 //
-// A line of N = 8 TL values of which only the first TL can be nonzero going
-// in, or are wanted coming out (radix 8 first).  In: every output of the first
-// pass's butterfly j equals x[j], so the pass and its exchange are one shared
-// copy of x: the second pass reads x[p >> 3] for its element p.  Out: the last
-// pass is one sum per thread over one butterfly's inputs.
+// A line of N = EPT TL values of which only the first TL can be nonzero going
+// in, or are wanted coming out (the first radix is EPT).  In: every output of
+// the first pass's butterfly j equals x[j], so the pass and its exchange are
+// one shared copy of x: the second pass reads x[p / EPT] for its element p.
+// Out: the last pass is one sum per thread over one butterfly's inputs.
 
 // forward: x[t], t < TL, is this thread's; `line` as for fft_regs
 template <int N, int TL, bool INV, typename C, typename TW>
 __device__ __forceinline__ void fft_short_in(C x, C* v, int t, C* line, const TW& tw) {
-  static_assert(N == 8 * TL && TL % 8 == 0 && pick_radix(N, 8) == 8, "radix 8 first");
+  constexpr int EPT = N / TL;
+  static_assert(TL % EPT == 0 && pick_radix(N, EPT) == EPT && EPT < N, "the first radix is EPT");
   line[t] = x;
   __syncthreads();
 #pragma unroll
-  for (int m = 0; m < 8; ++m) v[m] = line[(t >> 3) + (TL / 8) * m];
+  for (int m = 0; m < EPT; ++m) v[m] = line[t / EPT + (TL / EPT) * m];
   __syncthreads();
-  fft_regs_rec<N, TL, 8, INV>(v, t, line, tw);
+  fft_regs_rec<N, TL, EPT, INV>(v, t, line, tw);
 }
 // two lines in their own directions, sharing the barriers (fft_regs_dual)
 template <int N, int TL, bool INVA, bool INVB, typename C, typename TW>

@@ -39,10 +39,10 @@ __device__ __forceinline__ double2 fs_mul_mi(double c, double2 z) { return doubl
 // nodes zeta (|.| != 1 off the real axis), table ph[(j-1)(N1+N2) + k]; in
 // 3D the first N1 = N0 Nm entries are the products of the axis-0 and
 // middle-axis factors of the row (k0, k1).
-__device__ __forceinline__ void build_phase_table_fs(const FSArgs& a, int nthreads) {
+__device__ __forceinline__ void build_phase_table_fs(const FSArgs& a, int blk, int nblk, int nthreads) {
   const int per = a.N1 + a.N2;
   const int total = a.req.nj * per;
-  for (int idx = blockIdx.x * nthreads + threadIdx.x; idx < total; idx += gridDim.x * nthreads) {
+  for (int idx = blk * nthreads + threadIdx.x; idx < total; idx += nblk * nthreads) {
     const int j = idx / per;
     const int kk = idx - j * per;
     // theta = -(z . z) tau + z . dphi (complex); exp(i theta)
@@ -82,6 +82,7 @@ __device__ __forceinline__ void build_phase_table_fs(const FSArgs& a, int nthrea
 // split over (mode, chunk) pairs and reduced through LDS (part, N_D *
 // max(1, TL / N_D) entries, in the second exchange line once its FFT is done).
 constexpr int RAY = 4;
+constexpr int FS_FEW_WAVES = 1024;
 
 // nu-point twiddles from two small tables in LDS (TwPair): 2^LF fine and
 // nu / 2^LF coarse entries, staged from the full table at kernel start
@@ -98,11 +99,13 @@ __device__ __forceinline__ typename fs_tw<NU>::type stage_twiddles(const CFAxis&
   return typename fs_tw<NU>::type{tws, tws + NC};
 }
 
-// Grid points a thread can hold, of the eight FFT slots: one when M <= nu/8
+// Grid points a thread can hold, of its EPT FFT slots: one when M <= nu/EPT
 // (the short ends of fft_lds.h: the first pass going in and most of the last
-// pass coming out drop out), four when M <= nu/2 (the other slots are
-// compile-time zeros going in and unused coming out), else eight.
-__host__ __device__ constexpr int fs_points(int nu, int M) { return M <= nu / 8 ? 1 : M <= nu / 2 ? 4 : 8; }
+// pass coming out drop out), half when M <= nu/2 (the other slots are
+// compile-time zeros going in and unused coming out), else all.
+__host__ __device__ constexpr int fs_points(int nu, int M, int ept) {
+  return M <= nu / ept ? 1 : M <= nu / 2 ? ept / 2 : ept;
+}
 
 // sum_{j0 <= j < j1} r^(j - j0) f[j] (f in LDS): four interleaved Horner sums
 // in r^4, since one is a chain of dependent products (100 points of a row on
@@ -129,7 +132,7 @@ __device__ __forceinline__ double2 geometric_sum(const double2* f, int j0, int j
 template <int TL, int MP>
 __device__ __forceinline__ void dense_inverse(double2 (&acc)[MP], const double2* __restrict__ D, const double2* row,
                                               int q0, int q1, int M, int t) {
-  constexpr int DB = MP == 1 ? 18 : MP == 4 ? 6 : 3;
+  constexpr int DB = MP == 1 ? 18 : MP == 2 ? 12 : MP == 4 ? 6 : 3;
   for (int qb = q0; qb < q1; qb += DB) {
     double2 d[DB][MP];
 #pragma unroll
@@ -316,7 +319,8 @@ __device__ __forceinline__ void cf_inverse(const double2 (&v3)[RAY], const doubl
   }
 }
 
-// Ray-split line transforms: 2 TL threads per line.  Threads [0, TL) carry
+// Ray-split line transforms: 2 TL threads per line, TL = nu / EPT with EPT = 8
+// or 4 slots per thread (a thread carries EPT / 2 modes of its ray).  Threads [0, TL) carry
 // the E3 ray and threads [TL, 2 TL) the E1 ray, each thread one FFT line of
 // its own ray (v[m] = that ray's mode at e = t + TL m, as above).  Both
 // halves run the same forward FFT (the ray whose transform is an inverse FFT
@@ -334,12 +338,11 @@ __device__ __forceinline__ double2 conj_if(bool c, double2 z) { return c ? doubl
 
 // forward transform of f[0..M) (LDS) on the thread's ray; ends with dm
 // complete (a barrier).  dm may share f's LDS (CH), as in cf_forward.
-template <int NU, bool CH, int MP>
-__device__ __forceinline__ void rs_forward(const double2* f, double2 (&v)[RAY], double2* dm, double2* part,
+template <int NU, bool CH, int MP, int EPT>
+__device__ __forceinline__ void rs_forward(const double2* f, double2 (&v)[EPT / 2], double2* dm, double2* part,
                                            double2* fline, double2* fline2, const CFAxis& ax,
                                            const typename fs_tw<NU>::type& tw, int tid) {
-  constexpr int TL = NU / 8, NTH = 2 * TL;
-  constexpr int EPT = 8;
+  constexpr int TL = NU / EPT, NTH = 2 * TL, RAY = EPT / 2;
   const int M = ax.M, NE = ax.NE, ND = ax.ND;
   const bool ray = tid >= TL;   // false: E3 (forward FFT), true: E1 (inverse FFT)
   const int t = ray ? tid - TL : tid;
@@ -415,12 +418,11 @@ __device__ __forceinline__ void rs_forward(const double2* f, double2 (&v)[RAY], 
 // its own entries back without a barrier.  The dense rows are split between
 // the halves.  With the interpolant (CH) dm shares u's LDS: u is written only
 // after every read of dm.
-template <int NU, bool CH, int MP>
-__device__ __forceinline__ void rs_inverse(const double2 (&v)[RAY], const double2* dm, double2* fline,
+template <int NU, bool CH, int MP, int EPT>
+__device__ __forceinline__ void rs_inverse(const double2 (&v)[EPT / 2], const double2* dm, double2* fline,
                                            double2* fline2, const CFAxis& ax, const typename fs_tw<NU>::type& tw,
                                            int tid, double2* u) {
-  constexpr int TL = NU / 8, NTH = 2 * TL;
-  constexpr int EPT = 8;
+  constexpr int TL = NU / EPT, NTH = 2 * TL, RAY = EPT / 2;
   const int M = ax.M, NE = ax.NE, ND = ax.ND, NR = CH ? ax.NR : ND;
   const bool ray = tid >= TL;   // false: E3 (inverse FFT), true: E1 (forward FFT)
   const int t = ray ? tid - TL : tid;
@@ -799,10 +801,13 @@ __device__ __forceinline__ int fs_col_of(int b, int nb) {
 
 // The row pass with 2 TL threads per row: each thread carries RAY modes of
 // one ray (E3 for threads [0, TL), E1 for [TL, 2 TL)) through the forward
-// transform, the recurrence and the inverse transform.
-template <int NU, bool CH, int MP>
-__global__ __launch_bounds__(NU / 4) void k_fs_row_rs(FSArgs a) {
-  constexpr int TL = NU / 8, NTH = 2 * TL;
+// transform, the recurrence and the inverse transform.  The history and the
+// phase factors are read after the forward transform: loaded before it, the
+// transform's own table reads queue behind them (loads complete in order), and
+// the 1D row at nu = 1024 went from 16.0 to 26.6 us.
+template <int NU, bool CH, int EPT, int MP>
+__global__ __launch_bounds__(2 * NU / EPT) void k_fs_row_rs(FSArgs a) {
+  constexpr int TL = NU / EPT, NTH = 2 * TL, RAY = EPT / 2;
   HIP_DYNAMIC_SHARED(double2, fs_lds)
   __shared__ double2 fline2[lds_line_len(NU)];
   double2* part = fline2;
@@ -835,7 +840,7 @@ __global__ __launch_bounds__(NU / 4) void k_fs_row_rs(FSArgs a) {
   if (need_fwd) {
     for (int j = tid; j < M2; j += NTH) fin[j] = a.src[row_p + j];
     __syncthreads();
-    rs_forward<NU, CH, MP>(fin, v, dm, part, fline, fline2, ax, tw, tid);
+    rs_forward<NU, CH, MP, EPT>(fin, v, dm, part, fline, fline2, ax, tw, tid);
   } else {
 #pragma unroll
     for (int m = 0; m < RAY; ++m) v[m] = double2{0.0, 0.0};
@@ -931,7 +936,7 @@ __global__ __launch_bounds__(NU / 4) void k_fs_row_rs(FSArgs a) {
   }
   if (mode == R_UHACC) return;
   __syncthreads();
-  rs_inverse<NU, CH, MP>(v, dm, fline, fline2, ax, tw, tid, fin);
+  rs_inverse<NU, CH, MP, EPT>(v, dm, fline, fline2, ax, tw, tid, fin);
   if (!ray) {
 #pragma unroll
     for (int m = 0; m < MP; ++m) {
@@ -943,9 +948,9 @@ __global__ __launch_bounds__(NU / 4) void k_fs_row_rs(FSArgs a) {
 
 // The column pass with 2 TL threads per column (ray halves as in the row pass);
 // the columns are the ncol points of the other axes (x2, or (x1, x2) in 3D).
-template <int NU, bool CH, int MP>
-__global__ __launch_bounds__(NU / 4) void k_fs_col_rs(FSArgs a) {
-  constexpr int TL = NU / 8, NTH = 2 * TL;
+template <int NU, bool CH, int EPT, int MP>
+__global__ __launch_bounds__(2 * NU / EPT) void k_fs_col_rs(FSArgs a) {
+  constexpr int TL = NU / EPT, NTH = 2 * TL, RAY = EPT / 2;
   HIP_DYNAMIC_SHARED(double2, fs_lds)
   __shared__ double2 fline2[lds_line_len(NU)];
   double2* part = fline2;
@@ -959,11 +964,19 @@ __global__ __launch_bounds__(NU / 4) void k_fs_col_rs(FSArgs a) {
   const int tid = threadIdx.x;
   const bool ray = tid >= TL;
   const int t = ray ? tid - TL : tid;
-  const int y = fs_col_of(blockIdx.x, gridDim.x);
+  // workgroups past the columns build the next row pass's phase table; with
+  // none of them, the columns' own do it first
+  if (a.req.nj > 0) {
+    if ((int64_t)gridDim.x == M2) build_phase_table_fs(a, blockIdx.x, gridDim.x, NTH);
+    else if (blockIdx.x >= M2) {
+      build_phase_table_fs(a, blockIdx.x - (int)M2, gridDim.x - (int)M2, NTH);
+      return;
+    }
+  }
+  const int y = fs_col_of(blockIdx.x, (int)M2);
   const auto tw = stage_twiddles_n<NU>(ax, tws, tid, NTH);
   const int mode = a.mode;
 
-  if (a.req.nj > 0) build_phase_table_fs(a, NTH);
   double2 v[RAY];
   if (mode == C_SOLVE) {
 #pragma unroll
@@ -974,7 +987,7 @@ __global__ __launch_bounds__(NU / 4) void k_fs_col_rs(FSArgs a) {
     }
     for (int q = tid; q < ND; q += NTH) dm[q] = a.src[(int64_t)(NE + q) * M2 + y];
     __syncthreads();
-    rs_inverse<NU, CH, MP>(v, dm, fline, fline2, ax, tw, tid, fin);
+    rs_inverse<NU, CH, MP, EPT>(v, dm, fline, fline2, ax, tw, tid, fin);
     if (!ray) {
 #pragma unroll
       for (int m = 0; m < MP; ++m) {
@@ -1009,7 +1022,7 @@ __global__ __launch_bounds__(NU / 4) void k_fs_col_rs(FSArgs a) {
     }
   }
   __syncthreads();
-  rs_forward<NU, CH, MP>(fin, v, dm, part, fline, fline2, ax, tw, tid);
+  rs_forward<NU, CH, MP, EPT>(fin, v, dm, part, fline, fline2, ax, tw, tid);
 #pragma unroll
   for (int m = 0; m < RAY; ++m) {
     const int e = t + TL * m;
@@ -1024,7 +1037,7 @@ __global__ __launch_bounds__(NU / 4) void k_fs_col_rs(FSArgs a) {
 // points to modes (after it).
 template <int NU, bool CH, bool INV, int MP>
 __global__ __launch_bounds__(NU / 4) void k_fs_mid_rs(FSArgs a) {
-  constexpr int TL = NU / 8, NTH = 2 * TL;
+  constexpr int EPT = 8, TL = NU / EPT, NTH = 2 * TL;
   HIP_DYNAMIC_SHARED(double2, fs_lds)
   __shared__ double2 fline2[lds_line_len(NU)];
   double2* part = fline2;
@@ -1054,7 +1067,7 @@ __global__ __launch_bounds__(NU / 4) void k_fs_mid_rs(FSArgs a) {
     }
     for (int q = tid; q < ND; q += NTH) dm[q] = a.src[mbase + (int64_t)(NE + q) * M2];
     __syncthreads();
-    rs_inverse<NU, CH, MP>(v, dm, fline, fline2, ax, tw, tid, fin);
+    rs_inverse<NU, CH, MP, EPT>(v, dm, fline, fline2, ax, tw, tid, fin);
     if (!ray) {
 #pragma unroll
       for (int m = 0; m < MP; ++m) {
@@ -1065,7 +1078,7 @@ __global__ __launch_bounds__(NU / 4) void k_fs_mid_rs(FSArgs a) {
   } else {
     for (int e = tid; e < Mm; e += NTH) fin[e] = a.src[gbase + (int64_t)e * M2];
     __syncthreads();
-    rs_forward<NU, CH, MP>(fin, v, dm, part, fline, fline2, ax, tw, tid);
+    rs_forward<NU, CH, MP, EPT>(fin, v, dm, part, fline, fline2, ax, tw, tid);
 #pragma unroll
     for (int m = 0; m < RAY; ++m) {
       const int e = t + TL * m;
@@ -1080,7 +1093,7 @@ __global__ __launch_bounds__(NU / 4) void k_fs_mid_rs(FSArgs a) {
 // The 1D problem has no axis-0 transform: the "column pass" is the diagonal
 // solve (or the pre-multiply) on the M2 grid points of the single row.
 __global__ __launch_bounds__(256) void k_fs_point(FSArgs a) {
-  if (a.req.nj > 0) build_phase_table_fs(a, 256);
+  if (a.req.nj > 0) build_phase_table_fs(a, blockIdx.x, gridDim.x, 256);
   const int e = blockIdx.x * 256 + threadIdx.x;
   const int M2 = a.ax2.M;
   if (e >= M2) return;
@@ -1107,7 +1120,7 @@ __global__ __launch_bounds__(256) void k_fs_point(FSArgs a) {
 }
 
 // phase table only (before a row pass that has no transform-carrying column pass)
-__global__ __launch_bounds__(256) void k_fs_phase(FSArgs a) { build_phase_table_fs(a, 256); }
+__global__ __launch_bounds__(256) void k_fs_phase(FSArgs a) { build_phase_table_fs(a, blockIdx.x, gridDim.x, 256); }
 
 // ---------------------------------------------------------------- dispatch
 
@@ -1124,24 +1137,35 @@ __global__ __launch_bounds__(256) void k_fs_phase(FSArgs a) { build_phase_table_
     if (E0) hipExtLaunchKernelGGL(K, G, B, SH, S, E0, E1, 0, A);   \
     else hipLaunchKernelGGL(K, G, B, SH, S, A);                    \
   } while (0)
-// a line kernel K<nu, CH, ...> over the interpolant and the points per thread of axis AX
-#define TDSE_FS_LINE(K, n, AX, G, B, S, E0, E1, A, ...)                                                     \
-  do {                                                                                                      \
-    const size_t sh_ = fs_lds_bytes<n>(AX.M, AX.ND, AX.NT != 0);                                            \
-    switch (fs_points(n, AX.M)) {                                                                           \
-      case 1:                                                                                               \
-        if (AX.NT) TDSE_FS_LAUNCH_SH((K<n, true, ##__VA_ARGS__, 1>), G, B, sh_, S, E0, E1, A);              \
-        else TDSE_FS_LAUNCH_SH((K<n, false, ##__VA_ARGS__, 1>), G, B, sh_, S, E0, E1, A);                   \
-        break;                                                                                              \
-      case 4:                                                                                               \
-        if (AX.NT) TDSE_FS_LAUNCH_SH((K<n, true, ##__VA_ARGS__, 4>), G, B, sh_, S, E0, E1, A);              \
-        else TDSE_FS_LAUNCH_SH((K<n, false, ##__VA_ARGS__, 4>), G, B, sh_, S, E0, E1, A);                   \
-        break;                                                                                              \
-      default:                                                                                              \
-        if (AX.NT) TDSE_FS_LAUNCH_SH((K<n, true, ##__VA_ARGS__, 8>), G, B, sh_, S, E0, E1, A);              \
-        else TDSE_FS_LAUNCH_SH((K<n, false, ##__VA_ARGS__, 8>), G, B, sh_, S, E0, E1, A);                   \
-    }                                                                                                       \
+// a line kernel K<nu, CH, ..., MP> over the interpolant of axis AX
+#define TDSE_FS_CH(K, n, MP, AX, G, B, S, E0, E1, A, ...)                                                \
+  do {                                                                                                   \
+    const size_t sh_ = fs_lds_bytes<n>(AX.M, AX.ND, AX.NT != 0);                                         \
+    if (AX.NT) TDSE_FS_LAUNCH_SH((K<n, true, ##__VA_ARGS__, MP>), G, B, sh_, S, E0, E1, A);              \
+    else TDSE_FS_LAUNCH_SH((K<n, false, ##__VA_ARGS__, MP>), G, B, sh_, S, E0, E1, A);                   \
   } while (0)
+// ... and the points per thread, of eight slots
+#define TDSE_FS_LINE(K, n, AX, G, B, S, E0, E1, A, ...)                                                   \
+  do {                                                                                                   \
+    switch (fs_points(n, AX.M, 8)) {                                                                     \
+      case 1: TDSE_FS_CH(K, n, 1, AX, G, B, S, E0, E1, A, ##__VA_ARGS__); break;                         \
+      case 4: TDSE_FS_CH(K, n, 4, AX, G, B, S, E0, E1, A, ##__VA_ARGS__); break;                         \
+      default: TDSE_FS_CH(K, n, 8, AX, G, B, S, E0, E1, A, ##__VA_ARGS__);                               \
+    }                                                                                                    \
+  } while (0)
+// ... or of four (M <= nu/2)
+#define TDSE_FS_LINE4(K, n, AX, G, B, S, E0, E1, A)                                                      \
+  do {                                                                                                   \
+    if (fs_points(n, AX.M, 4) == 1) TDSE_FS_CH(K, n, 1, AX, G, B, S, E0, E1, A, 4);                      \
+    else TDSE_FS_CH(K, n, 2, AX, G, B, S, E0, E1, A, 4);                                                 \
+  } while (0)
+
+// Lines so few that they are at most one wave per SIMD with eight slots per
+// thread (a line has nu / 256 waves): four slots then, twice the threads.
+// Column and row pass of 100 columns and 270 rows at nu = 256: 14.2 and 17.6 ->
+// 11.0 and 14.3 us; 1024 columns at nu = 256: 19.4 -> 17.1 us; the 256 columns
+// of nu = 2048, two waves per SIMD already, would go from 24.0 to 27.0 us.
+inline bool fs_few(int nu, int64_t lines, int M) { return lines * nu <= (int64_t)FS_FEW_WAVES * 256 && M <= nu / 2; }
 
 bool fs_nu_supported(int nu) {
   switch (nu) {
@@ -1174,7 +1198,8 @@ hipError_t launch_fs_row(int nu, const FSArgs& a, hipStream_t s, hipEvent_t e0, 
     switch (nu) {
 #define X(n) \
   case n: \
-    TDSE_FS_LINE(k_fs_row_rs, n, a.ax2, dim3(a.N1), dim3(n / 4), s, e0, e1, a); \
+    if (fs_few(n, a.N1, a.ax2.M)) TDSE_FS_LINE4(k_fs_row_rs, n, a.ax2, dim3(a.N1), dim3(n / 2), s, e0, e1, a); \
+    else TDSE_FS_LINE(k_fs_row_rs, n, a.ax2, dim3(a.N1), dim3(n / 4), s, e0, e1, a, 8); \
     break;
       TDSE_FS_NU(X)
 #undef X
@@ -1204,10 +1229,15 @@ hipError_t launch_fs_col(int nu, const FSArgs& a, hipStream_t s, hipEvent_t e0, 
     TDSE_FS_LAUNCH(k_fs_point, dim3((unsigned)blocks), dim3(256), s, e0, e1, a);
     return hipGetLastError();
   }
+  // with fewer columns than compute units, workgroups of their own build the
+  // phase table beside the columns
+  const int64_t entries = (int64_t)a.req.nj * (a.N1 + a.N2);
+  const int64_t pb = a.ncol < 256 && entries > 0 ? std::min<int64_t>((entries + nu / 4 - 1) / (nu / 4), 256) : 0;
   switch (nu) {
 #define X(n) \
   case n: \
-    TDSE_FS_LINE(k_fs_col_rs, n, a.ax1, dim3((unsigned)a.ncol), dim3(n / 4), s, e0, e1, a); \
+    if (fs_few(n, a.ncol, a.ax1.M)) TDSE_FS_LINE4(k_fs_col_rs, n, a.ax1, dim3((unsigned)(a.ncol + pb)), dim3(n / 2), s, e0, e1, a); \
+    else TDSE_FS_LINE(k_fs_col_rs, n, a.ax1, dim3((unsigned)(a.ncol + pb)), dim3(n / 4), s, e0, e1, a, 8); \
     break;
       TDSE_FS_NU(X)
 #undef X
