@@ -17,7 +17,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libtdse.so")
 
-HIP_SOURCES = ["periodic_kernels.hip", "freespace_kernels.hip", "batch_fp64.hip", "batch_split.hip",
+HIP_SOURCES = ["freespace_kernels.hip", "periodic_kernels.hip", "freespace_run1d.hip", "batch_fp64.hip", "batch_split.hip",
                "adjoint_kernels.hip", "far_kernels.hip", "run1d_kernels.hip", "persist2d_kernels.hip",
                "diag_kernels.hip"]
 HOST_SOURCES = ["tdse_api.cpp"]

@@ -384,6 +384,14 @@ struct tdse_plan_s {
   size_t o_r1tab = 0, o_r1stab = 0, total_core = 0;
   int64_t r1_oH = 0, r1_oR = 0, r1_oA = 0, r1_oD = 0;
 
+  // one-workgroup Adams steps of a 1D free-space plan (freespace_run1d.hip):
+  // per-step scalars and the phase factors of one launch's steps, at the end
+  // of the workspace
+  bool fs1d = false;          // the plan qualifies
+  bool fs1d_on = false;       // the current run's Adams steps take it (chosen at the Adams start)
+  std::vector<double> f1tab;
+  size_t o_f1tab = 0, o_f1e = 0;
+
   // persistent Adams steps of a square 2D periodic FP64 plan
   // (persist2d_kernels.hip): per-step scalars, static column factors and the
   // timeout flag, at the end of the workspace
@@ -1443,13 +1451,71 @@ int fs_am_step(tdse_plan_s* p, int m, bool write_u) {
   return fs_launch(p, false, r, true);
 }
 
+// uhat_0 = F u0 and What_0 = F(V(0) u0) (Section 3.3)
+int fs_initial(tdse_plan_s* p) {
+  const int s = fs_forward(p, 0.0, 1.0, 0.0, 0.0, 0.0, p->UH(p->uh_cur));
+  return s ? s : fs_history(p, 0);
+}
+
+// ---- 1D, one workgroup (freespace_run1d.hip)
+// scalars per step time (layout in tdse_internal.h)
+void build_fs1d(tdse_plan_s* p) {
+  p->f1tab.assign((size_t)(p->nsteps + 1) * FSRUN1D_COLS, 0.0);
+  double pb[3], pa[3];
+  for (int m = 0; m <= p->nsteps; ++m) {
+    double* r = p->f1tab.data() + (size_t)m * FSRUN1D_COLS;
+    int64_t first = 0;
+    r[9] = (double)p->V_window(p->t_at(m), r, &first);
+    r[8] = (double)first;
+    if (m == 0) continue;
+    p->tf.phi(p->t_at(m), pb);
+    p->tf.phi(p->t_at(m - 1), pa);
+    r[FSRUN1D_COLS - 1] = pb[0] - pa[0];
+  }
+}
+
+int upload_fs1d(tdse_plan_s* p) {
+  HIP_TRY(hipMemcpyAsync(p->ws + p->o_f1tab, p->f1tab.data(), p->f1tab.size() * sizeof(double), hipMemcpyHostToDevice,
+                         p->stream));
+  return TDSE_OK;
+}
+
+// Adams steps cur+1 .. end (cur >= ns), FSRUN1D_STEPS per launch
+int fs1d_steps(tdse_plan_s* p, int end) {
+  if (p->cur == p->ns) {
+    int s = p->ns == 0 ? fs_initial(p) : TDSE_OK;
+    if (!s) s = fs_am_init(p);
+    if (s) return s;
+  }
+  while (p->cur < end) {
+    FSRun1DArgs a;
+    std::memset(&a, 0, sizeof(a));
+    a.ax = cf_axis(p, 1);
+    a.order = p->order;
+    a.nsteps = p->nsteps;
+    a.m0 = p->cur;
+    a.m1 = std::min(end, p->cur + FSRUN1D_STEPS);
+    a.i0 = std::max(1, a.m0 + 1 - (p->order - 3));   // the oldest held entry is propagated over order - 2 intervals
+    a.dt = p->dt;
+    a.c0 = p->mu[0] * p->dt;
+    for (int j = 1; j < p->order; ++j) a.ch[j] = p->dt * p->mu[j];
+    a.V = (const double*)(p->ws + p->o_Vf);
+    a.vstride = p->P;
+    a.tab = (const double*)(p->ws + p->o_f1tab);
+    a.etab = (double2*)(p->ws + p->o_f1e);
+    a.Bm = p->B();
+    a.ring = (double2*)(p->ws + p->o_ringf);
+    a.uout = p->u(p->ucur);
+    const hipError_t e = launch_fs_run1d(p->fx[1].nu, a, p->stream);
+    if (e != hipSuccess) return fail(TDSE_EDEVICE, std::string("1D free-space run kernel: ") + hipGetErrorString(e));
+    p->cur = a.m1;
+  }
+  return TDSE_OK;
+}
+
 int fs_step(tdse_plan_s* p, int m, bool write_u) {
   int s = TDSE_OK;
-  if (m == 1) {
-    // uhat_0 = F u0 and What_0 = F(V(0) u0) (Section 3.3)
-    s = fs_forward(p, 0.0, 1.0, 0.0, 0.0, 0.0, p->UH(p->uh_cur));
-    if (!s) s = fs_history(p, 0);
-  }
+  if (m == 1) s = fs_initial(p);
   if (s) return s;
   if (m <= p->ns) {
     s = fs_richardson(p, m);
@@ -1549,6 +1615,12 @@ int plan_free(tdse_plan_s* p, const tdse_problem_t* prob) {
   for (int a = 0; a < (d3 ? 3 : 2); ++a) {
     p->fx[a].o_tab = off;
     off = align256(off + p->fx[a].tables.size());
+  }
+  if (p->dim == 1 && p->nsteps > p->ns && fs_run1d_supported(p->fx[1].nu, cf_axis(p, 1))) {
+    p->fs1d = true;
+    build_fs1d(p);
+    p->o_f1tab = off; off = align256(off + p->f1tab.size() * sizeof(double));
+    p->o_f1e = off; off = align256(off + (size_t)(FSRUN1D_STEPS + MAXH) * p->NM * sizeof(double2));
   }
   p->total = off;
   return TDSE_OK;
@@ -3156,6 +3228,10 @@ int tdse_bind(tdse_plan_t p, void* ws, size_t bytes, void* stream) {
     const int s = upload_persist2d(p);
     if (s) return s;
   }
+  if (p->fs1d) {
+    const int s = upload_fs1d(p);
+    if (s) return s;
+  }
   if (p->free_space) {
     HIP_TRY(hipMemcpyAsync(p->ws + p->o_Vf, p->Vsrc.data(), p->Vsrc.size() * sizeof(double), hipMemcpyHostToDevice,
                            p->stream));
@@ -3226,6 +3302,17 @@ int step_range(tdse_plan_s* p, int k) {
   if (p->is_batch()) return batch_step(p, k);
   const int end = p->cur + k;
   if (p->run1d) return k > 0 ? run1d_step(p, end) : TDSE_OK;
+  // chosen once per run: the general path carries a tile that this one does
+  // not; timed passes (tdse_profile) are the general path's
+  if (p->fs1d && end > p->ns && p->cur <= p->ns) p->fs1d_on = !p->prof;
+  if (p->fs1d && end > p->ns && p->fs1d_on) {
+    for (int m = p->cur + 1; m <= p->ns; ++m) {
+      const int s = do_step(p, m, false);
+      if (s) return s;
+      p->cur = m;
+    }
+    return fs1d_steps(p, end);
+  }
   if (p->persist && p->persist_on && end > p->ns + 1 && !capturing(p->stream)) {
     // start-up and the Adams start by the passes, the rest in one persistent launch
     for (int m = p->cur + 1; m <= p->ns + 1; ++m) {
@@ -3707,6 +3794,13 @@ int tdse_set_field(tdse_plan_t p, const double* A_steps) {
     if (p->bound) {
       HIP_TRY(hipStreamSynchronize(p->stream));
       HIP_TRY(hipMemcpy(p->ws + p->o_r1tab, p->r1tab.data(), p->r1tab.size() * sizeof(double), hipMemcpyHostToDevice));
+    }
+  }
+  if (p->fs1d) {
+    build_fs1d(p);
+    if (p->bound) {
+      HIP_TRY(hipStreamSynchronize(p->stream));
+      HIP_TRY(hipMemcpy(p->ws + p->o_f1tab, p->f1tab.data(), p->f1tab.size() * sizeof(double), hipMemcpyHostToDevice));
     }
   }
   if (p->persist) {

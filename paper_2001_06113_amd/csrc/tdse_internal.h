@@ -293,6 +293,29 @@ hipError_t launch_fs_phase(const FSArgs& a, hipStream_t s);
 hipError_t launch_fs_mid(int nu, bool inverse, const FSArgs& a, hipStream_t s, hipEvent_t e0 = nullptr,
                          hipEvent_t e1 = nullptr);
 bool fs_nu_supported(int nu);
+
+// One-workgroup run of a 1D free-space problem (freespace_run1d.hip): Adams
+// steps m0+1 .. m1 (past the Adams start).  tab: FSRUN1D_COLS doubles per step
+// time m = 0..nsteps: the weights of the potential fields at t_m, the first
+// of them, their number, -, and phi(t_m) - phi(t_{m-1}).  etab: phase factors of the
+// intervals i0 .. m1+1 (i: [t_{i-1}, t_i]), filled by the launch, at most
+// FSRUN1D_STEPS + MAXH rows of N.
+constexpr int FSRUN1D_COLS = 12, FSRUN1D_STEPS = 128;
+struct FSRun1DArgs {
+  CFAxis ax;
+  int order, nsteps, m0, m1, i0, dinv_lds;
+  double dt, c0;
+  double ch[MAXH + 1];
+  const double* V;
+  int64_t vstride;
+  const double* tab;
+  double2* etab;
+  double2* Bm;
+  double2* ring;
+  double2* uout;
+};
+bool fs_run1d_supported(int nu, const CFAxis& ax);
+hipError_t launch_fs_run1d(int nu, const FSRun1DArgs& a, hipStream_t s);
 size_t fs_line_lds_bytes(int nu, int M, int ND, bool ch);   // dynamic LDS of a line workgroup (ch: interpolant on)
 
 // Evaluation of a free-space representation at arbitrary points (far_kernels.hip).

@@ -9,6 +9,7 @@ ROOT = os.path.dirname(os.path.dirname(HERE))
 CSRC = os.path.join(ROOT, "paper_2001_06113_amd", "csrc")
 OUT = os.path.join(HERE, "libtdse_emu.so")
 SOURCES = [os.path.join(CSRC, "periodic_kernels.hip"), os.path.join(CSRC, "freespace_kernels.hip"),
+           os.path.join(CSRC, "freespace_run1d.hip"),
            os.path.join(CSRC, "batch_fp64.hip"), os.path.join(CSRC, "batch_split.hip"),
            os.path.join(CSRC, "adjoint_kernels.hip"), os.path.join(CSRC, "far_kernels.hip"),
            os.path.join(CSRC, "run1d_kernels.hip"), os.path.join(CSRC, "persist2d_kernels.hip"),
