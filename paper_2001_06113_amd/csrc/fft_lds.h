@@ -473,8 +473,9 @@ __device__ __forceinline__ void hold_twiddles(C* held, int t, const C* tw) {
   }
 }
 
-template <int N, bool BA, bool INV, int Ns, int AT, typename C>
-__device__ __forceinline__ void fft_held_rec(C* v, int t, C* la, C* lb, const C* held) {
+// `tw`: the thread's held twiddles (HELD), or the full table
+template <int N, bool BA, bool INV, int Ns, int AT, bool HELD, typename C>
+__device__ __forceinline__ void fft_held_rec(C* v, int t, C* la, C* lb, const C* tw) {
   constexpr int R = held_radix<N, Ns, BA>(), E = held_ept(R), T = N / E, B = E / R;
   constexpr bool LAST = (Ns * R == N);
   if (N % 3 != 0 || t < T) {
@@ -486,7 +487,7 @@ __device__ __forceinline__ void fft_held_rec(C* v, int t, C* la, C* lb, const C*
       if constexpr (Ns > 1) {
 #pragma unroll
         for (int r = 1; r < R; ++r) {
-          C w = held[AT + b * (R - 1) + r - 1];
+          C w = tw[HELD ? AT + b * (R - 1) + r - 1 : r * ((t + b * T) % Ns) * (N / (Ns * R))];
           if (INV) w.y = -w.y;
           x[b][r] = cmul(x[b][r], w);
         }
@@ -516,15 +517,15 @@ __device__ __forceinline__ void fft_held_rec(C* v, int t, C* la, C* lb, const C*
 #pragma unroll
       for (int m = 0; m < EN; ++m) v[m] = la[lds_slot(t + TN * m)];
     }
-    fft_held_rec<N, BA, INV, Ns * R, AT + (Ns > 1 ? B * (R - 1) : 0)>(v, t, lb, la, held);
+    fft_held_rec<N, BA, INV, Ns * R, AT + (Ns > 1 ? B * (R - 1) : 0), HELD>(v, t, lb, la, tw);
   }
 }
 // FFT of one line from layout A to B (BA: from B to A) through the exchange
 // lines la and lb (la first); swaps the two after an odd number of exchanges,
 // so that the caller's next transform may use them as they are.
-template <int N, bool BA, bool INV, typename C>
-__device__ __forceinline__ void fft_held(C* v, int t, C*& la, C*& lb, const C* held) {
-  fft_held_rec<N, BA, INV, 1, 0>(v, t, la, lb, held);
+template <int N, bool BA, bool INV, bool HELD = true, typename C>
+__device__ __forceinline__ void fft_held(C* v, int t, C*& la, C*& lb, const C* tw) {
+  fft_held_rec<N, BA, INV, 1, 0, HELD>(v, t, la, lb, tw);
   if constexpr (exchange_count<N, BA>() % 2 == 1) {
     C* x = la;
     la = lb;

@@ -546,6 +546,278 @@ __device__ __forceinline__ void row_body(const LineArgs& a, int line0, C* lds) {
 }
 
 
+
+// ------------------------------------------------------ FP64, lengths 3 * 2^a
+//
+// The passes above for double2 lines of 24..768 points with a factor 3, in the
+// two layouts of fft_lds.h: tile elements go in and out four per thread, the
+// pointwise work and the history have three, N/3 threads per line.  With six or
+// twelve elements per thread in one layout, most passes of a transform are of
+// radix 2, or one wave holds several lines and reads the history at first use
+// (a 64 x 96 row pass: four workgroups, 16.8 us).  Whole steps, us: 64 x 96
+// 31.0 -> 18.8, 192 x 768 36.4 -> 24.9, 384 x 512 30.8 -> 28.0, 768^2 65.1 ->
+// 56.1, 96^3 246 -> 185.  The complex64 form keeps the passes above.
+__host__ __device__ constexpr bool three_smooth(int N) { return N % 3 == 0 && N >= 24 && N <= 768; }
+constexpr int tri_tl(int N) { return N / 3; }
+constexpr int tri_row_lpw(int N) { return 64 / tri_tl(N) > 1 ? 64 / tri_tl(N) : 1; }
+constexpr int tri_col_lpw(int N) { return N >= 384 ? 2 : 4; }
+template <int N, int LPW>
+struct tri_lds {
+  static constexpr int PITCH = lds_line_len(N) + 1;
+  static constexpr int elems = 2 * LPW * PITCH + N;   // two lines per line, then the twiddles
+};
+
+template <int N, int LPW>
+__device__ __forceinline__ void tri_col_body(const LineArgs& a, int line0, int blk, int nblk, double2* lds) {
+  constexpr int EA = 4, TA = N / EA, EPT = 3, TL = N / EPT, NT = LPW * TL, PITCH = tri_lds<N, LPW>::PITCH;
+  double2* twl = lds + 2 * LPW * PITCH;
+  const int tid = threadIdx.x, i = tid % LPW, t = tid / LPW;
+  const int line = line0 + i;
+  const bool active = line < a.nlines, inA = t < TA;
+  const int64_t es = a.elem_stride;
+  const int64_t g0 = active ? (int64_t)line * a.line_stride : 0;
+  const double2* __restrict__ src = (const double2*)a.src;
+  const double* __restrict__ V = (const double*)a.V;
+  double2* la = lds + i * PITCH;
+  double2* lb = lds + (LPW + i) * PITCH;
+  double2 twr[(N + NT - 1) / NT];
+#pragma unroll
+  for (int k = 0; k < (N + NT - 1) / NT; ++k) {
+    const int q = tid + k * NT;
+    twr[k] = ((const double2*)a.tw)[q < N ? q : 0];
+  }
+  double2 v[EA];
+#pragma unroll
+  for (int m = 0; m < EA; ++m) v[m] = double2{0.0, 0.0};
+  if (active) {
+    if (a.mode == C_FWD) {
+#pragma unroll
+      for (int m = 0; m < EPT; ++m) v[m] = src[g0 + (int64_t)(t + TL * m) * es];
+    } else if (inA) {
+#pragma unroll
+      for (int m = 0; m < EA; ++m) v[m] = src[g0 + (int64_t)(t + TA * m) * es];
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < (N + NT - 1) / NT; ++k) {
+    const int q = tid + k * NT;
+    if (q < N) twl[q] = twr[k];
+  }
+  double v0[EPT];
+#pragma unroll
+  for (int m = 0; m < EPT; ++m) v0[m] = active && a.nV > 0 ? V[g0 + (int64_t)(t + TL * m) * es] : 0.0;
+  constexpr double PI = 3.14159265358979323846264338327950288;
+  const bool well = a.vkind == 1;
+  const int wK = well ? (int)a.fV[4] : 0;
+  const double wline = well ? a.fV[0] * well_images(-PI + 2.0 * PI * line / a.M2 - a.fV[3], a.fV[1], wK) : 0.0;
+  const double f0 = a.nV > 0 ? a.fV[0] : 0.0;
+  auto V_at = [&](int m) -> double {
+    if (well) return wline * well_images(-PI + 2.0 * PI * (t + TL * m) / a.M1 - a.fV[2], a.fV[1], wK);
+    double s = f0 * v0[m];
+    for (int r = 1; r < a.nV; ++r) s += a.fV[r] * V[r * a.vstride + g0 + (int64_t)(t + TL * m) * es];
+    return s;
+  };
+  __syncthreads();
+  if (a.mode == C_FWD) {
+#pragma unroll
+    for (int m = 0; m < EPT; ++m) {
+      const double Vs = V_at(m);
+      const double cr = a.alpha_re + a.beta_re * Vs, ci = a.alpha_im + a.beta_im * Vs;
+      v[m] = double2{(cr * v[m].x - ci * v[m].y) * a.scale, (cr * v[m].y + ci * v[m].x) * a.scale};
+    }
+  } else {  // C_SOLVE
+    fft_held<N, false, true, false>(v, t, la, lb, twl);
+#pragma unroll
+    for (int m = 0; m < EPT; ++m) {
+      const double Vs = V_at(m), q = a.csolve * Vs, inv = 1.0 / (1.0 + q * q);
+      const double2 u = double2{(v[m].x + q * v[m].y) * inv, (v[m].y - q * v[m].x) * inv};
+      if (active) {
+        const int64_t g = g0 + (int64_t)(t + TL * m) * es;
+        if (a.uout) a.uout[g] = u;
+        if (a.uacc) {
+          double2 acc = a.acc_first ? double2{0.0, 0.0} : a.uacc[g];
+          acc.x += a.wacc * u.x;
+          acc.y += a.wacc * u.y;
+          a.uacc[g] = acc;
+        }
+      }
+      const double s = Vs * a.scale;
+      v[m] = double2{s * u.x, s * u.y};
+    }
+  }
+  fft_held<N, true, false, false>(v, t, la, lb, twl);
+  if (active && inA) {
+#pragma unroll
+    for (int m = 0; m < EA; ++m) ((double2*)a.dst)[g0 + (int64_t)(t + TA * m) * es] = v[m];
+  }
+  if (a.req.nj > 0) build_phase_table(a, NT, blk, nblk);
+}
+
+template <int N, int LPW, bool INV>
+__device__ __forceinline__ void tri_mid_body(const LineArgs& a, int line0, double2* lds) {
+  constexpr int EA = 4, TA = N / EA, EPT = 3, TL = N / EPT, NT = LPW * TL, PITCH = tri_lds<N, LPW>::PITCH;
+  double2* twl = lds + 2 * LPW * PITCH;
+  const int tid = threadIdx.x, i = tid % LPW, t = tid / LPW;
+  const int line = line0 + i;
+  const bool active = line < a.nlines, inA = t < TA;
+  const int64_t base = (int64_t)(line / a.slab_lines) * a.slab_stride + (int64_t)(line % a.slab_lines) * a.line_stride;
+  double2* la = lds + i * PITCH;
+  double2* lb = lds + (LPW + i) * PITCH;
+  for (int q = tid; q < N; q += NT) twl[q] = ((const double2*)a.tw)[q];
+  double2 v[EA];
+#pragma unroll
+  for (int m = 0; m < EA; ++m)
+    v[m] = active && inA ? ((const double2*)a.src)[base + (int64_t)(t + TA * m) * a.elem_stride] : double2{0.0, 0.0};
+  __syncthreads();
+  fft_held<N, false, INV, false>(v, t, la, lb, twl);
+  if (active) {
+#pragma unroll
+    for (int m = 0; m < EPT; ++m) ((double2*)a.dst)[base + (int64_t)(t + TL * m) * a.elem_stride] = v[m];
+  }
+}
+
+template <int N, int LPW, bool PW>
+__device__ __forceinline__ void tri_row_body(const LineArgs& a, int line0, double2* lds) {
+  constexpr int EA = 4, TA = N / EA, EPT = 3, TL = N / EPT, NT = LPW * TL, NH = MAXH - 1;
+  constexpr int PITCH = tri_lds<N, LPW>::PITCH, TWN = (N + NT - 1) / NT;
+  double2* twl = lds + 2 * LPW * PITCH;
+  const int tid = threadIdx.x, i = tid / TL, t = tid % TL;
+  const int k1 = line0 + i;
+  const bool active = k1 < a.nlines, inA = t < TA;
+  const int mode = a.mode, per = a.M1 + a.M2, nh = a.nh, M1 = a.M1;
+  const int64_t row0 = active ? (int64_t)k1 * a.line_stride : 0;
+  const double2* __restrict__ ph = a.ph;
+  const double2* __restrict__ ring = (const double2*)a.ring;
+  const int64_t rstride = a.ring_stride;
+  double2* la = lds + i * PITCH;
+  double2* lb = lds + (LPW + i) * PITCH;
+  int slot_r[MAXH + 1];
+#pragma unroll
+  for (int j = 0; j <= MAXH; ++j) slot_r[j] = a.slot_r[j];
+  // loads in the order of first use (see the load order above)
+  double2 twr[TWN];
+#pragma unroll
+  for (int k = 0; k < TWN; ++k) {
+    const int q = tid + k * NT;
+    twr[k] = ((const double2*)a.tw)[q < N ? q : 0];
+  }
+  double2 T1[NH];
+  const bool phases = active && mode != R_FWD && mode != R_INV;
+  const int nj = (mode == R_INIT) ? 1 : nh;
+  if (phases) {
+    const int njc = nj > 1 ? nj : 1;
+#pragma unroll
+    for (int j = 1; j <= NH; ++j) T1[j - 1] = ph[((j < njc ? j : njc) - 1) * per + k1];
+  }
+  double2 v[EA];
+#pragma unroll
+  for (int m = 0; m < EA; ++m) v[m] = double2{0.0, 0.0};
+  if (active) {
+    if (mode == R_INV) {
+#pragma unroll
+      for (int m = 0; m < EPT; ++m) v[m] = a.Bm[row0 + t + TL * m];
+    } else if (inA) {
+#pragma unroll
+      for (int m = 0; m < EA; ++m) v[m] = ((const double2*)a.src)[row0 + t + TA * m];
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < TWN; ++k) {
+    const int q = tid + k * NT;
+    if (q < N) twl[q] = twr[k];
+  }
+  double2 Bp[EPT], P1[EPT], Wr[NH - 1][EPT], T2[PW ? 1 : NH - 1][EPT];
+  if (active && mode == R_AM) {
+#pragma unroll
+    for (int m = 0; m < EPT; ++m) Bp[m] = a.Bm[row0 + t + TL * m];
+#pragma unroll
+    for (int j = 2; j <= NH; ++j) {
+      if (j <= nh) {
+#pragma unroll
+        for (int m = 0; m < EPT; ++m) Wr[j - 2][m] = ring[slot_r[j] * rstride + row0 + t + TL * m];
+      }
+    }
+  }
+  if (phases) {
+#pragma unroll
+    for (int m = 0; m < EPT; ++m) P1[m] = ph[M1 + t + TL * m];
+    if constexpr (!PW) {
+#pragma unroll
+      for (int j = 2; j <= NH; ++j) {
+        if (j <= nj) {
+#pragma unroll
+          for (int m = 0; m < EPT; ++m) T2[j - 2][m] = ph[(j - 1) * per + M1 + t + TL * m];
+        }
+      }
+    }
+  }
+  __syncthreads();
+  if (mode != R_INV) fft_held<N, false, false, false>(v, t, la, lb, twl);
+  if (mode == R_FWD) {
+    if (active) {
+#pragma unroll
+      for (int m = 0; m < EPT; ++m) ((double2*)a.fdst)[row0 + t + TL * m] = v[m];
+    }
+    return;
+  }
+  // (one loop per mode: a choice between a register array and memory would
+  // put the array into scratch)
+  if (active && mode == R_INIT) {
+#pragma unroll
+    for (int m = 0; m < EPT; ++m) {
+      v[m] = cmul(cmul(T1[0], P1[m]), v[m]);
+      a.Bm[row0 + t + TL * m] = v[m];
+    }
+  } else if (active && mode == R_AM) {
+#pragma unroll
+    for (int m = 0; m < EPT; ++m) {
+      const double2 W = v[m];
+      const double2 uh = cadd(Bp[m], mul_mi(a.c0, W));
+      double2 acc = cmul(cmul(T1[0], P1[m]), cadd(uh, mul_mi(a.ch[1], W)));
+      double2 hist = double2{0.0, 0.0}, R = P1[m];
+#pragma unroll
+      for (int j = 2; j <= NH; ++j) {
+        if (j <= nh) {
+          double2 Ej;
+          if constexpr (PW) {
+            R = cmul(R, P1[m]);
+            Ej = cmul(T1[j - 1], R);
+          } else {
+            Ej = cmul(T1[j - 1], T2[j - 2][m]);
+          }
+          hist = cadd(hist, mul_mi(a.ch[j], cmul(Ej, Wr[j - 2][m])));
+        }
+      }
+      acc = cadd(acc, hist);
+      const int64_t g = row0 + t + TL * m;
+      if (a.slot_w >= 0) ((double2*)a.ring)[a.slot_w * rstride + g] = W;
+      a.Bw[g] = acc;
+      v[m] = acc;
+    }
+  } else if (active && mode == R_FORM) {   // uhat is this transform, and every history entry comes from the ring
+#pragma unroll
+    for (int m = 0; m < EPT; ++m) {
+      const int64_t g = row0 + t + TL * m;
+      double2 acc = cmul(cmul(T1[0], P1[m]), cadd(v[m], mul_mi(a.ch[1], ring[slot_r[1] * rstride + g])));
+      double2 hist = double2{0.0, 0.0};
+#pragma unroll
+      for (int j = 2; j <= NH; ++j) {
+        if (j <= nh)
+          hist = cadd(hist, mul_mi(a.ch[j], cmul(cmul(T1[j - 1], ph[(j - 1) * per + M1 + t + TL * m]),
+                                                 ring[slot_r[j] * rstride + g])));
+      }
+      acc = cadd(acc, hist);
+      a.Bm[g] = acc;
+      v[m] = acc;
+    }
+  }
+  fft_held<N, true, true, false>(v, t, la, lb, twl);
+  if (active && inA) {
+#pragma unroll
+    for (int m = 0; m < EA; ++m) ((double2*)a.dst)[row0 + t + TA * m] = v[m];
+  }
+}
+
 // -------------------------------------------------------------- schedules
 
 // Column pass: EPT elements per thread (4 for lengths 256..1024, 8 otherwise,

@@ -34,6 +34,26 @@ __global__ __launch_bounds__(LPW * TL) void k_row(LineArgs a) {
   row_body<C, N, LPW, TL, PW>(a, blockIdx.x * LPW, lds);
 }
 
+// ------------------------------------------------------ FP64, lengths 3 * 2^a
+
+template <int N, int LPW>
+__global__ __launch_bounds__(LPW * tri_tl(N)) void k_tri_col(LineArgs a) {
+  __shared__ double2 lds[tri_lds<N, LPW>::elems];
+  const int tile = xcd_tile<(16 / LPW > 1 ? 16 / LPW : 1)>(blockIdx.x, gridDim.x);
+  tri_col_body<N, LPW>(a, tile * LPW, blockIdx.x, gridDim.x, lds);
+}
+template <int N, int LPW, bool INV>
+__global__ __launch_bounds__(LPW * tri_tl(N)) void k_tri_mid(LineArgs a) {
+  __shared__ double2 lds[tri_lds<N, LPW>::elems];
+  const int tile = xcd_tile<(16 / LPW > 1 ? 16 / LPW : 1)>(blockIdx.x, gridDim.x);
+  tri_mid_body<N, LPW, INV>(a, tile * LPW, lds);
+}
+template <int N, int LPW, bool PW>
+__global__ __launch_bounds__(LPW * tri_tl(N)) void k_tri_row(LineArgs a) {
+  __shared__ double2 lds[tri_lds<N, LPW>::elems];
+  tri_row_body<N, LPW, PW>(a, blockIdx.x * LPW, lds);
+}
+
 // ---------------------------------------------------------------- dispatch
 
 bool line_length_supported(int N) {
@@ -49,10 +69,10 @@ bool line_length_supported(int N) {
 
 // With events e0/e1 the launch records them at the kernel's own start and
 // end (hipExtLaunchKernelGGL), which times the kernel without launch gaps.
-#define TDSE_LAUNCH(K, G, B, S, E0, E1, A)                        \
-  do {                                                            \
-    if (E0) hipExtLaunchKernelGGL(K, G, B, 0, S, E0, E1, 0, A);   \
-    else hipLaunchKernelGGL(K, G, B, 0, S, A);                    \
+#define TDSE_LAUNCH(K, G, B, S, E0, E1, A) \
+  do { \
+    if (E0) hipExtLaunchKernelGGL(K, G, B, 0, S, E0, E1, 0, A); \
+    else hipLaunchKernelGGL(K, G, B, 0, S, A); \
   } while (0)
 
 // The pointwise pass of a 1D problem (length 1) fills one workgroup with its
@@ -67,14 +87,23 @@ inline int64_t col_blocks(int N, const LineArgs& a, int L, int T) {
   return nb;
 }
 
+// Lengths 3 * 2^a of FP64 plans take the passes in two layouts.  A split plan
+// (ph32) keeps the one-layout passes in its FP64 start-up: another order of the
+// same sums would change the last bits of what is then narrowed, and with them
+// the rounding of the whole complex64 run.
 template <typename C>
 hipError_t col_pass(int N, const LineArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   switch (N) {
-#define X(n)                                                                                      \
-  case n: {                                                                                       \
-    constexpr int L = (sizeof(C) == sizeof(float2) && n == 128) ? 16 : col_lpw(n), T = col_tl(n);                                                \
-    TDSE_LAUNCH((k_col<C, n, L, T>), dim3((unsigned)col_blocks(n, a, L, T)), dim3(L * T), s, e0, e1, a); \
-    break;                                                                                        \
+#define X(n) \
+  case n: { \
+    if (sizeof(C) == sizeof(double2) && three_smooth(n) && !a.ph32) { \
+      constexpr int NN = three_smooth(n) ? n : 24, L = tri_col_lpw(NN); \
+      TDSE_LAUNCH((k_tri_col<NN, L>), dim3((unsigned)((a.nlines + L - 1) / L)), dim3(L * tri_tl(NN)), s, e0, e1, a); \
+    } else { \
+      constexpr int L = (sizeof(C) == sizeof(float2) && n == 128) ? 16 : col_lpw(n), T = col_tl(n); \
+      TDSE_LAUNCH((k_col<C, n, L, T>), dim3((unsigned)col_blocks(n, a, L, T)), dim3(L * T), s, e0, e1, a); \
+    } \
+    break; \
   }
     X(1)
     TDSE_LINE_SIZES(X)
@@ -90,13 +119,20 @@ template <typename C>
 hipError_t mid_pass(int N, bool inverse, const LineArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   if (a.slab_lines < 1) return hipErrorInvalidValue;
   switch (N) {
-#define X(n)                                                                                          \
-  case n: {                                                                                           \
-    constexpr int L = (sizeof(C) == sizeof(float2) && n == 128) ? 16 : col_lpw(n), T = col_tl(n);                                                    \
-    const dim3 g((unsigned)((a.nlines + L - 1) / L));                                                 \
-    if (inverse) TDSE_LAUNCH((k_mid<C, n, L, T, true>), g, dim3(L * T), s, e0, e1, a);               \
-    else TDSE_LAUNCH((k_mid<C, n, L, T, false>), g, dim3(L * T), s, e0, e1, a);                      \
-    break;                                                                                            \
+#define X(n) \
+  case n: { \
+    if (sizeof(C) == sizeof(double2) && three_smooth(n) && !a.ph32) { \
+      constexpr int NN = three_smooth(n) ? n : 24, L = tri_col_lpw(NN); \
+      const dim3 g((unsigned)((a.nlines + L - 1) / L)); \
+      if (inverse) TDSE_LAUNCH((k_tri_mid<NN, L, true>), g, dim3(L * tri_tl(NN)), s, e0, e1, a); \
+      else TDSE_LAUNCH((k_tri_mid<NN, L, false>), g, dim3(L * tri_tl(NN)), s, e0, e1, a); \
+    } else { \
+      constexpr int L = (sizeof(C) == sizeof(float2) && n == 128) ? 16 : col_lpw(n), T = col_tl(n); \
+      const dim3 g((unsigned)((a.nlines + L - 1) / L)); \
+      if (inverse) TDSE_LAUNCH((k_mid<C, n, L, T, true>), g, dim3(L * T), s, e0, e1, a); \
+      else TDSE_LAUNCH((k_mid<C, n, L, T, false>), g, dim3(L * T), s, e0, e1, a); \
+    } \
+    break; \
   }
     TDSE_LINE_SIZES(X)
 #undef X
@@ -109,15 +145,20 @@ hipError_t mid_pass(int N, bool inverse, const LineArgs& a, hipStream_t s, hipEv
 template <typename C>
 hipError_t row_pass(int N, const LineArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   switch (N) {
-#define X(n)                                                                                      \
-  case n: {                                                                                       \
-    constexpr int L = row_lpw(n), T = row_tl(n);                                                  \
-    if (a.pf_pow) {                                                                               \
-      TDSE_LAUNCH((k_row<C, n, L, T, true>), dim3((a.nlines + L - 1) / L), dim3(L * T), s, e0, e1, a); \
-      break;                                                                                      \
-    }                                                                                             \
-    TDSE_LAUNCH((k_row<C, n, L, T>), dim3((a.nlines + L - 1) / L), dim3(L * T), s, e0, e1, a);   \
-    break;                                                                                        \
+#define X(n) \
+  case n: { \
+    if (sizeof(C) == sizeof(double2) && three_smooth(n) && !a.ph32) { \
+      constexpr int NN = three_smooth(n) ? n : 24, L = tri_row_lpw(NN); \
+      const dim3 g((a.nlines + L - 1) / L), b(L * tri_tl(NN)); \
+      if (a.pf_pow) TDSE_LAUNCH((k_tri_row<NN, L, true>), g, b, s, e0, e1, a); \
+      else TDSE_LAUNCH((k_tri_row<NN, L, false>), g, b, s, e0, e1, a); \
+    } else { \
+      constexpr int L = row_lpw(n), T = row_tl(n); \
+      const dim3 g((a.nlines + L - 1) / L); \
+      if (a.pf_pow) TDSE_LAUNCH((k_row<C, n, L, T, true>), g, dim3(L * T), s, e0, e1, a); \
+      else TDSE_LAUNCH((k_row<C, n, L, T>), g, dim3(L * T), s, e0, e1, a); \
+    } \
+    break; \
   }
     TDSE_LINE_SIZES(X)
 #undef X

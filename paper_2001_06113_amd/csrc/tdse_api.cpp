@@ -616,6 +616,7 @@ int launch_mid(const tdse_plan_s* p, int g, void* buf, bool inverse, hipEvent_t 
   m.slab_lines = p->M2;
   m.slab_stride = (int64_t)p->Mmid * p->M2;
   m.tw = p->tw(g, 2);
+  m.ph32 = p->ph32();   // a split plan's passes (see the dispatch)
   const hipError_t e = launch_mid_pass(p->st[g].prec, p->Mmid, inverse, m, p->stream, e0, e1);
   if (e != hipSuccess) return fail(TDSE_EDEVICE, std::string("kernel launch: ") + hipGetErrorString(e));
   return TDSE_OK;
