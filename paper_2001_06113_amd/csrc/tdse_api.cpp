@@ -1636,7 +1636,7 @@ int plan_free(tdse_plan_s* p, const tdse_problem_t* prob) {
 // exp(-i k^2 tau) of the Adams intervals tau = j dt and of the sub-steps
 // tau = dt / 2^l, from extended precision.
 void build_run1d(tdse_plan_s* p) {
-  const int N = p->nsteps, ns = p->ns, L = p->L, M = p->M2, nh = p->order - 1;
+  const int N = p->nsteps, ns = p->ns, L = p->L, M = p->M2;
   std::vector<double>& T = p->r1tab;
   T.clear();
   double f[MAXV];
@@ -1673,10 +1673,9 @@ void build_run1d(tdse_plan_s* p) {
     p->tf.phi(p->t_at(i - 1), pa);
     T.push_back(pb[0] - pa[0]);
   }
-  p->r1stab.assign((size_t)(nh + L) * M, double2{0.0, 0.0});
-  for (int r = 0; r < nh + L; ++r) {
-    const long double tau = r < nh ? (long double)(r + 1) * (long double)p->dt
-                                   : (long double)p->dt / (long double)(1 << (r - nh));
+  p->r1stab.assign((size_t)(1 + L) * M, double2{0.0, 0.0});
+  for (int r = 0; r <= L; ++r) {
+    const long double tau = (long double)p->dt / (long double)(r > 0 ? 1 << (r - 1) : 1);
     for (int idx = 0; idx < M; ++idx) {
       const long double k = (long double)(idx < M / 2 ? idx : idx - M);
       const long double th = -k * k * tau;
@@ -1709,7 +1708,6 @@ int run1d_step(tdse_plan_s* p, int end) {
   a.vkind = p->vkind;
   a.write_u = 1;
   a.has_phase = p->tf.A_kind != TDSE_A_NONE;
-  a.stab_rows = p->order - 1 + p->L;
   a.dt = p->dt;
   a.c0 = p->mu[0] * p->dt;
   for (int j = 1; j < p->order; ++j) a.ch[j] = p->dt * p->mu[j];

@@ -340,12 +340,12 @@ hipError_t launch_far_gemm(int M, int N, int K, const double2* A, int64_t sam, i
 //   oA + 8 (m - ns - 1)           f_r(t_m), Adams step m
 //   oD + i - 1                    phi(t_i) - phi(t_{i-1}), i = 1..nsteps
 // (f_r: the eight potential time factors, or the moving well's parameters).
-// stab holds exp(-i k^2 j dt), j = 1..n-1, then exp(-i k^2 dt / 2^l), l < L.
+// stab holds exp(-i k^2 dt), then exp(-i k^2 dt / 2^l), l < L.
 struct Run1DArgs {
   int M, order, ns, nsteps, L;
   int m0, m1;
   int nV, vkind;
-  int write_u, has_phase, stab_rows;
+  int write_u, has_phase;
   double dt, c0;
   double ch[MAXH + 1];
   double rich[4];
@@ -361,7 +361,6 @@ struct Run1DArgs {
   const double2* tw;
 };
 bool run1d_supported(int N);
-size_t run1d_lds_bytes(int N, int stab_rows, int nV);
 hipError_t launch_run1d(const Run1DArgs& a, hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 
 // Persistent implicit Adams steps of a square 2D periodic FP64 problem
