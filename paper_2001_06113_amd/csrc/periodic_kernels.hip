@@ -54,6 +54,34 @@ __global__ __launch_bounds__(LPW * tri_tl(N)) void k_tri_row(LineArgs a) {
   tri_row_body<N, LPW, PW>(a, blockIdx.x * LPW, lds);
 }
 
+// One pass of several Richardson levels of a start-up step, level blockIdx.y's
+// arguments in la.a[blockIdx.y] (FP64; the same bodies and schedules).
+template <int N, int LPW, int TL>
+__global__ __launch_bounds__(LPW * TL, (N >= 256 && N <= 1024 && (N & (N - 1)) == 0) ? 4 : 1) void k_col_lv(LevelArgs la) {
+  __shared__ double2 lds[col_lds<double2, N, LPW>::elems];
+  const int tile = xcd_tile<(16 / LPW > 1 ? 16 / LPW : 1)>(blockIdx.x, gridDim.x);
+  col_body<double2, N, LPW, TL>(la.a[blockIdx.y], tile * LPW, blockIdx.x, gridDim.x, lds);
+}
+
+template <int N, int LPW, int TL>
+__global__ __launch_bounds__(LPW * TL) void k_row_lv(LevelArgs la) {
+  __shared__ double2 lds[row_lds<double2, N, LPW>::elems];
+  row_body<double2, N, LPW, TL, false>(la.a[blockIdx.y], blockIdx.x * LPW, lds);
+}
+
+template <int N, int LPW>
+__global__ __launch_bounds__(LPW * tri_tl(N)) void k_tri_col_lv(LevelArgs la) {
+  __shared__ double2 lds[tri_lds<N, LPW>::elems];
+  const int tile = xcd_tile<(16 / LPW > 1 ? 16 / LPW : 1)>(blockIdx.x, gridDim.x);
+  tri_col_body<N, LPW>(la.a[blockIdx.y], tile * LPW, blockIdx.x, gridDim.x, lds);
+}
+
+template <int N, int LPW>
+__global__ __launch_bounds__(LPW * tri_tl(N)) void k_tri_row_lv(LevelArgs la) {
+  __shared__ double2 lds[tri_lds<N, LPW>::elems];
+  tri_row_body<N, LPW, false>(la.a[blockIdx.y], blockIdx.x * LPW, lds);
+}
+
 // ---------------------------------------------------------------- dispatch
 
 bool line_length_supported(int N) {
@@ -182,6 +210,49 @@ hipError_t launch_narrow(const double2* src, float2* dst, int64_t n, hipStream_t
 
 hipError_t launch_col_pass(int prec, int N, const LineArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   return prec == P_SPLIT ? col_pass<float2>(N, a, s, e0, e1) : col_pass<double2>(N, a, s, e0, e1);
+}
+// `count` levels of one pass (2D FP64 plans; every level has the geometry of the first)
+hipError_t launch_col_levels(int N, const LevelArgs& la, int count, hipStream_t s) {
+  const LineArgs& a = la.a[0];
+  switch (N) {
+#define X(n) \
+  case n: { \
+    if constexpr (three_smooth(n)) { \
+      constexpr int NN = three_smooth(n) ? n : 24, L = tri_col_lpw(NN); \
+      hipLaunchKernelGGL((k_tri_col_lv<NN, L>), dim3((unsigned)((a.nlines + L - 1) / L), count), dim3(L * tri_tl(NN)), 0, s, la); \
+    } else { \
+      constexpr int NN = three_smooth(n) ? 8 : n, L = col_lpw(NN), T = col_tl(NN); \
+      hipLaunchKernelGGL((k_col_lv<NN, L, T>), dim3((unsigned)((a.nlines + L - 1) / L), count), dim3(L * T), 0, s, la); \
+    } \
+    break; \
+  }
+    TDSE_LINE_SIZES(X)
+#undef X
+    default:
+      return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+hipError_t launch_row_levels(int N, const LevelArgs& la, int count, hipStream_t s) {
+  const LineArgs& a = la.a[0];
+  switch (N) {
+#define X(n) \
+  case n: { \
+    if constexpr (three_smooth(n)) { \
+      constexpr int NN = three_smooth(n) ? n : 24, L = tri_row_lpw(NN); \
+      hipLaunchKernelGGL((k_tri_row_lv<NN, L>), dim3((unsigned)((a.nlines + L - 1) / L), count), dim3(L * tri_tl(NN)), 0, s, la); \
+    } else { \
+      constexpr int NN = three_smooth(n) ? 8 : n, L = row_lpw(NN), T = row_tl(NN); \
+      hipLaunchKernelGGL((k_row_lv<NN, L, T>), dim3((unsigned)((a.nlines + L - 1) / L), count), dim3(L * T), 0, s, la); \
+    } \
+    break; \
+  }
+    TDSE_LINE_SIZES(X)
+#undef X
+    default:
+      return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
 }
 hipError_t launch_mid_pass(int prec, int N, bool inverse, const LineArgs& a, hipStream_t s, hipEvent_t e0,
                            hipEvent_t e1) {

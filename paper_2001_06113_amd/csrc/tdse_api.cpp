@@ -375,6 +375,11 @@ struct tdse_plan_s {
   size_t lds_max = 65536;                       // device limit of LDS per workgroup
   bool is_batch() const { return !sub.empty(); }
 
+  // Richardson levels of a start-up step side by side (small 2D FP64 plans):
+  // tile, B and phase table of levels 1.. at o_lv, lv_bytes per level
+  bool levels = false;
+  size_t o_lv = 0, lv_bytes = 0;
+
   // one-workgroup run of a 1D periodic FP64 plan (run1d_kernels.hip): the
   // per-step scalar table and the static phase factors, at the end of the
   // workspace (total_core: the workspace without them)
@@ -703,8 +708,108 @@ int op_history(tdse_plan_s* p, int m) {
   return launch(p, g, false, r);
 }
 
+// 2D FP64 plans of up to this many points march the Richardson levels of a
+// start-up step side by side.  Start-up of order 8 (six steps), in turn / side by
+// side: 64 x 96 1284 / 721 us, 256^2 1266 / 735, 512^2 1917 / 1470, 768^2 3377 /
+// 2543, 1024^2 4849 / 4169.  A small grid's pass leaves compute units idle and
+// is launch and latency; from 1024^2 on the passes' bytes are the time, and the
+// levels' own tiles (96 B per point) would be the price of a shrinking gain.
+// Split plans keep the levels in turn: their FP64 start-up is narrowed to
+// complex64, and a last bit of it would move the whole run's rounding.
+constexpr int64_t LEVELS_MAX_POINTS = 1 << 20;
+
+// The start-up step with its levels side by side: each pass is one launch over
+// the levels that still have a sub-step, so a step takes the passes of the
+// longest level alone (17 launches instead of 34 with four levels).  A level has a tile, a
+// B and a phase table of its own; the levels end in different launches, in
+// order, so the Richardson sum keeps its order and every bit.
+int op_richardson_levels(tdse_plan_s* p, int m) {
+  const int g = 0, L = p->L;
+  const double t = p->t_at(m - 1);
+  const int src = p->ucur, acc = 1 - p->ucur;
+  auto own = [&](LineArgs& a, int l) -> void* {   // level l's buffers; returns its tile
+    if (l == 0) return p->tmp(g);
+    char* b = p->ws + p->o_lv + (size_t)(l - 1) * p->lv_bytes;
+    const size_t c = align256((size_t)p->P * sizeof(double2));
+    a.Bm = a.Bw = (double2*)(b + c);
+    a.ph = (double2*)(b + 2 * c);
+    return b;
+  };
+  LevelArgs la;
+  auto go = [&](bool col, int count) -> int {
+    const hipError_t e = col ? launch_col_levels(p->col_len(), la, count, p->stream)
+                             : launch_row_levels(p->M2, la, count, p->stream);
+    return e == hipSuccess ? TDSE_OK : fail(TDSE_EDEVICE, std::string("kernel launch: ") + hipGetErrorString(e));
+  };
+  for (int l = 0; l < L; ++l) {
+    const double delta = p->dt / (1 << l);
+    LineArgs& a = la.a[l] = base_args(p, g);
+    col_geom(p, g, a);
+    a.mode = C_FWD;
+    a.dst = own(a, l);
+    a.src = p->u(src);
+    set_V(p, g, a, t);
+    a.alpha_re = 1.0; a.alpha_im = 0.0; a.beta_re = 0.0; a.beta_im = -0.5 * delta;
+    phase_req(p, a, 1, t + delta, delta, false, 0);
+  }
+  int s = go(true, L);
+  if (s) return s;
+  for (int l = 0; l < L; ++l) {
+    LineArgs& r = la.a[l] = base_args(p, g);
+    row_geom(p, g, r);
+    r.mode = R_INIT;
+    r.dst = own(r, l);
+    r.src = r.dst;
+  }
+  s = go(false, L);
+  if (s) return s;
+  for (int k = 0; k < 1 << (L - 1); ++k) {
+    int n = 0;
+    for (int l = 0; l < L; ++l) {
+      if (k >= 1 << l) continue;
+      const double delta = p->dt / (1 << l), ts1 = (t + k * delta) + delta;
+      LineArgs& c = la.a[n++] = base_args(p, g);
+      col_geom(p, g, c);
+      c.mode = C_SOLVE;
+      c.dst = own(c, l);
+      c.src = c.dst;
+      set_V(p, g, c, ts1);
+      c.csolve = 0.5 * delta;
+      if (k == (1 << l) - 1) {
+        c.uacc = p->u(acc);
+        c.wacc = p->rich[l];
+        c.acc_first = (l == 0);
+      } else {
+        phase_req(p, c, 1, ts1 + delta, delta, false, 0);
+      }
+    }
+    s = go(true, n);
+    if (s) return s;
+    n = 0;
+    for (int l = 0; l < L; ++l) {
+      if (k + 1 >= 1 << l) continue;
+      const double delta = p->dt / (1 << l);
+      LineArgs& r = la.a[n++] = base_args(p, g);
+      row_geom(p, g, r);
+      r.mode = R_AM;
+      r.dst = own(r, l);
+      r.src = r.dst;
+      r.nh = 1;
+      r.c0 = 0.5 * delta;
+      r.ch[1] = 0.5 * delta;
+      r.slot_w = -1;
+    }
+    if (n == 0) break;
+    s = go(false, n);
+    if (s) return s;
+  }
+  p->ucur = acc;
+  return TDSE_OK;
+}
+
 // One iterated-Richardson start-up step from t_{m-1} to t_m (FP64).
 int op_richardson(tdse_plan_s* p, int m) {
+  if (p->levels && !p->rec) return op_richardson_levels(p, m);
   const int g = 0;
   const double t = p->t_at(m - 1);
   const int src = p->ucur, acc = 1 - p->ucur;
@@ -2223,9 +2328,10 @@ int plan_batch(const tdse_problem_t* probs, int count, tdse_plan_s** out) {
     tdse_plan_s* q = nullptr;
     const int s = tdse_plan(&probs[i], &q);
     if (s) return s;
-    if (q->run1d || q->persist) {   // batches march every instance with the batched passes
+    if (q->run1d || q->persist || q->levels) {   // batches march every instance with the batched passes
       q->run1d = false;
       q->persist = false;
+      q->levels = false;
       q->total = q->total_core;
     }
     p->sub.push_back(q);
@@ -3167,6 +3273,12 @@ int tdse_plan(const tdse_problem_t* prob, tdse_plan_t* out) {
     off = align256(off + cbytes);
   }
   p->total_core = off;
+  if (p->dim == 2 && !split && p->ns > 0 && p->L > 1 && p->L <= MAXLEVELS && p->P <= LEVELS_MAX_POINTS) {
+    p->levels = true;
+    p->lv_bytes = 2 * align256((size_t)p->P * sizeof(double2)) +
+                  align256((size_t)(p->order - 1) * (p->M1 + p->M2) * sizeof(double2));
+    p->o_lv = off; off = align256(off + (size_t)(p->L - 1) * p->lv_bytes);
+  }
   if (p->dim == 2 && !split && p->M1 == p->M2 && persist2d_supported(p->M2) && p->vkind == TDSE_V_FIELDS &&
       p->nsteps > p->ns + 1) {
     p->persist = true;

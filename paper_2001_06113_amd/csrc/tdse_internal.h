@@ -92,6 +92,14 @@ struct LineArgs {
   PhaseReq req;
 };
 
+// The same pass of up to four Richardson levels in one launch (a kernel's
+// arguments may take 4 KB)
+constexpr int MAXLEVELS = 4;
+struct LevelArgs {
+  LineArgs a[MAXLEVELS];
+};
+static_assert(sizeof(LevelArgs) <= 4000, "kernel arguments");
+
 // One axis of the free-space complex-frequency transform (freespace_kernels.hip):
 // modes ordered E1 | A1 C A3 | E3 with N = 2 NE + ND.  All tables complex128,
 // device pointers into the plan's workspace.
@@ -408,6 +416,8 @@ hipError_t launch_diffnorm(const float2* a32, const double2* a64, const double2*
 // the kernel's own start and end.  Return a hipError_t.
 hipError_t launch_col_pass(int prec, int N, const LineArgs& a, hipStream_t s, hipEvent_t e0 = nullptr,
                            hipEvent_t e1 = nullptr);
+hipError_t launch_col_levels(int N, const LevelArgs& la, int count, hipStream_t s);
+hipError_t launch_row_levels(int N, const LevelArgs& la, int count, hipStream_t s);
 hipError_t launch_mid_pass(int prec, int N, bool inverse, const LineArgs& a, hipStream_t s, hipEvent_t e0 = nullptr,
                            hipEvent_t e1 = nullptr);   // 3D middle axis, in place (a.src == a.dst)
 hipError_t launch_row_pass(int prec, int N, const LineArgs& a, hipStream_t s, hipEvent_t e0 = nullptr,

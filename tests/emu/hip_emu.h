@@ -125,10 +125,11 @@ template <typename K, typename... Args>
 void launch(K kernel, dim3 grid, dim3 block, Args... args) {
   gridDim = grid;
   blockDim = block;
-  for (unsigned bi = 0; bi < grid.x; ++bi) {
+  for (unsigned bi = 0; bi < grid.x * grid.y; ++bi) {
     Block b;
     g_block = &b;
-    blockIdx.x = bi;
+    blockIdx.x = bi % grid.x;
+    blockIdx.y = bi / grid.x;
     b.body = [&]() { kernel(args...); };
     b.fibers.resize(block.x);
 #if defined(__SANITIZE_THREAD__)
