@@ -1120,6 +1120,7 @@ __global__ __launch_bounds__(256) void k_fs_phase(FSArgs a) { build_phase_table_
   do {                                                                                                   \
     switch (fs_points(n, AX.M, 8)) {                                                                     \
       case 1: TDSE_FS_CH(K, n, 1, AX, G, B, S, E0, E1, A, ##__VA_ARGS__); break;                         \
+      case 2: TDSE_FS_CH(K, n, 2, AX, G, B, S, E0, E1, A, ##__VA_ARGS__); break;                         \
       case 4: TDSE_FS_CH(K, n, 4, AX, G, B, S, E0, E1, A, ##__VA_ARGS__); break;                         \
       default: TDSE_FS_CH(K, n, 8, AX, G, B, S, E0, E1, A, ##__VA_ARGS__);                               \
     }                                                                                                    \

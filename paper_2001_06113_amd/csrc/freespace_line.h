@@ -12,10 +12,12 @@ __device__ __forceinline__ double2 fs_mul_mi(double c, double2 z) { return doubl
 
 // Grid points a thread can hold, of its EPT FFT slots: one when M <= nu/EPT
 // (the short ends of fft_lds.h: the first pass going in and most of the last
-// pass coming out drop out), half when M <= nu/2 (the other slots are
-// compile-time zeros going in and unused coming out), else all.
+// pass coming out drop out), two when M <= 2 nu/EPT, half when M <= nu/2 (the
+// other slots are compile-time zeros going in and unused coming out), else all.
+// Two of eight: a 3D row pass of 38 points at nu = 256 took 563 us with half the
+// slots, whose dense sums mostly worked on empty ones, and takes 512 us.
 __host__ __device__ constexpr int fs_points(int nu, int M, int ept) {
-  return M <= nu / ept ? 1 : M <= nu / 2 ? ept / 2 : ept;
+  return M <= nu / ept ? 1 : M <= 2 * nu / ept ? 2 : M <= nu / 2 ? ept / 2 : ept;
 }
 
 // sum_{j0 <= j < j1} r^(j - j0) f[j] (f in LDS): four interleaved Horner sums

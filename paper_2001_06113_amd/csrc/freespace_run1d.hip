@@ -329,7 +329,7 @@ hipError_t launch_fs_run1d(int nu, const FSRun1DArgs& a0, hipStream_t s) {
 #define X(n)                                 \
   case n:                                    \
     switch (fs_points(n, a.ax.M, 8)) {       \
-      Y(n, 1) Y(n, 4) Y(n, 8)                \
+      Y(n, 1) Y(n, 2) Y(n, 4) Y(n, 8)        \
     }                                        \
     break;
   switch (nu) {
