@@ -233,7 +233,7 @@ int tdse_far_eval_noalloc(tdse_plan_t plan, const double* xs, int32_t nx, const 
 #define TDSE_Q_PROF_MS_FAR   14   /* profiling: summed ms of tdse_far_eval's first product */
 #define TDSE_Q_PROF_N_FAR    15   /* profiling: number of timed tdse_far_eval calls        */
 #define TDSE_Q_MU             16  /* + j: Adams weight mu_j                    */
-#define TDSE_Q_PROF_MS_RUN1D  24  /* profiling: summed ms of one-workgroup 1D runs (1D periodic FP64 plans, M <= 512) */
+#define TDSE_Q_PROF_MS_RUN1D  24  /* profiling: summed ms of one-workgroup 1D runs (1D periodic FP64 plans) */
 #define TDSE_Q_PROF_N_RUN1D   25  /* profiling: number of timed one-workgroup 1D runs */
 #define TDSE_Q_PROF_MS_PERSIST 26 /* profiling: summed ms of persistent 2D launches */
 #define TDSE_Q_PROF_N_PERSIST 27  /* profiling: number of timed persistent 2D launches */
