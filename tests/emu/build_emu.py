@@ -20,6 +20,22 @@ SOURCES = [os.path.join(CSRC, "periodic_kernels.hip"), os.path.join(CSRC, "frees
 
 TSAN_DRIVER = os.path.join(HERE, "tsan_batch_adjoint.cpp")
 TSAN_OUT = os.path.join(HERE, "tsan_batch_adjoint")
+TSAN_LIB = TSAN_OUT + ".so"
+# the executable: the driver's main, from the shared object beside it
+TSAN_MAIN = r"""
+#include <dlfcn.h>
+#include <cstdio>
+#include <string>
+int main(int argc, char** argv) {
+  void* lib = dlopen((std::string(argv[0]) + ".so").c_str(), RTLD_NOW);
+  auto run = lib ? (int (*)(int, char**))dlsym(lib, "_Z11driver_mainiPPc") : nullptr;
+  if (!run) {
+    std::fprintf(stderr, "%s\n", dlerror());
+    return 3;
+  }
+  return run(argc, argv);
+}
+"""
 
 
 def build(sanitize: bool = False) -> str:
@@ -35,15 +51,20 @@ def build(sanitize: bool = False) -> str:
 
 
 def build_tsan_driver() -> str:
-    """The library's host code and kernels with the batch-adjoint driver in one
-    ThreadSanitizer executable (host CPU build; no GPU code is involved)."""
-    flags = ["-O1", "-g", "-std=c++17", "-pthread", "-fsanitize=thread", "-fno-omit-frame-pointer",
-             "-include", os.path.join(HERE, "hip_emu.h"), f"-I{os.path.join(HERE, 'stub')}", f"-I{CSRC}",
-             f"-I{os.path.join(ROOT, 'include')}", "-x", "c++"]
-    cmd = ["g++", *flags, *SOURCES, TSAN_DRIVER, "-o", TSAN_OUT]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError(" ".join(cmd) + "\n" + r.stderr[-4000:])
+    """The library's host code and kernels with the batch-adjoint driver under
+    ThreadSanitizer (host CPU build; no GPU code is involved).  The emulated
+    __shared__ arrays are thread-local, and in an executable every thread's
+    stack, the main thread's 8 MB among them, would have to hold them all.  In
+    a shared object that the executable opens when it runs, they are dynamic
+    thread-local storage, which lives on the heap."""
+    tsan = ["-O1", "-g", "-std=c++17", "-pthread", "-fsanitize=thread", "-fno-omit-frame-pointer"]
+    flags = [*tsan, "-fPIC", "-shared", "-include", os.path.join(HERE, "hip_emu.h"), f"-I{os.path.join(HERE, 'stub')}",
+             f"-I{CSRC}", f"-I{os.path.join(ROOT, 'include')}", "-Dmain=driver_main", "-x", "c++"]
+    for cmd, text in ((["g++", *flags, *SOURCES, TSAN_DRIVER, "-o", TSAN_LIB], None),
+                      (["g++", *tsan, "-x", "c++", "-", "-o", TSAN_OUT, "-ldl"], TSAN_MAIN)):
+        r = subprocess.run(cmd, input=text, capture_output=True, text=True)
+        if r.returncode != 0:
+            raise RuntimeError(" ".join(cmd) + "\n" + r.stderr[-4000:])
     return TSAN_OUT
 
 
