@@ -422,6 +422,7 @@ struct tdse_plan_s {
   hipGraph_t graph = nullptr;
   hipGraphExec_t gexec = nullptr;
   int graph_ucur = 0;
+  int graph_steps = 0;   // steps it holds
 
   void drop_graph() {
     if (gexec) (void)hipGraphExecDestroy(gexec);
@@ -3597,6 +3598,8 @@ int tdse_run(tdse_plan_t p, const void* u0, void* uT, int32_t on_device) {
   // with persistent Adams steps the graph holds the start-up and the Adams
   // start; the persistent launch (one per run) follows it outside the graph
   const int pre = (p->persist && p->persist_on) ? p->ns + 1 : p->nsteps;
+  // (a persistent launch that did not fit the device has made it the whole run)
+  if (p->gexec && p->graph_steps != pre) p->drop_graph();
   if (!p->gexec) {
     // capture the whole step sequence once; kernel arguments depend only on
     // the plan and the bound workspace
@@ -3620,6 +3623,7 @@ int tdse_run(tdse_plan_t p, const void* u0, void* uT, int32_t on_device) {
       return fail(TDSE_EDEVICE, std::string("hipGraphInstantiate: ") + hipGetErrorString(e));
     }
     p->graph_ucur = p->ucur;
+    p->graph_steps = pre;
   }
   HIP_TRY(hipGraphLaunch(p->gexec, p->stream));
   p->cur = pre;

@@ -5,3 +5,5 @@ thread_local uint3_ blockIdx;
 thread_local dim3 blockDim, gridDim;
 thread_local emu::Block* emu::g_block = nullptr;
 thread_local emu::CoopRun* emu::g_coop = nullptr;
+thread_local emu_graph* emu_capture = nullptr;
+int emu_coop_blocks = 1;

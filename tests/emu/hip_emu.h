@@ -62,7 +62,8 @@ enum {
   hipErrorInvalidValue = 1,
   hipErrorInvalidDevice = 101,
   hipErrorInvalidSymbol = 701,
-  hipErrorCooperativeLaunchTooLarge = 720
+  hipErrorCooperativeLaunchTooLarge = 720,
+  hipErrorStreamCaptureUnsupported = 900
 };
 #define __align__(n) __attribute__((aligned(n)))
 // a __device__ variable is a host variable here: its address is the symbol's
@@ -72,6 +73,15 @@ inline hipError_t hipGetSymbolAddress(void** p, const void* sym) {
   return hipSuccess;
 }
 enum hipMemcpyKind { hipMemcpyHostToDevice, hipMemcpyDeviceToHost, hipMemcpyDeviceToDevice, hipMemcpyHostToHost };
+
+// Stream capture: while a host thread captures, its launches and copies are
+// kept as a list, which a graph launch runs.
+struct emu_graph {
+  std::vector<std::function<void()>> ops;
+};
+extern thread_local emu_graph* emu_capture;
+// co-resident workgroups per multiprocessor of a cooperative launch (a test may lower it)
+extern "C" int emu_coop_blocks;
 
 namespace emu {
 // Cooperative fibers: every emulated thread of a block runs on one OS thread
@@ -123,6 +133,10 @@ inline void fiber_entry() {
 }
 template <typename K, typename... Args>
 void launch(K kernel, dim3 grid, dim3 block, Args... args) {
+  if (emu_capture) {
+    emu_capture->ops.push_back([=]() { launch(kernel, grid, block, args...); });
+    return;
+  }
   gridDim = grid;
   blockDim = block;
   for (unsigned bi = 0; bi < grid.x * grid.y; ++bi) {
@@ -365,26 +379,47 @@ using std::max;
 inline hipError_t hipGetLastError() { return hipSuccess; }
 inline const char* hipGetErrorString(hipError_t) { return "emulated"; }
 inline hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) {
-  std::memcpy(d, s, n);
+  if (emu_capture) emu_capture->ops.push_back([=]() { std::memcpy(d, s, n); });
+  else std::memcpy(d, s, n);
   return hipSuccess;
 }
 inline hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) {
-  std::memset(d, v, n);
+  if (emu_capture) emu_capture->ops.push_back([=]() { std::memset(d, v, n); });
+  else std::memset(d, v, n);
   return hipSuccess;
 }
-inline hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+inline hipError_t hipStreamSynchronize(hipStream_t) {
+  return emu_capture ? hipErrorStreamCaptureUnsupported : hipSuccess;
+}
 typedef struct emu_event* hipEvent_t;
-typedef struct emu_graph* hipGraph_t;
-typedef struct emu_graph_exec* hipGraphExec_t;
+typedef emu_graph* hipGraph_t;
+typedef emu_graph* hipGraphExec_t;
 enum hipStreamCaptureMode { hipStreamCaptureModeGlobal, hipStreamCaptureModeThreadLocal, hipStreamCaptureModeRelaxed };
-inline hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipErrorInvalidValue; }
-inline hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t* g) { *g = nullptr; return hipErrorInvalidValue; }
+inline hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) {
+  if (emu_capture) return hipErrorStreamCaptureUnsupported;
+  emu_capture = new emu_graph;
+  return hipSuccess;
+}
+inline hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t* g) {
+  *g = emu_capture;
+  emu_capture = nullptr;
+  return *g ? hipSuccess : hipErrorInvalidValue;
+}
 enum hipStreamCaptureStatus { hipStreamCaptureStatusNone, hipStreamCaptureStatusActive, hipStreamCaptureStatusInvalidated };
-inline hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* st) { *st = hipStreamCaptureStatusNone; return hipSuccess; }
-inline hipError_t hipGraphInstantiate(hipGraphExec_t*, hipGraph_t, void*, void*, size_t) { return hipErrorInvalidValue; }
-inline hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipErrorInvalidValue; }
-inline hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
-inline hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
+inline hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* st) {
+  *st = emu_capture ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
+inline hipError_t hipGraphInstantiate(hipGraphExec_t* e, hipGraph_t g, void*, void*, size_t) {
+  *e = new emu_graph(*g);
+  return hipSuccess;
+}
+inline hipError_t hipGraphLaunch(hipGraphExec_t e, hipStream_t) {
+  for (const auto& op : e->ops) op();
+  return hipSuccess;
+}
+inline hipError_t hipGraphDestroy(hipGraph_t g) { delete g; return hipSuccess; }
+inline hipError_t hipGraphExecDestroy(hipGraphExec_t e) { delete e; return hipSuccess; }
 inline hipError_t hipEventCreate(hipEvent_t* e) { *e = (hipEvent_t)new char[1]; return hipSuccess; }
 inline hipError_t hipEventDestroy(hipEvent_t e) { delete[] (char*)e; return hipSuccess; }
 inline hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
@@ -399,11 +434,12 @@ enum hipDeviceAttribute_t { hipDeviceAttributeMaxSharedMemoryPerBlock, hipDevice
 inline hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 template <typename K>
 inline hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, K, int, size_t) {
-  *n = 1;
+  *n = emu_coop_blocks;
   return hipSuccess;
 }
 template <typename A>
 inline hipError_t hipLaunchCooperativeKernel(void (*k)(A), dim3 grid, dim3 block, void** args, unsigned lds, hipStream_t) {
+  if (emu_capture) return hipErrorStreamCaptureUnsupported;
   const A arg = *(const A*)args[0];
   emu::launch_coop([&]() { k(arg); }, grid, block, lds);
   return hipSuccess;
