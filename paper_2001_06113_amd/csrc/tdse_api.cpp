@@ -3627,14 +3627,14 @@ int tdse_run(tdse_plan_t p, const void* u0, void* uT, int32_t on_device) {
   }
   HIP_TRY(hipGraphLaunch(p->gexec, p->stream));
   p->cur = pre;
-  if (p->guard_every > 0) {
-    s = guard_check(p);
-    if (s) return s;
-  }
   p->ucur = p->graph_ucur;
   for (tdse_plan_s* q : p->sub) {
     q->ucur = p->ucur_after[p->nsteps];
     q->cur = p->nsteps;
+  }
+  if (p->guard_every > 0) {
+    s = guard_check(p);
+    if (s) return s;
   }
   if (pre < p->nsteps) {
     s = tdse_step(p, p->nsteps - pre);

@@ -38,3 +38,16 @@ def test_replay_after_the_persistent_launch_did_not_fit(emu, coop_blocks, M):
     for rep in range(3):
         assert np.array_equal(plan.run(prob.u0), passes), rep
     assert plan.query(28) == 0.0
+
+
+@pytest.mark.parametrize("M", [(32,), (24, 32)])
+def test_guard_after_a_replay_scans_the_final_state(emu, M):
+    """An odd number of start-up steps leaves u in the second physical buffer."""
+    prob = periodic_problem_from_seed(95, len(M), M, 0.5, 5, order=2)
+    prob.n_start = 3
+    plan = _graph_plan(emu, prob)
+    plan.call("tdse_configure", 1, 1)
+    for rep in range(3):
+        u0 = (1.0 + rep) * np.asarray(prob.u0)
+        u = plan.run(u0)
+        assert abs(plan.query(30) - np.linalg.norm(u)) <= 1e-12 * np.linalg.norm(u), rep
