@@ -55,7 +55,9 @@
 //
 // Every wait is bounded: a reader that polled spin_limit times reports a
 // timeout to the host, takes what is there and waits no more, so every
-// workgroup always runs to the end of the kernel.
+// workgroup always runs to the end of the kernel.  What it takes early are
+// marks, so the line it transforms becomes NaN, and with it all that the line
+// reaches: a run that timed out never ends with finite wrong values.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -104,7 +106,7 @@ __device__ __forceinline__ bool arrived(double2 v) {
 // there.  `late`: this thread timed out before.
 template <int EPT, typename F>
 __device__ __forceinline__ void receive(__amdgpu_buffer_rsrc_t rs, F idx, double2 (&v)[EPT], int limit, unsigned* flag,
-                                        bool& late) {
+                                        unsigned run, bool& late) {
   int it = 0;
   for (;;) {
     bool ok = true;
@@ -115,7 +117,7 @@ __device__ __forceinline__ void receive(__amdgpu_buffer_rsrc_t rs, F idx, double
     if (ok || late) break;
     if (++it > limit) {
       late = true;
-      __hip_atomic_store(flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(flag, run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
     __builtin_amdgcn_s_sleep(1);
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");   // the loads are issued anew
@@ -218,7 +220,7 @@ __global__ __launch_bounds__(persist2d_threads(N)) void k_persist2d(Persist2DArg
 #pragma unroll
           for (int q = 0; q < EA; ++q) v[q] = cload(rtile, (int64_t)(t + TA * q) * N + line);
         } else {
-          receive<EA>(xcol, [&](int q) { return blk(t + TA * q, line, N); }, v, a.spin_limit, a.flag, late);
+          receive<EA>(xcol, [&](int q) { return blk(t + TA * q, line, N); }, v, a.spin_limit, a.flag, a.run, late);
         }
       }
       fft_ab(v, Inv());
@@ -260,7 +262,7 @@ __global__ __launch_bounds__(persist2d_threads(N)) void k_persist2d(Persist2DArg
 #pragma unroll
         for (int q = 0; q < EPT; ++q) dh[0][q] = incr2(dphi2_at(m + 1), q);
       }
-      if (inA) receive<EA>(xrow, [&](int q) { return blk(line, t + TA * q, N); }, v, a.spin_limit, a.flag, late);
+      if (inA) receive<EA>(xrow, [&](int q) { return blk(line, t + TA * q, N); }, v, a.spin_limit, a.flag, a.run, late);
       fft_ab(v, Fwd());   // its barriers publish t1s
       if (inA) {
 #pragma unroll
@@ -326,11 +328,9 @@ __global__ __launch_bounds__(persist2d_threads(N)) void k_persist2d(Persist2DArg
   }
 }
 
-// before each launch: the timeout flag, and marks in both exchange buffers
-// (n entries each)
-__global__ __launch_bounds__(256) void k_persist2d_reset(unsigned* flag, double2* xrow, double2* xcol, int n) {
+// before each launch: marks in both exchange buffers (n entries each)
+__global__ __launch_bounds__(256) void k_persist2d_reset(double2* xrow, double2* xcol, int n) {
   const int g = blockIdx.x * 256 + threadIdx.x;
-  if (g == 0) *flag = 0u;
   if (g < n) {
     xrow[g] = xmark();
     xcol[g] = xmark();
@@ -364,7 +364,7 @@ hipError_t persist2d_launch(const Persist2DArgs& a, hipStream_t s) {
   Persist2DArgs arg = a;
   void* args[] = {&arg};
   const size_t lds = persist2d_lds_bytes(N, a.order);
-  hipLaunchKernelGGL(k_persist2d_reset, dim3((N * N + 255) / 256), dim3(256), 0, s, a.flag, a.xrow, a.xcol, N * N);
+  hipLaunchKernelGGL(k_persist2d_reset, dim3((N * N + 255) / 256), dim3(256), 0, s, a.xrow, a.xcol, N * N);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return hipLaunchCooperativeKernel(k_persist2d<N, PH2>, dim3(N / 2), dim3(persist2d_threads(N)), args, (unsigned)lds, s);

@@ -12,6 +12,7 @@
 #include <algorithm>
 #include <atomic>
 #include <memory>
+#include <mutex>
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
@@ -34,6 +35,12 @@ int fail(int status, const std::string& msg) {
   g_last_error = msg;
   return status;
 }
+
+// polls after which a reader of the persistent 2D launch gives an exchange up
+// (the CPU build of the tests sets its own)
+#ifndef TDSE_P2_SPIN_LIMIT
+#define TDSE_P2_SPIN_LIMIT 1000000
+#endif
 
 #define HIP_TRY(expr)                                                                      \
   do {                                                                                     \
@@ -280,6 +287,48 @@ constexpr int NFAM = 6;   // batched pass families (schedule families 0..2, phas
 // a whole run (1D instances; 2D with both lengths 2^a, both 3 * 2^a, mixed)
 constexpr int NLANE = 4;
 
+// Words of pinned host memory in which persistent launches report a timeout, so
+// that the host can look without waiting for the stream.  A plan holds one from
+// its first bind to its end; the memory (a page per 1024 plans alive at once)
+// is kept, since to free it would wait for the whole device.
+class TimeoutWords {
+ public:
+  unsigned* take() {
+    std::lock_guard<std::mutex> lock(mx_);
+    if (free_.empty()) {
+      void* b = nullptr;
+      if (hipHostMalloc(&b, 1024 * sizeof(unsigned), hipHostMallocPortable | hipHostMallocMapped) != hipSuccess)
+        return nullptr;
+      std::memset(b, 0, 1024 * sizeof(unsigned));
+      for (int i = 0; i < 1024; ++i) free_.push_back((unsigned*)b + i);
+    }
+    unsigned* w = free_.back();
+    free_.pop_back();
+    return w;
+  }
+  void give(unsigned* w) {
+    std::lock_guard<std::mutex> lock(mx_);
+    free_.push_back(w);
+  }
+  // a run number no other run of the process has (a word's late writer of an
+  // earlier run cannot be taken for this one's)
+  unsigned next_run() {
+    unsigned r;
+    do r = run_.fetch_add(1) + 1;
+    while (r == 0);
+    return r;
+  }
+
+ private:
+  std::mutex mx_;
+  std::vector<unsigned*> free_;
+  std::atomic<unsigned> run_{0};
+};
+TimeoutWords& timeout_words() {
+  static TimeoutWords* w = new TimeoutWords;   // outlives every plan
+  return *w;
+}
+
 struct tdse_plan_s {
   // grid: M1 x M2 (1D: M1 = 1).  A 3D grid M0 x Mmid x M2 is held as M1 =
   // M0 Mmid rows of M2: the row pass runs over the last axis, the column pass
@@ -398,14 +447,17 @@ struct tdse_plan_s {
   size_t o_f1tab = 0, o_f1e = 0;
 
   // persistent Adams steps of a square 2D periodic FP64 plan
-  // (persist2d_kernels.hip): per-step scalars, static column factors and the
-  // timeout flag, at the end of the workspace
+  // (persist2d_kernels.hip): per-step scalars and static column factors, at
+  // the end of the workspace; a launch whose exchange timed out writes p2_run,
+  // the number of the run since tdse_set_state, to the host word p2_word
   bool persist = false;       // the plan qualifies
   bool persist_on = true;     // tdse_configure(TDSE_CFG_PERSISTENT)
   int persist_cap = -1;       // co-resident workgroups of the device (-1: not asked yet)
   std::vector<double> p2tab;
   std::vector<double2> p2S2;
-  size_t o_p2tab = 0, o_p2S2 = 0, o_p2flag = 0;
+  size_t o_p2tab = 0, o_p2S2 = 0;
+  unsigned* p2_word = nullptr;
+  unsigned p2_run = 0;        // 0: no persistent launch since tdse_set_state
   int64_t p2_oD2 = 0;
   bool p2_ph2 = false;
   static constexpr int P2_OSTEP = 16;
@@ -446,6 +498,7 @@ struct tdse_plan_s {
       if (side_st[i]) (void)hipStreamDestroy(side_st[i]);
     }
     if (lane_fork) (void)hipEventDestroy(lane_fork);
+    if (p2_word) timeout_words().give(p2_word);
     for (tdse_plan_s* q : sub) delete q;
   }
 
@@ -1898,6 +1951,17 @@ int upload_persist2d(tdse_plan_s* p) {
   return TDSE_OK;
 }
 
+// Has a persistent launch of this run reported a timeout?  Its readers took
+// marks for data, so u, B and the history hold NaN from there on, and only
+// tdse_set_state makes the plan usable again.  Does not wait: a launch still
+// under way is found by a later call.
+int persist2d_report(tdse_plan_s* p) {
+  if (!p->p2_run || __atomic_load_n(p->p2_word, __ATOMIC_RELAXED) != p->p2_run) return TDSE_OK;
+  p->p2_run = 0;
+  p->cur = -1;
+  return fail(TDSE_EDEVICE, "persistent 2D kernel: an exchange timed out (co-resident grid not scheduled)");
+}
+
 // Adams steps cur+1 .. end (cur > ns, after the Adams start) in one persistent
 // launch.  Returns 1 (and clears p->persist) when the device cannot hold the
 // co-resident grid, so the caller takes the two-pass path.
@@ -1920,7 +1984,7 @@ int persist2d_step(tdse_plan_s* p, int end, bool write_u) {
   a.nV = p->nV;
   a.write_u = write_u ? 1 : 0;
   a.ph2 = p->p2_ph2 ? 1 : 0;
-  a.spin_limit = 1000000;
+  a.spin_limit = TDSE_P2_SPIN_LIMIT;
   a.dt = p->dt;
   a.c0 = p->mu[0] * p->dt;
   a.scale = 1.0 / (double)p->P;
@@ -1937,7 +2001,9 @@ int persist2d_step(tdse_plan_s* p, int end, bool write_u) {
   a.S2 = (const double2*)(p->ws + p->o_p2S2);
   a.tw = (const double2*)p->tw(0, 1);
   a.uout = p->u(p->ucur);
-  a.flag = (unsigned*)(p->ws + p->o_p2flag);
+  if (!p->p2_run) p->p2_run = timeout_words().next_run();
+  a.run = p->p2_run;
+  a.flag = p->p2_word;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   const size_t first = p->ev_used;
   if (p->prof) {
@@ -1957,13 +2023,8 @@ int persist2d_step(tdse_plan_s* p, int end, bool write_u) {
     HIP_TRY(hipEventRecord(e1, p->stream));
     p->prof_marks.push_back({first, 4});
   }
-  // an exchange that timed out leaves the run unusable: report it now
-  unsigned flag = 0;
-  HIP_TRY(hipMemcpyAsync(&flag, a.flag, sizeof(flag), hipMemcpyDeviceToHost, p->stream));
-  HIP_TRY(hipStreamSynchronize(p->stream));
-  if (flag) return fail(TDSE_EDEVICE, "persistent 2D kernel: an exchange timed out (co-resident grid not scheduled)");
   p->cur = end;
-  return TDSE_OK;
+  return persist2d_report(p);
 }
 
 // ============================================================ diagnostics
@@ -1985,6 +2046,8 @@ int guard_check(tdse_plan_s* p) {
   double h[3] = {0.0, 0.0, 0.0};
   HIP_TRY(hipMemcpyAsync(h, acc, 3 * sizeof(double), hipMemcpyDeviceToHost, p->stream));
   HIP_TRY(hipStreamSynchronize(p->stream));
+  const int s = persist2d_report(p);
+  if (s) return s;
   unsigned bad = 0;
   std::memcpy(&bad, &h[2], sizeof(bad));
   p->state_norm = std::sqrt(h[0]);
@@ -2030,6 +2093,8 @@ int history_residual(tdse_plan_s* p, double* value) {
   double h[2] = {0.0, 0.0};
   HIP_TRY(hipMemcpyAsync(h, acc, sizeof(h), hipMemcpyDeviceToHost, p->stream));
   HIP_TRY(hipStreamSynchronize(p->stream));
+  s = persist2d_report(p);
+  if (s) return s;
   *value = h[1] > 0.0 ? std::sqrt(h[0] / h[1]) : 0.0;
   return TDSE_OK;
 }
@@ -3286,7 +3351,6 @@ int tdse_plan(const tdse_problem_t* prob, tdse_plan_t* out) {
     build_persist2d(p);
     p->o_p2tab = off; off = align256(off + p->p2tab.size() * sizeof(double));
     p->o_p2S2 = off; off = align256(off + p->p2S2.size() * sizeof(double2));
-    p->o_p2flag = off; off = align256(off + sizeof(unsigned));
   }
   if (p->dim == 1 && !split && run1d_supported(p->M2) && p->vkind != TDSE_V_SAMPLED) {
     p->run1d = true;
@@ -3337,6 +3401,8 @@ int tdse_bind(tdse_plan_t p, void* ws, size_t bytes, void* stream) {
     if (s) return s;
   }
   if (p->persist) {
+    if (!p->p2_word) p->p2_word = timeout_words().take();
+    if (!p->p2_word) return fail(TDSE_ENOMEM, "no pinned host memory");
     const int s = upload_persist2d(p);
     if (s) return s;
   }
@@ -3370,6 +3436,7 @@ int tdse_set_state(tdse_plan_t p, const void* u0, int32_t on_device) {
   }
   p->ucur = 0;
   p->uh_cur = 0;
+  p->p2_run = 0;
   const size_t bytes = (size_t)p->P * sizeof(double2);
   if (on_device) {
     HIP_TRY(hipMemcpyAsync(p->u(0), u0, bytes, hipMemcpyDeviceToDevice, p->stream));
@@ -3403,8 +3470,8 @@ int tdse_step(tdse_plan_t p, int32_t k) {
 }
 
 namespace {
-// a stream under capture records kernel passes: a cooperative launch, and the
-// read of its timeout flag, cannot be captured
+// a stream under capture records kernel passes: a cooperative launch cannot be
+// captured
 bool capturing(hipStream_t s) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   return s && hipStreamIsCapturing(s, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
@@ -3412,6 +3479,8 @@ bool capturing(hipStream_t s) {
 
 int step_range(tdse_plan_s* p, int k) {
   if (p->is_batch()) return batch_step(p, k);
+  const int r = persist2d_report(p);
+  if (r) return r;
   const int end = p->cur + k;
   if (p->run1d) return k > 0 ? run1d_step(p, end) : TDSE_OK;
   // chosen once per run: the general path carries a tile that this one does
@@ -3454,6 +3523,8 @@ int tdse_get_state(tdse_plan_t p, void* u, int32_t on_device) {
     }
     return TDSE_OK;
   }
+  int s = persist2d_report(p);
+  if (s) return s;
   const size_t bytes = (size_t)p->P * sizeof(double2);
   if (on_device) {
     HIP_TRY(hipMemcpyAsync(u, p->u(p->ucur), bytes, hipMemcpyDeviceToDevice, p->stream));
@@ -3461,6 +3532,8 @@ int tdse_get_state(tdse_plan_t p, void* u, int32_t on_device) {
   }
   HIP_TRY(hipMemcpyAsync(u, p->u(p->ucur), bytes, hipMemcpyDeviceToHost, p->stream));
   HIP_TRY(hipStreamSynchronize(p->stream));
+  s = persist2d_report(p);
+  if (s) return s;
   const double* d = (const double*)u;
   for (size_t i = 0; i < 2 * (size_t)p->P; ++i)
     if (!std::isfinite(d[i])) return fail(TDSE_ENONFINITE, "state is not finite");

@@ -379,7 +379,8 @@ hipError_t launch_run1d(const Run1DArgs& a, hipStream_t s, hipEvent_t e0 = nullp
 // S2 holds exp(-i k2^2 j dt), j = 1..n-1.  tile: the row-major tile of the
 // two-pass path (read by the first step, written by a launch that ends
 // before T); xrow, xcol: N x N complex128 exchange buffers (blocked layout),
-// filled with marks by the launch; flag: the timeout flag (reset by the launch).
+// filled with marks by the launch; flag: a word of pinned host memory that a
+// reader whose exchange timed out sets to `run`.
 struct Persist2DArgs {
   int N, order, nsteps, m0, m1, mbase, ostep, nV, write_u, ph2, spin_limit;
   double dt, c0, scale;
@@ -397,6 +398,7 @@ struct Persist2DArgs {
   const double2* tw;
   double2* uout;
   unsigned* flag;
+  unsigned run;
 };
 bool persist2d_supported(int N);
 size_t persist2d_lds_bytes(int N, int order);

@@ -82,6 +82,9 @@ struct emu_graph {
 extern thread_local emu_graph* emu_capture;
 // co-resident workgroups per multiprocessor of a cooperative launch (a test may lower it)
 extern "C" int emu_coop_blocks;
+// polls of the persistent launch's readers, and the waits of the host for a stream
+extern "C" int emu_spin_limit, emu_stream_waits;
+#define TDSE_P2_SPIN_LIMIT emu_spin_limit
 
 namespace emu {
 // Cooperative fibers: every emulated thread of a block runs on one OS thread
@@ -338,6 +341,7 @@ inline unsigned atomicOr(unsigned* p, unsigned v) {
 using std::isfinite;
 #define __HIP_MEMORY_SCOPE_WORKGROUP 2
 #define __HIP_MEMORY_SCOPE_AGENT 3
+#define __HIP_MEMORY_SCOPE_SYSTEM 4
 template <typename T>
 inline T __hip_atomic_load(const T* p, int, int) { return *p; }
 template <typename T>
@@ -389,6 +393,7 @@ inline hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) {
   return hipSuccess;
 }
 inline hipError_t hipStreamSynchronize(hipStream_t) {
+  __atomic_fetch_add(&emu_stream_waits, 1, __ATOMIC_RELAXED);
   return emu_capture ? hipErrorStreamCaptureUnsupported : hipSuccess;
 }
 typedef struct emu_event* hipEvent_t;
@@ -443,6 +448,11 @@ inline hipError_t hipLaunchCooperativeKernel(void (*k)(A), dim3 grid, dim3 block
   const A arg = *(const A*)args[0];
   emu::launch_coop([&]() { k(arg); }, grid, block, lds);
   return hipSuccess;
+}
+constexpr unsigned hipHostMallocPortable = 1, hipHostMallocMapped = 2;
+inline hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
+  *p = std::malloc(n);
+  return *p ? hipSuccess : hipErrorInvalidValue;
 }
 inline hipError_t hipSetDevice(int) { return hipSuccess; }
 constexpr unsigned hipStreamNonBlocking = 1, hipEventDisableTiming = 2;
