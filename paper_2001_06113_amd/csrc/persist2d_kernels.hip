@@ -173,10 +173,12 @@ __global__ __launch_bounds__(persist2d_threads(N)) void k_persist2d(Persist2DArg
   double2 B[EPT];
 #pragma unroll
   for (int q = 0; q < EPT; ++q) B[q] = a.B[(int64_t)line * N + t + TL * q];
-  for (int s = 0; s < nh; ++s)
+  for (int s = 0; s < nh; ++s) {
+    if (s == (a.m0 + 1) % nh) continue;   // the entry the first step replaces
 #pragma unroll
     for (int q = 0; q < EPT; ++q)
       ringL[(s * LPW + i) * N + t + TL * q] = a.ring[(int64_t)s * N * N + (int64_t)line * N + t + TL * q];
+  }
   // static column factors exp(-i k2^2 j dt)
   double2 S2[H][EPT];
 #pragma unroll
@@ -316,19 +318,24 @@ __global__ __launch_bounds__(persist2d_threads(N)) void k_persist2d(Persist2DArg
       }
     }
   }
-  // the state goes back to memory for the next launch (or the two-pass path)
+  // the state goes back to memory for the next launch (or the two-pass path):
+  // of the history, the entries this launch made
   if (a.m1 < a.nsteps) {
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < EPT; ++q) a.B[(int64_t)line * N + t + TL * q] = B[q];
-    for (int s = 0; s < nh; ++s)
+    for (int m = max(a.m0 + 1, a.m1 + 1 - nh); m <= a.m1; ++m) {
+      const int s = m % nh;
 #pragma unroll
       for (int q = 0; q < EPT; ++q)
         a.ring[(int64_t)s * N * N + (int64_t)line * N + t + TL * q] = ringL[(s * LPW + i) * N + t + TL * q];
+    }
   }
 }
 
-// before each launch: marks in both exchange buffers (n entries each)
+// marks in both exchange buffers (n entries each), before the first launch of
+// a run: every launch that ends before T leaves each entry marked, as its
+// reader put it back and the last row phase sends none
 __global__ __launch_bounds__(256) void k_persist2d_reset(double2* xrow, double2* xcol, int n) {
   const int g = blockIdx.x * 256 + threadIdx.x;
   if (g < n) {
@@ -364,9 +371,11 @@ hipError_t persist2d_launch(const Persist2DArgs& a, hipStream_t s) {
   Persist2DArgs arg = a;
   void* args[] = {&arg};
   const size_t lds = persist2d_lds_bytes(N, a.order);
-  hipLaunchKernelGGL(k_persist2d_reset, dim3((N * N + 255) / 256), dim3(256), 0, s, a.xrow, a.xcol, N * N);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (!a.marked) {
+    hipLaunchKernelGGL(k_persist2d_reset, dim3((N * N + 255) / 256), dim3(256), 0, s, a.xrow, a.xcol, N * N);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   return hipLaunchCooperativeKernel(k_persist2d<N, PH2>, dim3(N / 2), dim3(persist2d_threads(N)), args, (unsigned)lds, s);
 }
 

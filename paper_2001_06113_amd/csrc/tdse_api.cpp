@@ -458,6 +458,7 @@ struct tdse_plan_s {
   size_t o_p2tab = 0, o_p2S2 = 0;
   unsigned* p2_word = nullptr;
   unsigned p2_run = 0;        // 0: no persistent launch since tdse_set_state
+  bool p2_marked = false;     // the exchange buffers hold marks throughout, as a launch leaves them
   int64_t p2_oD2 = 0;
   bool p2_ph2 = false;
   static constexpr int P2_OSTEP = 16;
@@ -2004,6 +2005,7 @@ int persist2d_step(tdse_plan_s* p, int end, bool write_u) {
   if (!p->p2_run) p->p2_run = timeout_words().next_run();
   a.run = p->p2_run;
   a.flag = p->p2_word;
+  a.marked = p->p2_marked ? 1 : 0;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   const size_t first = p->ev_used;
   if (p->prof) {
@@ -2024,6 +2026,7 @@ int persist2d_step(tdse_plan_s* p, int end, bool write_u) {
     p->prof_marks.push_back({first, 4});
   }
   p->cur = end;
+  p->p2_marked = true;
   return persist2d_report(p);
 }
 
@@ -2068,6 +2071,7 @@ int history_residual(tdse_plan_s* p, double* value) {
   const int n = p->cur, nh = p->order - 1;
   const bool split = p->precision == TDSE_FP32_SPLIT;
   double2* X = p->u(1 - p->ucur);                                  // free in the Adams phase
+  p->p2_marked = false;                                            // X and Y are the persistent launch's buffers
   double2* Y = split ? (double2*)p->ring_slot(0, 0) : (double2*)(p->ws + p->o_dbuf);
   LineArgs a = base_args(p, 0);
   col_geom(p, 0, a);
@@ -3437,6 +3441,7 @@ int tdse_set_state(tdse_plan_t p, const void* u0, int32_t on_device) {
   p->ucur = 0;
   p->uh_cur = 0;
   p->p2_run = 0;
+  p->p2_marked = false;
   const size_t bytes = (size_t)p->P * sizeof(double2);
   if (on_device) {
     HIP_TRY(hipMemcpyAsync(p->u(0), u0, bytes, hipMemcpyDeviceToDevice, p->stream));

@@ -379,10 +379,10 @@ hipError_t launch_run1d(const Run1DArgs& a, hipStream_t s, hipEvent_t e0 = nullp
 // S2 holds exp(-i k2^2 j dt), j = 1..n-1.  tile: the row-major tile of the
 // two-pass path (read by the first step, written by a launch that ends
 // before T); xrow, xcol: N x N complex128 exchange buffers (blocked layout),
-// filled with marks by the launch; flag: a word of pinned host memory that a
+// filled with marks by the launch unless they hold them (marked); flag: a word of pinned host memory that a
 // reader whose exchange timed out sets to `run`.
 struct Persist2DArgs {
-  int N, order, nsteps, m0, m1, mbase, ostep, nV, write_u, ph2, spin_limit;
+  int N, order, nsteps, m0, m1, mbase, ostep, nV, write_u, ph2, spin_limit, marked;
   double dt, c0, scale;
   double ch[MAXH + 1];
   const double* V;

@@ -82,8 +82,9 @@ struct emu_graph {
 extern thread_local emu_graph* emu_capture;
 // co-resident workgroups per multiprocessor of a cooperative launch (a test may lower it)
 extern "C" int emu_coop_blocks;
-// polls of the persistent launch's readers, and the waits of the host for a stream
-extern "C" int emu_spin_limit, emu_stream_waits;
+// polls of the persistent launch's readers; counts of the host's waits for a
+// stream and of kernel launches
+extern "C" int emu_spin_limit, emu_stream_waits, emu_launches;
 #define TDSE_P2_SPIN_LIMIT emu_spin_limit
 
 namespace emu {
@@ -140,6 +141,7 @@ void launch(K kernel, dim3 grid, dim3 block, Args... args) {
     emu_capture->ops.push_back([=]() { launch(kernel, grid, block, args...); });
     return;
   }
+  __atomic_fetch_add(&emu_launches, 1, __ATOMIC_RELAXED);
   gridDim = grid;
   blockDim = block;
   for (unsigned bi = 0; bi < grid.x * grid.y; ++bi) {
@@ -244,6 +246,7 @@ inline void coop_entry() {
 }
 template <typename F>
 void launch_coop(F body, dim3 grid, dim3 block, size_t lds_bytes) {
+  __atomic_fetch_add(&emu_launches, 1, __ATOMIC_RELAXED);
   gridDim = grid;
   blockDim = block;
   CoopRun r;
