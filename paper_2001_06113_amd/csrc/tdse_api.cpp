@@ -430,21 +430,24 @@ struct tdse_plan_s {
   size_t o_lv = 0, lv_bytes = 0;
 
   // one-workgroup run of a 1D periodic FP64 plan (run1d_kernels.hip): the
-  // per-step scalar table and the static phase factors, at the end of the
-  // workspace (total_core: the workspace without them)
+  // per-step scalar table, the static phase factors and the propagated
+  // history between launches, at the end of the workspace (total_core: the
+  // workspace without them)
   bool run1d = false;
   std::vector<double> r1tab;
   std::vector<double2> r1stab;
-  size_t o_r1tab = 0, o_r1stab = 0, total_core = 0;
+  size_t o_r1tab = 0, o_r1stab = 0, o_r1g = 0, total_core = 0;
   int64_t r1_oH = 0, r1_oR = 0, r1_oA = 0, r1_oD = 0;
 
   // one-workgroup Adams steps of a 1D free-space plan (freespace_run1d.hip):
-  // per-step scalars and the phase factors of one launch's steps, at the end
-  // of the workspace
+  // per-step scalars, the phase factors of one launch's steps and the
+  // propagated history between launches, at the end of the workspace
   bool fs1d = false;          // the plan qualifies
   bool fs1d_on = false;       // the current run's Adams steps take it (chosen at the Adams start)
   std::vector<double> f1tab;
-  size_t o_f1tab = 0, o_f1e = 0;
+  size_t o_f1tab = 0, o_f1e = 0, o_f1g = 0;
+  // the propagated history in memory (run1d, fs1d) is that of t_{cur+1}
+  bool held = false;
 
   // persistent Adams steps of a square 2D periodic FP64 plan
   // (persist2d_kernels.hip): per-step scalars and static column factors, at
@@ -1656,7 +1659,10 @@ int fs1d_steps(tdse_plan_s* p, int end) {
     a.nsteps = p->nsteps;
     a.m0 = p->cur;
     a.m1 = std::min(end, p->cur + FSRUN1D_STEPS);
-    a.i0 = std::max(1, a.m0 + 1 - (p->order - 3));   // the oldest held entry is propagated over order - 2 intervals
+    a.held = p->held;
+    // the factors of the launch's own steps, and without a held history those
+    // that propagate the ring (its oldest entry over order - 2 intervals)
+    a.i0 = p->held ? a.m0 + 2 : std::max(1, a.m0 + 1 - (p->order - 3));
     a.dt = p->dt;
     a.c0 = p->mu[0] * p->dt;
     for (int j = 1; j < p->order; ++j) a.ch[j] = p->dt * p->mu[j];
@@ -1664,12 +1670,14 @@ int fs1d_steps(tdse_plan_s* p, int end) {
     a.vstride = p->P;
     a.tab = (const double*)(p->ws + p->o_f1tab);
     a.etab = (double2*)(p->ws + p->o_f1e);
+    a.G = (double2*)(p->ws + p->o_f1g);
     a.Bm = p->B();
     a.ring = (double2*)(p->ws + p->o_ringf);
     a.uout = p->u(p->ucur);
     const hipError_t e = launch_fs_run1d(p->fx[1].nu, a, p->stream);
     if (e != hipSuccess) return fail(TDSE_EDEVICE, std::string("1D free-space run kernel: ") + hipGetErrorString(e));
     p->cur = a.m1;
+    p->held = true;
   }
   return TDSE_OK;
 }
@@ -1782,6 +1790,7 @@ int plan_free(tdse_plan_s* p, const tdse_problem_t* prob) {
     build_fs1d(p);
     p->o_f1tab = off; off = align256(off + p->f1tab.size() * sizeof(double));
     p->o_f1e = off; off = align256(off + (size_t)(FSRUN1D_STEPS + MAXH) * p->NM * sizeof(double2));
+    p->o_f1g = off; off = align256(off + (size_t)(p->order - 2) * p->NM * sizeof(double2));
   }
   p->total = off;
   return TDSE_OK;
@@ -1884,6 +1893,8 @@ int run1d_step(tdse_plan_s* p, int end) {
   a.u_out = p->u(uo);
   a.B = p->B();
   a.ring = (double2*)p->ring(0);
+  a.G = (double2*)(p->ws + p->o_r1g);
+  a.held = p->held;
   a.stab = (const double2*)(p->ws + p->o_r1stab);
   a.tw = (const double2*)p->tw(0, 1);
   hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -1898,6 +1909,7 @@ int run1d_step(tdse_plan_s* p, int end) {
   if (e0) p->prof_marks.push_back({first, 3});
   p->cur = end;
   p->ucur = uo;
+  p->held = end > p->ns;
   return TDSE_OK;
 }
 
@@ -3361,6 +3373,7 @@ int tdse_plan(const tdse_problem_t* prob, tdse_plan_t* out) {
     build_run1d(p);
     p->o_r1tab = off; off = align256(off + p->r1tab.size() * sizeof(double));
     p->o_r1stab = off; off = align256(off + p->r1stab.size() * sizeof(double2));
+    p->o_r1g = off; off = align256(off + (size_t)(p->order - 2) * p->M2 * sizeof(double2));
   }
   p->total = off;
   *out = p;
@@ -3442,6 +3455,7 @@ int tdse_set_state(tdse_plan_t p, const void* u0, int32_t on_device) {
   p->uh_cur = 0;
   p->p2_run = 0;
   p->p2_marked = false;
+  p->held = false;
   const size_t bytes = (size_t)p->P * sizeof(double2);
   if (on_device) {
     HIP_TRY(hipMemcpyAsync(p->u(0), u0, bytes, hipMemcpyDeviceToDevice, p->stream));
@@ -3982,6 +3996,7 @@ int tdse_set_field(tdse_plan_t p, const double* A_steps) {
   p->tf.A_steps.assign(A_steps, A_steps + (size_t)p->nsteps * p->dim);
   p->tf.prepare();
   p->drop_graph();
+  p->held = false;   // the next launch propagates the ring's entries with the new field
   if (p->run1d) {
     build_run1d(p);
     if (p->bound) {

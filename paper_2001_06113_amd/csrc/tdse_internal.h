@@ -307,11 +307,13 @@ bool fs_nu_supported(int nu);
 // time m = 0..nsteps: the weights of the potential fields at t_m, the first
 // of them, their number, -, and phi(t_m) - phi(t_{m-1}).  etab: phase factors of the
 // intervals i0 .. m1+1 (i: [t_{i-1}, t_i]), filled by the launch, at most
-// FSRUN1D_STEPS + MAXH rows of N.
+// FSRUN1D_STEPS + MAXH rows of N.  G: What_{m1+2-j} propagated to t_{m1+1},
+// j = 2..order-1, left by a launch that ends before T; held: the next launch
+// starts from it, else it propagates the ring's entries.
 constexpr int FSRUN1D_COLS = 12, FSRUN1D_STEPS = 128;
 struct FSRun1DArgs {
   CFAxis ax;
-  int order, nsteps, m0, m1, i0, dinv_lds;
+  int order, nsteps, m0, m1, i0, dinv_lds, held;
   double dt, c0;
   double ch[MAXH + 1];
   const double* V;
@@ -320,6 +322,7 @@ struct FSRun1DArgs {
   double2* etab;
   double2* Bm;
   double2* ring;
+  double2* G;
   double2* uout;
 };
 bool fs_run1d_supported(int nu, const CFAxis& ax);
@@ -348,12 +351,13 @@ hipError_t launch_far_gemm(int M, int N, int K, const double2* A, int64_t sam, i
 //   oA + 8 (m - ns - 1)           f_r(t_m), Adams step m
 //   oD + i - 1                    phi(t_i) - phi(t_{i-1}), i = 1..nsteps
 // (f_r: the eight potential time factors, or the moving well's parameters).
-// stab holds exp(-i k^2 dt), then exp(-i k^2 dt / 2^l), l < L.
+// stab holds exp(-i k^2 dt), then exp(-i k^2 dt / 2^l), l < L.  G and held as
+// in FSRun1DArgs, for launches past the Adams start.
 struct Run1DArgs {
   int M, order, ns, nsteps, L;
   int m0, m1;
   int nV, vkind;
-  int write_u, has_phase;
+  int write_u, has_phase, held;
   double dt, c0;
   double ch[MAXH + 1];
   double rich[4];
@@ -365,6 +369,7 @@ struct Run1DArgs {
   double2* u_out;
   double2* B;
   double2* ring;
+  double2* G;
   const double2* stab;
   const double2* tw;
 };

@@ -36,3 +36,61 @@ def test_persistent_pieces_mark_the_exchange_buffers_once(emu, M, order):
         assert launches.value - before == 2
         plan.step(5)
         assert np.array_equal(_state(plan, prob.M), full)
+
+
+def test_free_1d_pieces_equal_the_whole_run(emu):
+    from emu.emu_plan import EmuPlan
+
+    from workloads import free_problem_from_seed
+
+    for M, nu, order, cheb in (((32,), (256,), 8, 0), ((40,), (512,), 4, 20), ((24,), (256,), 2, 0)):
+        prob = free_problem_from_seed(60 + M[0], 1, M, 0.02, order + 14, order=order, nu=nu, eps=1e-8, q=8)
+        prob.cheb = cheb
+        plan = EmuPlan(emu, prob)
+        full = plan.run(prob.u0)
+        plan.set_state(prob.u0)
+        plan.step(order)
+        for k in (1, 1, 5, 1, 5):
+            plan.step(k)
+        plan.step(1)
+        assert np.array_equal(_state(plan, M), full), (M, order)
+
+
+@pytest.mark.parametrize("domain, order", [("periodic", 8), ("periodic", 4), ("free", 6)])
+def test_field_changed_between_pieces(emu, domain, order):
+    """The entries in flight are carried with the new field, as by the general
+    passes (a sampled potential takes those; in free space a profiled run)."""
+    from emu.emu_plan import EmuPlan
+
+    from workloads import free_problem_from_seed
+
+    N = order + 9
+    if domain == "periodic":
+        prob = periodic_problem_from_seed(150, 1, (32,), 0.05, N, order=order, A_kind="stepwise")
+        prob.n_start, prob.f_kind, prob.f_params = order - 1, ["const"], [(0.0, 0.0)]
+    else:
+        prob = free_problem_from_seed(151, 1, (32,), 0.02, N, order=order, nu=(256,), eps=1e-8, q=8)
+    rng = np.random.default_rng(7)
+    fields = [np.ascontiguousarray(rng.uniform(-1, 1, size=(N, 1))) for _ in range(2)]
+
+    prob.A_kind, prob.A_steps = "stepwise", fields[0]
+
+    def march(plan):
+        plan.call("tdse_set_field", fields[0].ctypes.data_as(C.POINTER(C.c_double)))
+        plan.set_state(prob.u0)
+        plan.step(order + 2)
+        plan.step(1)
+        plan.call("tdse_set_field", fields[1].ctypes.data_as(C.POINTER(C.c_double)))
+        plan.step(1)
+        plan.step(3)
+        return _state(plan, prob.M)
+
+    plan = EmuPlan(emu, prob)
+    got = march(plan)
+    if domain == "periodic":
+        prob.V_samples, prob.V_kind = np.stack([prob.V_fields[0]] * (N + 1)), "sampled"
+        ref = march(EmuPlan(emu, prob))
+    else:
+        plan.call("tdse_profile", 1)
+        ref = march(plan)
+    assert np.linalg.norm(got - ref) <= 1e-12 * np.linalg.norm(ref)
