@@ -1644,6 +1644,14 @@ int upload_fs1d(tdse_plan_s* p) {
   return TDSE_OK;
 }
 
+// The steps of the tdse_step call that enters the Adams phase from which the
+// run takes this path; below, it is taken to be cut into as small pieces, and
+// the launch's start and end are most of its time.  M = 256, nu = 2048 (512
+// threads that spill), two launches per step / this path, us per step in pieces
+// of 1: 47 / 62, 2: 34 / 40, 4: 29 / 30, 8: 27 / 24; nu <= 1024 gains from 1 on
+// (48 / 43 at M = 100, nu = 1024).
+int fs1d_min_piece(int nu) { return nu >= 2048 ? 4 : 1; }
+
 // Adams steps cur+1 .. end (cur >= ns), FSRUN1D_STEPS per launch
 int fs1d_steps(tdse_plan_s* p, int end) {
   if (p->cur == p->ns) {
@@ -3504,7 +3512,7 @@ int step_range(tdse_plan_s* p, int k) {
   if (p->run1d) return k > 0 ? run1d_step(p, end) : TDSE_OK;
   // chosen once per run: the general path carries a tile that this one does
   // not; timed passes (tdse_profile) are the general path's
-  if (p->fs1d && end > p->ns && p->cur <= p->ns) p->fs1d_on = !p->prof;
+  if (p->fs1d && end > p->ns && p->cur <= p->ns) p->fs1d_on = !p->prof && k >= fs1d_min_piece(p->fx[1].nu);
   if (p->fs1d && end > p->ns && p->fs1d_on) {
     for (int m = p->cur + 1; m <= p->ns; ++m) {
       const int s = do_step(p, m, false);

@@ -94,3 +94,24 @@ def test_field_changed_between_pieces(emu, domain, order):
         plan.call("tdse_profile", 1)
         ref = march(plan)
     assert np.linalg.norm(got - ref) <= 1e-12 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("nu, piece, six_steps", [(2048, 1, 12), (2048, 3, 12), (2048, 6, 2), (1024, 1, 2)])
+def test_free_1d_path_by_the_first_piece(emu, nu, piece, six_steps):
+    """Launches of a piece of six steps: two passes per step where the
+    one-workgroup launch does not pay, else a phase table and one launch."""
+    from emu.emu_plan import EmuPlan
+
+    from workloads import free_problem_from_seed
+
+    launches = C.c_int.in_dll(emu, "emu_launches")
+    prob = free_problem_from_seed(63, 1, (20,), 0.02, 20, order=2, nu=(nu,), eps=1e-8, q=8)
+    plan = EmuPlan(emu, prob)
+    full = plan.run(prob.u0)
+    plan.set_state(prob.u0)
+    plan.step(piece)
+    before = launches.value
+    plan.step(6)
+    assert launches.value - before == six_steps
+    plan.step(14 - piece)
+    assert np.linalg.norm(_state(plan, prob.M) - full) <= 1e-13 * np.linalg.norm(full)
