@@ -511,7 +511,7 @@ __device__ __forceinline__ void row_body(const LineArgs& a, int line0, C* lds) {
       acc = cadd(acc, hist);
       const int64_t g = row0 + (t + TL * m);
       if (a.slot_w >= 0) ((C*)a.ring)[a.slot_w * rstride + g] = W;
-      a.Bw[g] = acc;
+      ((double2*)a.fdst)[g] = acc;
       v[m] = from_d<C>(acc);
     }
   } else if (mode == R_INIT) {
@@ -791,7 +791,7 @@ __device__ __forceinline__ void tri_row_body(const LineArgs& a, int line0, doubl
       acc = cadd(acc, hist);
       const int64_t g = row0 + t + TL * m;
       if (a.slot_w >= 0) ((double2*)a.ring)[a.slot_w * rstride + g] = W;
-      a.Bw[g] = acc;
+      ((double2*)a.fdst)[g] = acc;
       v[m] = acc;
     }
   } else if (active && mode == R_FORM) {   // uhat is this transform, and every history entry comes from the ring

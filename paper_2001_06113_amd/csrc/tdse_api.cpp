@@ -604,7 +604,7 @@ LineArgs base_args(const tdse_plan_s* p, int g) {
   a.ring = p->ring(g);
   a.ring_stride = p->P;
   a.Bm = p->B();
-  a.Bw = p->B();
+  a.fdst = p->B();
   a.ph = p->ph();
   a.ph32 = p->ph32();
   a.slot_w = -1;
@@ -789,7 +789,8 @@ int op_richardson_levels(tdse_plan_s* p, int m) {
     if (l == 0) return p->tmp(g);
     char* b = p->ws + p->o_lv + (size_t)(l - 1) * p->lv_bytes;
     const size_t c = align256((size_t)p->P * sizeof(double2));
-    a.Bm = a.Bw = (double2*)(b + c);
+    a.Bm = (double2*)(b + c);
+    a.fdst = a.Bm;
     a.ph = (double2*)(b + 2 * c);
     return b;
   };
@@ -1027,7 +1028,7 @@ int am_passes(tdse_plan_s* p, int m, bool write_u, void* ring, int sw, int slots
   r.c0 = p->mu[0] * p->dt;
   r.ring = ring;
   r.Bm = Br;
-  r.Bw = Bw;
+  r.fdst = Bw;
   r.slot_w = sw;
   for (int j = 1; j <= n - 1; ++j) {
     r.ch[j] = p->dt * p->mu[j];

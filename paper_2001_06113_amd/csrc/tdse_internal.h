@@ -75,7 +75,6 @@ struct LineArgs {
   int acc_first;
   // row pass
   double2* Bm;
-  double2* Bw;         // where R_AM leaves the new state (Bm, or a slot of the adjoint's store)
   void* ring;          // history ring (transform precision)
   int64_t ring_stride;
   int nh;
@@ -83,7 +82,8 @@ struct LineArgs {
   int slot_r[MAXH + 1];
   double c0;           // mu_0 dt  (uhat = B - i c0 W)
   double ch[MAXH + 1]; // dt mu_j
-  void* fdst;          // R_FWD destination (transform precision)
+  void* fdst;          // R_FWD destination (transform precision), or where R_AM leaves the new state (Bm, or a slot
+                       // of the adjoint's store; complex128)
   int pf_pow;          // R_AM: no field along the last axis, its factors of E^(j) are the
                        // j-th powers of E^(1)'s (formed by products, not loaded)
   // phase table
@@ -91,6 +91,10 @@ struct LineArgs {
   float2* ph32;        // split form: the table rounded to complex64 (null in FP64 plans)
   PhaseReq req;
 };
+// 704 bytes, eleven cache lines: with eight bytes more, in the middle or at the
+// end, every pass took 0.1 to 0.2 us longer (split 256^2 12.95 -> 13.35 us per
+// step, 1D split 1024 12.1 -> 12.4)
+static_assert(sizeof(LineArgs) % 64 == 0, "kernel arguments in whole cache lines");
 
 // The same pass of up to four Richardson levels in one launch (a kernel's
 // arguments may take 4 KB)
