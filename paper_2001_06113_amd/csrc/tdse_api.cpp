@@ -2299,15 +2299,19 @@ int batch_record(tdse_plan_s* p) {
 // Instances of different lanes share no data, so no pass of a run waits for
 // another lane's.  (With a fork and a join around every pass, a step of 64
 // uneven instances spent 25 us of 190 in event waits, and every pass lasted as
-// long as its slowest family.)  Not while launches are being timed.
-int batch_fork(tdse_plan_s* p) {
+// long as its slowest family.)  Not while launches are being timed, and not for
+// fewer than four lanes that would be joined after one step: stepped one at a
+// time, us per step on one stream / forked, a 64-point and a 128^2 instance
+// 79 / 105, these and a 192^2 one 94 / 126, eight instances in four lanes 169 / 150.
+int batch_fork(tdse_plan_s* p, int steps) {
   bool any[NLANE] = {};
   for (int l : p->lane) any[l] = true;
+  const int lanes = (int)std::count(any, any + NLANE, true);
   int side = 0;
   bool on_main = false;
   for (int l = 0; l < NLANE; ++l) {
     p->lane_st[l] = p->stream;
-    if (!any[l] || p->prof) continue;
+    if (!any[l] || p->prof || (lanes < NLANE && steps <= 1)) continue;
     if (on_main) {
       if (side == 0) HIP_TRY(hipEventRecord(p->lane_fork, p->stream));
       p->lane_st[l] = p->side_st[side++];
@@ -2371,12 +2375,22 @@ int batch_step(tdse_plan_s* p, int k) {
   if (!p->batch_ready) return fail(TDSE_ESTATE, "tdse_bind must come first");
   const int end = p->cur + k;
   const char* args = p->ws + p->o_args;
-  int s = batch_fork(p);
+  int s = TDSE_OK;
+  bool forked = false;
+  // a stop inside the Adams phase joins the lanes before its last step
+  const int stop = end > p->sub[0]->ns && end < p->nsteps ? end : end + 1;
+  // the launches of a step, on lanes that stay forked for the `steps` from here on
+  auto exec = [&](const std::vector<tdse_plan_s::GLaunch>& L, const char* table,
+                  const std::vector<tdse_plan_s::Narrow>& nar, int steps) {
+    const int e = forked ? TDSE_OK : batch_fork(p, steps);
+    forked = true;
+    return e ? e : batch_exec(p, L, table, nar);
+  };
   for (int m = p->cur + 1; m <= end && !s; ++m) {
     if (m < end || m <= p->sub[0]->ns) {
-      s = batch_exec(p, p->seg[m], args, p->narrows);
+      s = exec(p->seg[m], args, p->narrows, stop - m);
     } else if (m == p->nsteps) {
-      s = batch_exec(p, p->seg_last, args, p->narrows);
+      s = exec(p->seg_last, args, p->narrows, 1);
     } else {
       // a run that stops inside the Adams phase: step m with output,
       // recorded now into the table of such steps
@@ -2387,12 +2401,12 @@ int batch_step(tdse_plan_s* p, int k) {
       s = batch_record_step(p, m, true, L, a, nar);
       if (!s && a.size() > p->cap_targs) s = fail(TDSE_EINVAL, "output step table overflow");
       // the table's last readers, on whichever lane, are done
-      if (!s) s = batch_join(p);
+      if (!s && forked) s = batch_join(p);
+      forked = false;
       if (s) break;
       HIP_TRY(hipStreamSynchronize(p->stream));
       HIP_TRY(hipMemcpy(p->ws + p->o_targs, a.data(), a.size() * sizeof(LineArgs), hipMemcpyHostToDevice));
-      s = batch_fork(p);
-      if (!s) s = batch_exec(p, L, p->ws + p->o_targs, nar);
+      s = exec(L, p->ws + p->o_targs, nar, 1);
     }
     if (!s) p->cur = m;
   }
@@ -2560,7 +2574,7 @@ int autotune_batch(tdse_plan_s* p, int reps) {
           if (lens[i] == N) trial[i] = e;
         status = batch_tiles(p, kind, 1, trial);
         auto pass = [&]() {
-          int e = batch_fork(p);
+          int e = batch_fork(p, 2);
           if (!e) e = batch_exec(p, one, p->ws + p->o_args, p->narrows);
           const int j = batch_join(p);
           return e ? e : j;

@@ -83,8 +83,8 @@ extern thread_local emu_graph* emu_capture;
 // co-resident workgroups per multiprocessor of a cooperative launch (a test may lower it)
 extern "C" int emu_coop_blocks;
 // polls of the persistent launch's readers; counts of the host's waits for a
-// stream and of kernel launches
-extern "C" int emu_spin_limit, emu_stream_waits, emu_launches;
+// stream, of a stream's waits for an event and of kernel launches
+extern "C" int emu_spin_limit, emu_stream_waits, emu_event_waits, emu_launches;
 #define TDSE_P2_SPIN_LIMIT emu_spin_limit
 
 namespace emu {
@@ -462,7 +462,10 @@ constexpr unsigned hipStreamNonBlocking = 1, hipEventDisableTiming = 2;
 inline hipError_t hipStreamCreateWithFlags(hipStream_t* st, unsigned) { *st = (hipStream_t)new char[1]; return hipSuccess; }
 inline hipError_t hipStreamDestroy(hipStream_t st) { delete[] (char*)st; return hipSuccess; }
 inline hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = (hipEvent_t)new char[1]; return hipSuccess; }
-inline hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+inline hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) {
+  __atomic_fetch_add(&emu_event_waits, 1, __ATOMIC_RELAXED);
+  return hipSuccess;
+}
 inline hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) {
   *v = a == hipDeviceAttributeMultiprocessorCount ? 256 : 160 * 1024;
   return hipSuccess;

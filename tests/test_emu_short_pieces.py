@@ -115,3 +115,24 @@ def test_free_1d_path_by_the_first_piece(emu, nu, piece, six_steps):
     assert launches.value - before == six_steps
     plan.step(14 - piece)
     assert np.linalg.norm(_state(plan, prob.M) - full) <= 1e-13 * np.linalg.norm(full)
+
+
+@pytest.mark.parametrize("shapes, lanes", [([(64,), (64, 64)], 2), ([(64,), (64, 64), (192, 192), (64, 192)], 4)])
+def test_batch_pieces_fork_their_lanes_at_most_once(emu, shapes, lanes):
+    """A fork and a join are a wait per side stream each; fewer than four lanes
+    stay on one stream for a single step."""
+    from emu.emu_plan import EmuBatchPlan
+
+    waits = C.c_int.in_dll(emu, "emu_event_waits")
+    probs = [periodic_problem_from_seed(160 + i, len(M), M, 0.01, 6, order=2) for i, M in enumerate(shapes)]
+    plan = EmuBatchPlan(emu, probs)
+    full = plan.run([p.u0 for p in probs])
+    packed = np.concatenate([np.asarray(p.u0, dtype=np.complex128).ravel() for p in probs])
+    plan.call("tdse_set_state", C.c_void_p(packed.ctypes.data), 1)
+    for k, forks in ((1, lanes == 4), (2, 2 if lanes == 4 else 0), (3, 1)):
+        before = waits.value
+        plan.call("tdse_step", k)
+        assert waits.value - before == 2 * (lanes - 1) * forks, k
+    out = np.zeros_like(packed)
+    plan.call("tdse_get_state", C.c_void_p(out.ctypes.data), 1)
+    assert np.array_equal(out, np.concatenate([u.ravel() for u in full]))
