@@ -431,12 +431,11 @@ struct tdse_plan_s {
 
   // one-workgroup run of a 1D periodic FP64 plan (run1d_kernels.hip): the
   // per-step scalar table, the static phase factors and the propagated
-  // history between launches, at the end of the workspace (total_core: the
-  // workspace without them)
+  // history between launches, at the end of the workspace
   bool run1d = false;
   std::vector<double> r1tab;
   std::vector<double2> r1stab;
-  size_t o_r1tab = 0, o_r1stab = 0, o_r1g = 0, total_core = 0;
+  size_t o_r1tab = 0, o_r1stab = 0, o_r1g = 0;
   int64_t r1_oH = 0, r1_oR = 0, r1_oA = 0, r1_oD = 0;
 
   // one-workgroup Adams steps of a 1D free-space plan (freespace_run1d.hip):
@@ -1808,13 +1807,42 @@ int plan_free(tdse_plan_s* p, const tdse_problem_t* prob) {
 
 // ============================================================ 1D, one workgroup
 //
+// Static phase factors exp(-i k^2 tau) from extended precision, for k = 0..M/2:
+// k and -k have the same one, and the multiples of an interval are powers in
+// extended precision (a table of four levels at M = 2048 took 10240 sines and
+// cosines one by one and 2.0 ms of tdse_plan; now 1025).
+struct StaticPhase {
+  long double c, s;
+  StaticPhase(int k, long double tau) { sincosl(-(long double)k * (long double)k * tau, &s, &c); }
+  StaticPhase operator*(const StaticPhase& o) const {
+    StaticPhase r = *this;
+    r.c = c * o.c - s * o.s;
+    r.s = c * o.s + s * o.c;
+    return r;
+  }
+  // into entries k and -k of a table row of M
+  void put(double2* row, int k, int M) const { row[k] = row[k ? M - k : 0] = double2{(double)c, (double)s}; }
+};
+
 // Tables of the one-workgroup 1D run (layout in tdse_internal.h): the time
 // factors and phase increments of every step and start-up sub-step, in the
-// order the kernel consumes them, and the static phase factors
-// exp(-i k^2 tau) of the Adams intervals tau = j dt and of the sub-steps
-// tau = dt / 2^l, from extended precision.
+// order the kernel consumes them, and once per plan the static phase factors
+// of the intervals dt and dt / 2^l.
+void build_run1d_static(tdse_plan_s* p) {
+  const int L = p->L, M = p->M2;
+  p->r1stab.resize((size_t)(1 + L) * M);
+  for (int k = 0; k <= M / 2; ++k) {
+    StaticPhase z(k, (long double)p->dt / (long double)(1 << (L - 1)));
+    for (int l = L - 1; l >= 0; --l) {
+      z.put(p->r1stab.data() + (size_t)(1 + l) * M, k, M);
+      if (l > 0) z = z * z;
+    }
+    z.put(p->r1stab.data(), k, M);
+  }
+}
+
 void build_run1d(tdse_plan_s* p) {
-  const int N = p->nsteps, ns = p->ns, L = p->L, M = p->M2;
+  const int N = p->nsteps, ns = p->ns, L = p->L;
   std::vector<double>& T = p->r1tab;
   T.clear();
   double f[MAXV];
@@ -1850,15 +1878,6 @@ void build_run1d(tdse_plan_s* p) {
     p->tf.phi(p->t_at(i), pb);
     p->tf.phi(p->t_at(i - 1), pa);
     T.push_back(pb[0] - pa[0]);
-  }
-  p->r1stab.assign((size_t)(1 + L) * M, double2{0.0, 0.0});
-  for (int r = 0; r <= L; ++r) {
-    const long double tau = (long double)p->dt / (long double)(r > 0 ? 1 << (r - 1) : 1);
-    for (int idx = 0; idx < M; ++idx) {
-      const long double k = (long double)(idx < M / 2 ? idx : idx - M);
-      const long double th = -k * k * tau;
-      p->r1stab[(size_t)r * M + idx] = double2{(double)cosl(th), (double)sinl(th)};
-    }
   }
 }
 
@@ -1927,10 +1946,23 @@ int run1d_step(tdse_plan_s* p, int end) {
 // Tables of the persistent 2D Adams steps (layout in tdse_internal.h): per
 // Adams step m = ns+1..N the potential time factors at t_m and the axis-0
 // phase differences of the n-1 intervals ending at t_{m+1}; the axis-1 phase
-// increments of every step; the static axis-1 factors exp(-i k2^2 j dt) from
-// extended precision.
+// increments of every step; and once per plan the static axis-1 factors
+// exp(-i k2^2 j dt).
+void build_persist2d_static(tdse_plan_s* p) {
+  const int M = p->M2, nh = p->order - 1;
+  p->p2S2.resize((size_t)nh * M);
+  for (int k = 0; k <= M / 2; ++k) {
+    const StaticPhase z(k, (long double)p->dt);
+    StaticPhase zj = z;
+    for (int j = 1; j <= nh; ++j) {
+      zj.put(p->p2S2.data() + (size_t)(j - 1) * M, k, M);
+      zj = zj * z;
+    }
+  }
+}
+
 void build_persist2d(tdse_plan_s* p) {
-  const int N = p->nsteps, ns = p->ns, M = p->M2, nh = p->order - 1;
+  const int N = p->nsteps, ns = p->ns, nh = p->order - 1;
   std::vector<double>& T = p->p2tab;
   T.clear();
   double f[MAXV], pb[3], pa[3];
@@ -1956,13 +1988,6 @@ void build_persist2d(tdse_plan_s* p) {
     T.push_back(pb[1] - pa[1]);
     if (pb[1] - pa[1] != 0.0) p->p2_ph2 = true;
   }
-  p->p2S2.assign((size_t)nh * M, double2{0.0, 0.0});
-  for (int j = 1; j <= nh; ++j)
-    for (int idx = 0; idx < M; ++idx) {
-      const long double k = (long double)(idx < M / 2 ? idx : idx - M);
-      const long double th = -k * k * (long double)j * (long double)p->dt;
-      p->p2S2[(size_t)(j - 1) * M + idx] = double2{(double)cosl(th), (double)sinl(th)};
-    }
 }
 
 int upload_persist2d(tdse_plan_s* p) {
@@ -2419,6 +2444,8 @@ int batch_step(tdse_plan_s* p, int k) {
   return TDSE_OK;
 }
 
+int plan_single(const tdse_problem_t* prob, tdse_plan_s** out, bool alone);
+
 // Plan a batch: instances planned one by one, then a dry recording of the
 // run (no device memory touched) to size the argument tables.
 int plan_batch(const tdse_problem_t* probs, int count, tdse_plan_s** out) {
@@ -2431,14 +2458,8 @@ int plan_batch(const tdse_problem_t* probs, int count, tdse_plan_s** out) {
     if (probs[i].dim == 3) return fail(TDSE_EUNSUPPORTED, "batches take 1D and 2D instances");
     if (probs[i].V_kind == TDSE_V_SAMPLED) return fail(TDSE_EUNSUPPORTED, "batches take stored fields or the moving well");
     tdse_plan_s* q = nullptr;
-    const int s = tdse_plan(&probs[i], &q);
+    const int s = plan_single(&probs[i], &q, false);   // batches march every instance with the batched passes
     if (s) return s;
-    if (q->run1d || q->persist || q->levels) {   // batches march every instance with the batched passes
-      q->run1d = false;
-      q->persist = false;
-      q->levels = false;
-      q->total = q->total_core;
-    }
     p->sub.push_back(q);
     const tdse_plan_s* q0 = p->sub[0];
     if (q->order != q0->order || q->nsteps != q0->nsteps || q->ns != q0->ns || q->precision != q0->precision)
@@ -3203,7 +3224,12 @@ const char* tdse_status_string(int status) {
 
 const char* tdse_last_error(void) { return g_last_error.c_str(); }
 
-int tdse_plan(const tdse_problem_t* prob, tdse_plan_t* out) {
+int tdse_plan(const tdse_problem_t* prob, tdse_plan_t* out) { return plan_single(prob, out, true); }
+
+}  // extern "C"
+
+namespace {
+int plan_single(const tdse_problem_t* prob, tdse_plan_s** out, bool alone) {
   if (!prob || !out) return fail(TDSE_EINVAL, "NULL argument");
   *out = nullptr;
   if (prob->dim < 1 || prob->dim > 3) return fail(TDSE_EINVAL, "dim must be 1, 2 or 3");
@@ -3334,10 +3360,10 @@ int tdse_plan(const tdse_problem_t* prob, tdse_plan_t* out) {
     return TDSE_OK;
   }
 
-  for (int g = 0; g < 2; ++g) {
-    p->st[g].tw1 = twiddles(p->col_len(), p->st[g].prec == P_SPLIT);
+  for (int g = 0; g < (split ? 2 : 1); ++g) {
     p->st[g].tw2 = twiddles(p->M2, p->st[g].prec == P_SPLIT);
-    if (p->Mmid) p->st[g].tw3 = twiddles(p->Mmid, p->st[g].prec == P_SPLIT);
+    p->st[g].tw1 = p->col_len() == p->M2 ? p->st[g].tw2 : twiddles(p->col_len(), p->st[g].prec == P_SPLIT);
+    if (p->Mmid) p->st[g].tw3 = p->Mmid == p->M2 ? p->st[g].tw2 : twiddles(p->Mmid, p->st[g].prec == P_SPLIT);
   }
 
   size_t off = 0;
@@ -3377,23 +3403,25 @@ int tdse_plan(const tdse_problem_t* prob, tdse_plan_t* out) {
     p->o_dbuf = off;
     off = align256(off + cbytes);
   }
-  p->total_core = off;
-  if (p->dim == 2 && !split && p->ns > 0 && p->L > 1 && p->L <= MAXLEVELS && p->P <= LEVELS_MAX_POINTS) {
+  // what follows is for plans that march alone
+  if (alone && p->dim == 2 && !split && p->ns > 0 && p->L > 1 && p->L <= MAXLEVELS && p->P <= LEVELS_MAX_POINTS) {
     p->levels = true;
     p->lv_bytes = 2 * align256((size_t)p->P * sizeof(double2)) +
                   align256((size_t)(p->order - 1) * (p->M1 + p->M2) * sizeof(double2));
     p->o_lv = off; off = align256(off + (size_t)(p->L - 1) * p->lv_bytes);
   }
-  if (p->dim == 2 && !split && p->M1 == p->M2 && persist2d_supported(p->M2) && p->vkind == TDSE_V_FIELDS &&
+  if (alone && p->dim == 2 && !split && p->M1 == p->M2 && persist2d_supported(p->M2) && p->vkind == TDSE_V_FIELDS &&
       p->nsteps > p->ns + 1) {
     p->persist = true;
     build_persist2d(p);
+    build_persist2d_static(p);
     p->o_p2tab = off; off = align256(off + p->p2tab.size() * sizeof(double));
     p->o_p2S2 = off; off = align256(off + p->p2S2.size() * sizeof(double2));
   }
-  if (p->dim == 1 && !split && run1d_supported(p->M2) && p->vkind != TDSE_V_SAMPLED) {
+  if (alone && p->dim == 1 && !split && run1d_supported(p->M2) && p->vkind != TDSE_V_SAMPLED) {
     p->run1d = true;
     build_run1d(p);
+    build_run1d_static(p);
     p->o_r1tab = off; off = align256(off + p->r1tab.size() * sizeof(double));
     p->o_r1stab = off; off = align256(off + p->r1stab.size() * sizeof(double2));
     p->o_r1g = off; off = align256(off + (size_t)(p->order - 2) * p->M2 * sizeof(double2));
@@ -3402,6 +3430,9 @@ int tdse_plan(const tdse_problem_t* prob, tdse_plan_t* out) {
   *out = p;
   return TDSE_OK;
 }
+}  // namespace
+
+extern "C" {
 
 int tdse_workspace_size(tdse_plan_t p, size_t* bytes) {
   if (!p || !bytes) return fail(TDSE_EINVAL, "NULL argument");
