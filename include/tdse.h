@@ -238,7 +238,9 @@ int tdse_far_eval_noalloc(tdse_plan_t plan, const double* xs, int32_t nx, const 
 #define TDSE_Q_PROF_MS_PERSIST 26 /* profiling: summed ms of persistent 2D launches */
 #define TDSE_Q_PROF_N_PERSIST 27  /* profiling: number of timed persistent 2D launches */
 #define TDSE_Q_PATH           28  /* how tdse_step marches: 0 kernel passes per step, 1 one-workgroup 1D run,
-                                     2 persistent 2D launch for the Adams steps (eligible and enabled) */
+                                     2 persistent 2D launch for the Adams steps (eligible and enabled),
+                                     3 one-workgroup 1D free-space run for the Adams steps (past the Adams
+                                     start: of the run under way; profiled runs take the passes) */
 #define TDSE_Q_RESIDUAL       29  /* single periodic plans, at an Adams step before T: relative L2 difference of the
                                      history entry What_n = F(V(t_n) u_n) as the plan stores it (complex64 in the
                                      split form) from its FP64 recomputation out of u_n; measures the transform
@@ -246,6 +248,7 @@ int tdse_far_eval_noalloc(tdse_plan_t plan, const double* xs, int32_t nx, const 
                                      solve itself is a diagonal division, Section 2.1).  Synchronizes the stream;
                                      ESTATE before the Adams start or at T, EUNSUPPORTED for batches and free space */
 #define TDSE_Q_STATE_NORM     30  /* 2-norm of the state at the last guard check (TDSE_CFG_GUARD); ESTATE if none ran */
+#define TDSE_Q_LEVELS         31  /* Richardson levels of a start-up step that march side by side (1: in turn) */
 #define TDSE_Q_RICHARDSON     32  /* + l: weight of the 2^l-sub-step result    */
 #define TDSE_Q_PHI            64  /* + axis: phi_axis(T)                       */
 #define TDSE_Q_FS_H           80  /* free space: contour parameter H of axis 0 */
@@ -290,7 +293,9 @@ int tdse_configure(tdse_plan_t plan, int32_t key, int32_t value);
 /* Per-kernel timing: with enable != 0 every implicit Adams column and row
  * pass is bracketed by HIP events on the bound stream; the TDSE_Q_PROF_*
  * queries synchronize that stream and return the sums since the last call
- * with enable != 0.  enable = 0 stops recording. */
+ * with enable != 0.  enable = 0 stops recording.  The one-workgroup 1D
+ * periodic runs and the persistent 2D launches are timed whole; a profiled 1D
+ * free-space run takes the passes (TDSE_Q_PATH). */
 int tdse_profile(tdse_plan_t plan, int32_t enable);
 
 /* Whole-run graph replay: with enable != 0, tdse_run captures the complete

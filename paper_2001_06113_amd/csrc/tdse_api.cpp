@@ -3846,9 +3846,11 @@ int tdse_query(tdse_plan_t p, int32_t key, double* value) {
     return TDSE_OK;
   }
   if (key == TDSE_Q_PATH) {
-    *value = p->run1d ? 1.0 : (p->persist && p->persist_on) ? 2.0 : 0.0;
+    const bool fs1d = p->fs1d && (p->cur > p->ns ? p->fs1d_on : !p->prof);
+    *value = p->run1d ? 1.0 : (p->persist && p->persist_on) ? 2.0 : fs1d ? 3.0 : 0.0;
     return TDSE_OK;
   }
+  if (key == TDSE_Q_LEVELS) { *value = p->levels ? (double)p->L : 1.0; return TDSE_OK; }
   if (p->free_space && p->dim == 3 && key == TDSE_Q_BYTES_MID) {
     *value = 16.0 * (double)p->fx[0].N * p->fx[1].M * ((double)p->fx[2].N + p->fx[2].M);
     return TDSE_OK;
