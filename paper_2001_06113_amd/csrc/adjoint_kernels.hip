@@ -8,12 +8,10 @@
 // The reverse sweep applies the conjugate transpose of each operation; the
 // transforms and the conjugated implicit solve reuse the forward passes, and
 // these kernels do the mode-wise parts:
-//   k_adj_am     adjoint of one implicit Adams step in mode space: the
-//                adjoint beta_n of B_n, the adjoint omega_{n-1} of What_{n-1},
-//                and per-workgroup partial sums of dJ/d(dphi) of the phase
-//                factors of step n+1;
-//   k_adj_sub    the phase factor of an order-2 sub-step (forward, or adjoint
-//                with its dJ/d(dphi) partial sums);
+//   k_adj_am     the Adams phase's part of a reverse step n <= n_start: the
+//                adjoint omega_{n-1} of What_{n-1} and per-workgroup partial
+//                sums of dJ/d(dphi) of the phase factors of step n+1;
+//   k_adj_sub    the conjugated phase factor of the Adams start;
 //   k_adj_axpy, k_adj_phase, k_adj_phases, k_adj_reduce, k_adj_to_A  (helpers);
 // and fused with the line FFTs on either side of them, as in the forward
 // passes (periodic_body.h), for the many steps of the sweeps:
@@ -30,8 +28,6 @@
 namespace tdse {
 
 __device__ __forceinline__ double2 conjd(double2 z) { return double2{z.x, -z.y}; }
-// i z
-__device__ __forceinline__ double2 mul_i(double2 z) { return double2{-z.y, z.x}; }
 
 // E at (k1 index, k2 index) from entry e of the per-axis table
 __device__ __forceinline__ double2 adj_phase(const double2* ph, int per, int M1, int e, int i1, int i2) {
@@ -104,14 +100,6 @@ __global__ __launch_bounds__(256) void k_adj_am(AdjAm a) {
     const int i1 = (int)(g / a.M2), i2 = (int)(g - (int64_t)i1 * a.M2);
     const double k1 = (double)signed_mode(i1, a.M1), k2 = (double)signed_mode(i2, a.M2);
     const double2 b1 = a.slot_b1 >= 0 ? a.beta[a.slot_b1 * a.P + g] : double2{0.0, 0.0};
-    double2 bn = double2{0.0, 0.0};
-    if (a.beta_mode == 1) {
-      // beta_n = conj(E^(1)_{n+1}) beta_{n+1} + G_n^H omega_n
-      bn = cadd(cmul(conjd(adj_phase(a.ph, per, a.M1, 0, i1, i2)), b1), a.Z[g]);
-      a.beta[a.slot_bn * a.P + g] = bn;
-    } else if (a.beta_mode == 2) {
-      bn = a.beta[a.slot_bn * a.P + g];
-    }
     if (a.has_grad) {
       // step n+1: B_{n+1} = sum_j E^(j)_{n+1} x_j,
       //   x_1 = B_n - i c_1 What_n,  x_j = -i c_j What_{n+1-j};
@@ -128,14 +116,11 @@ __global__ __launch_bounds__(256) void k_adj_am(AdjAm a) {
       }
     }
     if (a.omega) {
-      // omega_{n-1} = sum_j i w_j conj(E^(j)_{n-1+j}) beta_{n-1+j}
+      // omega_{n-1} = sum_j i w_j conj(E^(j)_{n-1+j}) beta_{n-1+j}, beta_n = 0
       double2 om = double2{0.0, 0.0};
-      for (int j = 1; j <= H; ++j) {
-        if (a.wj[j] == 0.0) continue;
-        double2 b;
-        if (j == 1) b = bn;
-        else if (a.slot_bj[j] >= 0) b = a.beta[a.slot_bj[j] * a.P + g];
-        else continue;
+      for (int j = 2; j <= H; ++j) {
+        if (a.wj[j] == 0.0 || a.slot_bj[j] < 0) continue;
+        const double2 b = a.beta[a.slot_bj[j] * a.P + g];
         const double2 t = cmul(conjd(adj_phase(a.ph, per, a.M1, H + j - 1, i1, i2)), b);
         om = cadd(om, double2{-a.wj[j] * t.y, a.wj[j] * t.x});
       }
@@ -145,30 +130,12 @@ __global__ __launch_bounds__(256) void k_adj_am(AdjAm a) {
   if (a.has_grad) block_partials<2 * MAXH>(val, a.part, a.nblk);
 }
 
-// Order-2 sub-step phase, entry 0 of the table: mode 1: y = E g; mode 0:
-// partial sums of Re(conj(y) i E g) k_a, then y = conj(E) y; mode 2:
-// y = conj(E) y only.
+// y = conj(E) y with the phase factor of entry 0 of the table
 __global__ __launch_bounds__(256) void k_adj_sub(AdjSub a) {
   const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int per = a.M1 + a.M2;
-  double val[2] = {0.0, 0.0};
-  if (g < a.P) {
-    const int i1 = (int)(g / a.M2), i2 = (int)(g - (int64_t)i1 * a.M2);
-    const double2 E = adj_phase(a.ph, per, a.M1, 0, i1, i2);
-    if (a.mode == 1) {
-      a.y[g] = cmul(E, a.g[g]);
-    } else {
-      const double2 y = a.y[g];
-      if (a.mode == 0) {
-        const double2 Ex = cmul(E, a.g[g]);
-        const double term = -(y.x * Ex.y - y.y * Ex.x);    // Re(conj(y) i E g)
-        val[0] = (double)signed_mode(i1, a.M1) * term;
-        val[1] = (double)signed_mode(i2, a.M2) * term;
-      }
-      a.y[g] = cmul(conjd(E), y);
-    }
-  }
-  if (a.mode == 0) block_partials<2>(val, a.part, a.nblk);
+  if (g >= a.P) return;
+  const int i1 = (int)(g / a.M2), i2 = (int)(g - (int64_t)i1 * a.M2);
+  a.y[g] = cmul(conjd(adj_phase(a.ph, a.M1 + a.M2, a.M1, 0, i1, i2)), a.y[g]);
 }
 
 // out = x + c y (complex c)
@@ -236,7 +203,7 @@ constexpr int adj_row_lds() {
 // A row pass moves 18 entries of 16 bytes per mode (tile in and out, seven
 // adjoint states and a new one, seven history entries, B_n) and is bound by
 // that traffic on large grids, by latency on small ones.  PF: everything is
-// loaded before the forward FFT, 15 entries per element in registers, which
+// loaded before the forward FFT, 16 entries per element in registers, which
 // leaves one wave per SIMD; else term by term after it (four waves).
 template <int N, int L, int TL, bool PF>
 __global__ __launch_bounds__(L * TL) void k_adj_row_am(AdjRowAm a) {
@@ -445,7 +412,7 @@ __global__ __launch_bounds__(LPW * TL) void k_adj_col(AdjCol a) {
   for (int m = 0; m < EPT; ++m) {
     const double q = a.di * Vs[m], iv = a.s / (1.0 + q * q);
     // s (a + b V) / (1 + i q) = s (a + b V) (1 - i q) / (1 + q^2)
-    const double2 f = cmul(double2{a.ar + a.br * Vs[m], a.ai + a.bi * Vs[m]}, double2{iv, -q * iv});
+    const double2 f = cmul(double2{a.ar + a.br * Vs[m], a.bi * Vs[m]}, double2{iv, -q * iv});
     v[m] = cmul(f, v[m]);
     if (a.yout && active) {
       double2 y = v[m];
@@ -511,7 +478,12 @@ hipError_t launch_adj_row_am(const AdjRowAm& a, hipStream_t s) {
 hipError_t launch_adj_row_sub(const AdjRowSub& a, hipStream_t s) {
   const dim3 grid((unsigned)adj_row_blocks(a.M1, a.M2));
   switch (a.M2) {
-#define X(n)   case n: hipLaunchKernelGGL((k_adj_row_sub<n, row_lpw(n), row_tl(n)>), grid, dim3(row_lpw(n) * row_tl(n)), 0, s, a); break;
+#define X(n)                                                                                             \
+  case n: {                                                                                              \
+    constexpr int L = row_lpw(n), T = row_tl(n);                                                         \
+    hipLaunchKernelGGL((k_adj_row_sub<n, L, T>), grid, dim3(L * T), 0, s, a);                            \
+    break;                                                                                               \
+  }
     TDSE_LINE_SIZES(X)
 #undef X
     default:
@@ -521,7 +493,12 @@ hipError_t launch_adj_row_sub(const AdjRowSub& a, hipStream_t s) {
 }
 hipError_t launch_adj_col(const AdjCol& a, hipStream_t s) {
   switch (a.M1) {
-#define X(n)                                                                                                         case n:                                                                                                              hipLaunchKernelGGL((k_adj_col<n, col_lpw(n), col_tl(n)>), dim3((unsigned)((a.M2 + col_lpw(n) - 1) / col_lpw(n))),                        dim3(col_lpw(n) * col_tl(n)), 0, s, a);                                                         break;
+#define X(n)                                                                                             \
+  case n: {                                                                                              \
+    constexpr int L = col_lpw(n), T = col_tl(n);                                                         \
+    hipLaunchKernelGGL((k_adj_col<n, L, T>), dim3((unsigned)((a.M2 + L - 1) / L)), dim3(L * T), 0, s, a); \
+    break;                                                                                               \
+  }
     X(1)
     TDSE_LINE_SIZES(X)
 #undef X
@@ -531,7 +508,7 @@ hipError_t launch_adj_col(const AdjCol& a, hipStream_t s) {
   return hipGetLastError();
 }
 hipError_t launch_adj_sub(const AdjSub& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_adj_sub, dim3(a.nblk), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(k_adj_sub, dim3(nb(a.P)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 hipError_t launch_adj_axpy(int64_t P, const double2* x, const double2* y, double cr, double ci, double2* out,

@@ -2651,7 +2651,7 @@ struct AdjLayout {
   int K = 1, C = 0, H = 1, nblk = 1, L = 1, nsub_max = 1;
   int64_t P = 1, rows = 0;
   size_t o_ustore = 0, o_ck = 0, o_bseg = 0, o_wwin = 0, o_beta = 0, o_omega = 0, o_omsu = 0, o_Z = 0;
-  size_t o_phys[3] = {0, 0, 0}, o_modes[2] = {0, 0}, o_bvirt = 0, o_subg = 0, o_ph = 0, o_plist = 0, o_ptab = 0;
+  size_t o_phys[3] = {0, 0, 0}, o_modes = 0, o_bvirt = 0, o_subg = 0, o_ph = 0, o_plist = 0, o_ptab = 0;
   int64_t entries = 0;   // phase entries of the fused passes: Adams steps, then start-up sub-steps
   int chunk = 1;         // reverse steps whose phase table is built at once
   size_t o_part = 0, o_red = 0, o_csr = 0, o_gA = 0, csr_bytes = 0, total = 0;
@@ -2680,7 +2680,7 @@ AdjLayout adj_layout(const tdse_plan_s* p, int K) {
     return o;
   };
   L.o_ustore = take((size_t)(ns + 1) * a);
-  L.o_ck = take((size_t)L.C * L.ck_bytes);
+  L.o_ck = take((size_t)std::max(L.C - 1, 0) * L.ck_bytes);   // none for the newest segment
   L.o_bseg = take((size_t)K * a);
   L.o_wwin = take((size_t)(K + L.H) * a);
   L.o_beta = take(8 * a);
@@ -2688,7 +2688,7 @@ AdjLayout adj_layout(const tdse_plan_s* p, int K) {
   L.o_omsu = take((size_t)L.H * a);
   L.o_Z = take(a);
   for (int i = 0; i < 3; ++i) L.o_phys[i] = take(a);
-  for (int i = 0; i < 2; ++i) L.o_modes[i] = take(a);
+  L.o_modes = take(a);
   L.o_bvirt = take(a);
   L.o_subg = take((size_t)L.nsub_max * a);
   L.o_ph = take((size_t)ADJ_PH * (p->M1 + p->M2) * sizeof(double2));
@@ -2874,9 +2874,8 @@ int adjoint_single(tdse_plan_s* p, char* w, size_t wbytes, int K, const void* u0
   };
   AdjPh PH(p, R.at(L.o_ph));
   const double2* Bvirt = R.at(L.o_bvirt);
-  // one adjoint Adams iteration at n: beta_n, the partials of step n+1, omega_{n-1}
-  auto am_iter = [&](int n, int beta_mode, bool grad, const double2* Bn, const double2* const* Wx,
-                     double2* omega_out) -> int {
+  // the Adams phase's part of reverse step n <= ns: the partials of step n+1, omega_{n-1}
+  auto am_iter = [&](int n, bool grad, const double2* Bn, const double2* const* Wx, double2* omega_out) -> int {
     PH.q.nj = 0;
     for (int j = 1; j <= H; ++j) {
       PH.set(p, j - 1, (n + 1) * dt, j * dt);
@@ -2893,9 +2892,6 @@ int adjoint_single(tdse_plan_s* p, char* w, size_t wbytes, int K, const void* u0
     A.ph = PH.q.ph;
     A.beta = beta;
     A.slot_b1 = bslot(n + 1);
-    A.slot_bn = n % 8;
-    A.beta_mode = beta_mode;
-    A.Z = R.at(L.o_Z);
     A.omega = omega_out;
     for (int j = 2; j <= H; ++j) A.slot_bj[j] = bslot(n - 1 + j);
     for (int j = 1; j <= H; ++j) A.wj[j] = (n - 1 + j >= ns + 1 && n - 1 + j <= N && n - 1 >= 0) ? dt * cfac(n - 1, j) : 0.0;
@@ -3060,15 +3056,15 @@ int adjoint_single(tdse_plan_s* p, char* w, size_t wbytes, int K, const void* u0
     // step ns+1 formed B from F u_ns: B_virt = F u_ns + i mu_0 dt What_ns gives x_1
     {
       const int w0 = ns + 1 - H;
-      s = adj_fft2(p, R.at(L.o_ustore, ns), R.at(L.o_modes[0]), invP, 1.0, 0.0, 0.0, 0.0, ns * dt);
-      if (!s) s = adj_err(launch_adj_axpy(p->P, R.at(L.o_modes[0]), R.at(L.o_wwin, ns - w0), 0.0, mu[0] * dt,
+      s = adj_fft2(p, R.at(L.o_ustore, ns), R.at(L.o_modes), invP, 1.0, 0.0, 0.0, 0.0, ns * dt);
+      if (!s) s = adj_err(launch_adj_axpy(p->P, R.at(L.o_modes), R.at(L.o_wwin, ns - w0), 0.0, mu[0] * dt,
                                           R.at(L.o_bvirt), st), "adjoint axpy");
       const double2* Wx[MAXH + 1] = {nullptr};
       for (int j = 1; j <= H; ++j) Wx[j] = R.at(L.o_wwin, (j == 1 ? ns : ns + 1 - j) - w0);
-      if (!s) s = am_iter(ns, 0, true, Bvirt, Wx, ns >= 1 ? R.at(L.o_omega) : nullptr);
+      if (!s) s = am_iter(ns, true, Bvirt, Wx, ns >= 1 ? R.at(L.o_omega) : nullptr);
       if (!s && ns >= 1 && ns - 1 >= ns + 1 - H) s = adj_copy(p, omsu(ns - 1), R.at(L.o_omega), a);
       for (int n = ns - 1; n >= std::max(1, ns + 2 - H) && !s; --n) {
-        s = am_iter(n, 0, false, nullptr, nullptr, R.at(L.o_omega));
+        s = am_iter(n, false, nullptr, nullptr, R.at(L.o_omega));
         if (!s) s = adj_copy(p, omsu(n - 1), R.at(L.o_omega), a);
       }
     }
@@ -3077,15 +3073,14 @@ int adjoint_single(tdse_plan_s* p, char* w, size_t wbytes, int K, const void* u0
     PH.q.nj = 0;
     PH.set(p, 0, (ns + 1) * dt, dt);
     s = adj_err(launch_adj_phase(PH.q, st), "adjoint phases");
-    if (!s) s = adj_copy(p, R.at(L.o_modes[0]), beta + (int64_t)((ns + 1) % 8) * p->P, a);
+    if (!s) s = adj_copy(p, R.at(L.o_modes), beta + (int64_t)((ns + 1) % 8) * p->P, a);
     if (!s) {
       AdjSub S;
       std::memset(&S, 0, sizeof(S));
-      S.M1 = p->M1; S.M2 = p->M2; S.mode = 2; S.P = p->P; S.ph = PH.q.ph; S.y = R.at(L.o_modes[0]);
-      S.nblk = L.nblk;
+      S.M1 = p->M1; S.M2 = p->M2; S.P = p->P; S.ph = PH.q.ph; S.y = R.at(L.o_modes);
       s = adj_err(launch_adj_sub(S, st), "adjoint phase");
     }
-    if (!s) s = row_inverse(R.at(L.o_modes[0]));
+    if (!s) s = row_inverse(R.at(L.o_modes));
     if (!s) s = col_op(nullptr, R.at(L.o_phys[1]), false, false, ns * dt, 1.0, 0.0, 0.0, 0.0, invP);
     if (!s) s = row_inverse(omsu(ns));
     if (!s) s = col_op(nullptr, R.at(L.o_phys[1]), true, false, ns * dt, 0.0, 1.0, 0.0, 0.0, invP);

@@ -200,15 +200,12 @@ struct AdjPhase {                  // per-axis table ph[e (M1+M2) + k], e < nj
   double tau[ADJ_PH], dphi1[ADJ_PH], dphi2[ADJ_PH];
   double2* ph;
 };
-struct AdjAm {                     // one adjoint implicit Adams step (mode space, P modes)
+struct AdjAm {                     // reverse step n <= ns of the Adams phase, where beta_n = 0 (mode space, P modes)
   int M1, M2, H;
   int64_t P;
   const double2* ph;               // entries j-1: E^(j)_{n+1}; H+j-1: E^(j)_{n-1+j}
   double2* beta;                   // ring of adjoint states, slots of P modes
   int slot_b1;                     // beta_{n+1} (-1: zero)
-  int slot_bn;                     // beta_n
-  int beta_mode;                   // 0: beta_n = 0; 1: beta_n = conj(E^(1)_{n+1}) beta_{n+1} + Z; 2: read
-  const double2* Z;                // G_n^H omega_n
   double2* omega;                  // out: omega_{n-1} (null: none)
   int slot_bj[MAXH + 1];           // beta_{n-1+j}, j >= 2 (-1: zero)
   double wj[MAXH + 1];             // omega weights dt c_{n-1,j}
@@ -219,14 +216,11 @@ struct AdjAm {                     // one adjoint implicit Adams step (mode spac
   double* part;                    // partial sums [2 (j-1) + axis][nblk]
   int nblk;
 };
-struct AdjSub {                    // phase factor of an order-2 sub-step (entry 0 of ph)
-  int M1, M2, mode;                // 1: y = E g; 0: partials and y = conj(E) y; 2: y = conj(E) y
+struct AdjSub {                    // y = conj(E) y, E from entry 0 of ph
+  int M1, M2;
   int64_t P;
   const double2* ph;
   double2* y;
-  const double2* g;
-  double* part;                    // partial sums [axis][nblk]
-  int nblk;
 };
 // Fused row pass of the reverse sweep (entries as for AdjAm): forward FFT of
 // a tile row (Z), beta_n = conj(E^(1)_{n+1}) beta_{n+1} + Z, the partials of
@@ -264,7 +258,7 @@ struct AdjRowSub {
   int nblk;
 };
 // Fused column pass: x from the tile (inverse FFT along axis 0) or from the
-// grid array xin, y = s x (ar + i ai + (br + i bi) V) / (1 + i di V), y into (or
+// grid array xin, y = s x (ar + (br + i bi) V) / (1 + i di V), y into (or
 // added to) the grid array yout, and the forward FFT of y into the tile.
 struct AdjCol {
   int M1, M2;
@@ -278,7 +272,7 @@ struct AdjCol {
   int nV;
   int64_t vstride;
   double fV[MAXV];
-  double ar, ai, br, bi, di, s;
+  double ar, br, bi, di, s;
 };
 hipError_t launch_adj_phase(const AdjPhase& q, hipStream_t s);
 hipError_t launch_adj_am(const AdjAm& a, hipStream_t s);
