@@ -428,6 +428,16 @@ __global__ __launch_bounds__(LPW * TL) void k_adj_col(AdjCol a) {
   }
 }
 
+// Row schedules of the fused passes: those of the forward passes, but six
+// elements per thread at 1536 and 3072.  A thread holds three arrays of its
+// elements here; with twelve, lines of these lengths were slower than the
+// unfused passes where there are few (adjoints of 100 steps, ms, unfused / twelve /
+// six: 1536 points 15.3 / 16.6 / 13.3, 3072 17.5 / 18.5 / 17.1, 8 x 1536 17.4 / 17.9 /
+// 14.6, 512 x 1536 35.3 / 31.3 / 27.0, 1536^2 112 / 98.6 / 85.0).
+constexpr int adj_ept(int N) { return N == 1536 || N == 3072 ? 6 : row_ept(N); }
+constexpr int adj_tl(int N) { return N / adj_ept(N); }
+constexpr int adj_lpw(int N) { return N == 1536 || N == 3072 ? 1 : row_lpw(N); }
+
 static int nb(int64_t n) { return (int)((n + 255) / 256); }
 
 hipError_t launch_adj_phase(const AdjPhase& q, hipStream_t s) {
@@ -445,7 +455,7 @@ hipError_t launch_adj_phases(const AdjPhases& q, hipStream_t s) {
 }
 int adj_row_blocks(int M1, int M2) {
   switch (M2) {
-#define X(n) case n: return (M1 + row_lpw(n) - 1) / row_lpw(n);
+#define X(n) case n: return (M1 + adj_lpw(n) - 1) / adj_lpw(n);
     TDSE_LINE_SIZES(X)
 #undef X
     default:
@@ -462,10 +472,10 @@ hipError_t launch_adj_row_am(const AdjRowAm& a, hipStream_t s) {
   switch (a.M2) {
 #define X(n)                                                                                              \
   case n: {                                                                                               \
-    constexpr bool PF = row_ept(n) <= 4;                                                                  \
-    const dim3 block(row_lpw(n) * row_tl(n));                                                             \
-    if (PF && few) hipLaunchKernelGGL((k_adj_row_am<n, row_lpw(n), row_tl(n), PF>), grid, block, 0, s, a); \
-    else hipLaunchKernelGGL((k_adj_row_am<n, row_lpw(n), row_tl(n), false>), grid, block, 0, s, a);        \
+    constexpr bool PF = adj_ept(n) <= 4;                                                                  \
+    const dim3 block(adj_lpw(n) * adj_tl(n));                                                             \
+    if (PF && few) hipLaunchKernelGGL((k_adj_row_am<n, adj_lpw(n), adj_tl(n), PF>), grid, block, 0, s, a); \
+    else hipLaunchKernelGGL((k_adj_row_am<n, adj_lpw(n), adj_tl(n), false>), grid, block, 0, s, a);        \
     break;                                                                                                \
   }
     TDSE_LINE_SIZES(X)
@@ -480,7 +490,7 @@ hipError_t launch_adj_row_sub(const AdjRowSub& a, hipStream_t s) {
   switch (a.M2) {
 #define X(n)                                                                                             \
   case n: {                                                                                              \
-    constexpr int L = row_lpw(n), T = row_tl(n);                                                         \
+    constexpr int L = adj_lpw(n), T = adj_tl(n);                                                         \
     hipLaunchKernelGGL((k_adj_row_sub<n, L, T>), grid, dim3(L * T), 0, s, a);                            \
     break;                                                                                               \
   }
