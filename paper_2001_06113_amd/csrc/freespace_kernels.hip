@@ -1136,8 +1136,11 @@ __global__ __launch_bounds__(256) void k_fs_phase(FSArgs a) { build_phase_table_
 // thread (a line has nu / 256 waves): four slots then, twice the threads.
 // Column and row pass of 100 columns and 270 rows at nu = 256: 14.2 and 17.6 ->
 // 11.0 and 14.3 us; 1024 columns at nu = 256: 19.4 -> 17.1 us; the 256 columns
-// of nu = 2048, two waves per SIMD already, would go from 24.0 to 27.0 us.
-inline bool fs_few(int nu, int64_t lines, int M) { return lines * nu <= (int64_t)FS_FEW_WAVES * 256 && M <= nu / 2; }
+// of nu = 2048, two waves per SIMD already, would go from 24.0 to 27.0 us.  Not
+// at nu = 2048, where a line would have 1024 threads: steps of one 100-point
+// line with eight / four slots 25.2 / 31.0 us, of 16 columns of 200 points 42.5 /
+// 47.1, of 120 of 100 points 57.7 / 61.8.
+inline bool fs_few(int nu, int64_t lines, int M) { return nu <= 1024 && lines * nu <= (int64_t)FS_FEW_WAVES * 256 && M <= nu / 2; }
 
 bool fs_nu_supported(int nu) {
   switch (nu) {

@@ -1648,9 +1648,10 @@ int upload_fs1d(tdse_plan_s* p) {
 // run takes this path; below, it is taken to be cut into as small pieces, and
 // the launch's start and end are most of its time.  M = 256, nu = 2048 (512
 // threads that spill), two launches per step / this path, us per step in pieces
-// of 1: 47 / 62, 2: 34 / 40, 4: 29 / 30, 8: 27 / 24; nu <= 1024 gains from 1 on
-// (48 / 43 at M = 100, nu = 1024).
-int fs1d_min_piece(int nu) { return nu >= 2048 ? 4 : 1; }
+// of 1: 48.7 / 65.4, 2: 35.2 / 42.1, 4: 30.8 / 30.6, 8: 28.6 / 24.6, 64: 25.7 / 18.7
+// (600 points: 36.4 / 38.2 in pieces of 4, 34.0 / 32.6 of 8); nu <= 1024 gains from 1
+// on (48.3 / 43.4 at M = 100, nu = 1024).
+int fs1d_min_piece(int nu) { return nu >= 2048 ? 8 : 1; }
 
 // Adams steps cur+1 .. end (cur >= ns), FSRUN1D_STEPS per launch
 int fs1d_steps(tdse_plan_s* p, int end) {
