@@ -511,7 +511,8 @@ __device__ __forceinline__ void row_body(const LineArgs& a, int line0, C* lds) {
       acc = cadd(acc, hist);
       const int64_t g = row0 + (t + TL * m);
       if (a.slot_w >= 0) ((C*)a.ring)[a.slot_w * rstride + g] = W;
-      ((double2*)a.fdst)[g] = acc;
+      if constexpr (sizeof(C) == sizeof(double2)) ((double2*)a.fdst)[g] = acc;
+      else a.Bm[g] = acc;   // (no adjoint: one pointer less)
       v[m] = from_d<C>(acc);
     }
   } else if (mode == R_INIT) {
