@@ -170,12 +170,29 @@ hipError_t mid_pass(int N, bool inverse, const LineArgs& a, hipStream_t s, hipEv
   return hipGetLastError();
 }
 
+// ... and rows with phase factors of their own along the line (no powers) where
+// there are so many that the registers of seven terms and their factors, one
+// wave per SIMD, cost more than the two layouts gain.  us per row pass, two
+// layouts less one, in sub-steps (at most one term): 2048 x 384 +2.5, 4096 x 384
+// +6.2, 1024 x 768 +1.2, 4096 x 768 +9.8, 16384 x 96 +5.4, 8192 x 192 +4.4; 1024 x 384
+// -0.2, 512 x 768 -1.2, 8192 x 96 -0.5, 4096 x 192 -0.7.  Adams steps with a field along
+// the rows, two layouts / one: 1536 x 768 42.1 / 34.8, 2048 x 384 29.6 / 26.3, 4096 x
+// 384 50.1 / 49.4 (one wave per line fills two per SIMD with 2048 lines); 3072 x 384
+// 40.0 / 43.3, 512 x 768 18.3 / 22.4, 4096 x 768 109 / 119, 16384 x 96 46.9 / 47.4.
+inline bool tri_row(int N, const LineArgs& a) {
+  if (a.pf_pow || N < 48) return true;
+  const int64_t P = (int64_t)a.nlines * N;
+  if (P < (N >= 384 ? 3 << 18 : 3 << 19)) return true;
+  if (a.nh <= 1) return false;
+  return N < 384 || P > 1 << 21 || (N == 384 && a.nlines % 2048 != 0);
+}
+
 template <typename C>
 hipError_t row_pass(int N, const LineArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   switch (N) {
 #define X(n) \
   case n: { \
-    if (sizeof(C) == sizeof(double2) && three_smooth(n) && !a.ph32) { \
+    if (sizeof(C) == sizeof(double2) && three_smooth(n) && !a.ph32 && tri_row(n, a)) { \
       constexpr int NN = three_smooth(n) ? n : 24, L = tri_row_lpw(NN); \
       const dim3 g((a.nlines + L - 1) / L), b(L * tri_tl(NN)); \
       if (a.pf_pow) TDSE_LAUNCH((k_tri_row<NN, L, true>), g, b, s, e0, e1, a); \
