@@ -276,10 +276,12 @@ int tdse_query(tdse_plan_t plan, int32_t key, double* value);
  * exchange the tile between the two transform directions of each step), falling
  * back to two kernel passes per step when the device cannot hold the grid;
  * 0 always takes the passes.  Not while a run is under way (ESTATE).  The
- * launch is asynchronous.  An exchange that times out leaves u(t) not finite,
- * and the next tdse_step or tdse_get_state that finds the launch's report
- * (a copy to the host or a guard check, which wait, always do) returns
- * TDSE_EDEVICE; tdse_set_state must come next. */
+ * launch is asynchronous like every step; tdse_run of such a plan, and the
+ * tdse_set_state that follows its steps, wait for it.  An exchange that times
+ * out leaves u(t) not finite: tdse_run returns TDSE_EDEVICE, and so does the
+ * next tdse_step or tdse_get_state that finds the launch's report (a copy to
+ * the host or a guard check, which wait, always do); tdse_set_state must come
+ * next. */
 #define TDSE_CFG_PERSISTENT 0
 /* TDSE_CFG_GUARD (default 0, off): with value K >= 1, tdse_step marches in
  * pieces of at most K steps and after each piece, and tdse_run after the

@@ -43,6 +43,8 @@ def test_a_timed_out_run_is_reported_and_not_continued(emu, spin_limit, M):
     assert emu.tdse_step(plan.h, 1) == ESTATE
     assert emu.tdse_get_state(plan.h, C.c_void_p(out.ctypes.data), 1) == ESTATE
     assert np.array_equal(plan.run(prob.u0), ref)
+    spin_limit.value = 0
+    assert emu.tdse_run(plan.h, C.c_void_p(np.asarray(prob.u0).ctypes.data), C.c_void_p(out.ctypes.data), 1) == EDEVICE
 
 
 @pytest.mark.parametrize("M", [32, 48])
@@ -54,3 +56,9 @@ def test_steps_do_not_wait_for_the_stream(emu, M):
     for k in (2, 5, 1, 4):
         plan.step(k)
     assert waits.value == before
+    plan.set_state(prob.u0)            # the next run waits for the last one's launch
+    assert waits.value == before + 1
+    plan.run(prob.u0)                  # (no launch under way) and a run for its own
+    assert waits.value == before + 2
+    plan.set_state(prob.u0)
+    assert waits.value == before + 2
