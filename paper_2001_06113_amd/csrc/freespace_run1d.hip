@@ -324,10 +324,10 @@ __global__ __launch_bounds__(NU / 4) void k_fs_run1d(FSRun1DArgs a) {
 constexpr size_t FSR_LDS = 160 * 1024;
 
 // Eligible lines: every dense mode on a thread of its own, every grid point in
-// the rays' lines, and the LDS of one compute unit.  Faster than the passes
-// wherever it applies (600-step runs, us per step): M = 64, nu = 256 18.2 ->
-// 11.4; 100, 1024 22.4 -> 10.8; 128, 1024 through the interpolant 28.2 -> 17.4;
-// 256, 2048 33.0 -> 25.4 (512 threads: 160 of their registers spill).
+// the rays' lines, and the LDS of one compute unit.  us per Adams step over 600
+// steps, the passes / this kernel: M = 64, nu = 256 16.7 / 8.7; 100, 1024 20.2 /
+// 7.8; 128, 1024 through the interpolant 22.1 / 10.2; 256, 2048 22.9 / 17.7 (512
+// threads: 160 of their registers spill).
 bool fs_run1d_supported(int nu, const CFAxis& ax) {
   return ax.ND <= nu / 4 && ax.NR <= nu / 4 && ax.M <= nu && fs_run1d_lds_bytes(nu, ax, false) <= FSR_LDS;
 }

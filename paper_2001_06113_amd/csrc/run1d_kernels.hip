@@ -322,10 +322,10 @@ __global__ __launch_bounds__(run1d_threads(N)) void k_run1d(Run1DArgs a) {
 }
 
 // Lengths 2^a up to 2048 and 3 * 2^a up to 1536: at most 512 threads, so that a
-// thread has at least 256 registers for its modes and history.  us per step of
-// 400-step runs with a pulse, two launches per step / this kernel: N = 192
-// 33.2 / 3.1, 384 22.4 / 3.7, 768 25.2 / 4.6, 1024 14.2 / 5.6, 1536 37.6 / 9.2,
-// 2048 31.5 / 12.4.
+// thread has at least 256 registers for its modes and history.  us per step in
+// pieces of 64 Adams steps with a pulse, two launches per step / this kernel:
+// N = 192 31.9 / 3.0, 384 20.2 / 3.6, 768 23.9 / 4.3, 1024 14.1 / 5.2, 1536 36.7 /
+// 8.3, 2048 28.2 / 10.6.
 #define TDSE_RUN1D_SIZES(X) \
   X(8) X(16) X(32) X(64) X(128) X(256) X(512) X(1024) X(2048) X(24) X(48) X(96) X(192) X(384) X(768) X(1536)
 

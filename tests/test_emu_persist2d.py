@@ -1,6 +1,6 @@
 """CPU run of the persistent 2D Adams steps (persist2d_kernels.hip: one
-co-resident grid, grid barriers between the transform directions, the
-multistep state on chip) through the emulation harness, whose cooperative
+co-resident grid, the tile exchanged as marked data between the transform
+directions, the multistep state on chip) through the emulation harness, whose cooperative
 launches run every workgroup's threads as fibers of one scheduler: against
 the oracle, against the two-pass path, and in pieces."""
 import numpy as np

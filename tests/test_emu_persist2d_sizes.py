@@ -1,5 +1,5 @@
-"""CPU run of the persistent 2D Adams steps at lengths 3 * 2^a (six elements
-per thread) through the emulation harness: against the oracle and the
+"""CPU run of the persistent 2D Adams steps at lengths 3 * 2^a (four and three
+elements per thread in the two layouts) through the emulation harness: against the oracle and the
 two-pass path, with and without a field along axis 1."""
 import numpy as np
 import pytest

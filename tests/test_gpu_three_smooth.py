@@ -1,7 +1,7 @@
 """GPU parity of the FP64 passes over lengths 3 * 2^a (24..768 points: rows,
 columns and the middle axis) against the oracle: ragged sets of lines, two
-potential fields, a field along every axis, low orders, and the passes of the
-adjoint that share them."""
+potential fields, a field along every axis, low orders.  (The adjoint has row
+passes of its own; its recomputation takes these.)"""
 import os
 
 import numpy as np
