@@ -3489,7 +3489,9 @@ int tdse_bind(tdse_plan_t p, void* ws, size_t bytes, void* stream) {
   }
   if (p->persist) {
     if (!p->p2_word) p->p2_word = timeout_words().take();
-    if (!p->p2_word) return fail(TDSE_ENOMEM, "no pinned host memory");
+    if (!p->p2_word) p->persist = false;   // no pinned memory: the passes
+  }
+  if (p->persist) {
     const int s = upload_persist2d(p);
     if (s) return s;
   }
@@ -3521,7 +3523,8 @@ int tdse_set_state(tdse_plan_t p, const void* u0, int32_t on_device) {
     p->cur = 0;
     return TDSE_OK;
   }
-  if (!capturing(p->stream)) (void)persist2d_wait(p);   // a timeout of the run that ends here is nobody's any more
+  if (p->p2_pending && !capturing(p->stream)) (void)persist2d_wait(p);   // (a timeout of the run that ends here is nobody's)
+  p->p2_pending = false;
   p->ucur = 0;
   p->uh_cur = 0;
   p->p2_run = 0;

@@ -41,3 +41,31 @@ def test_steps_are_asynchronous(M):
     ref = PeriodicOracle(prob).run()[0]
     assert np.linalg.norm(out - ref) <= 1e-11 * np.linalg.norm(ref)
     assert np.array_equal(out, first)
+
+
+def test_a_run_captured_while_steps_are_under_way():
+    """The captured run takes the passes and does not wait for the launch."""
+    import torch
+
+    from paper_2001_06113_amd.tdse import CFG_PERSISTENT, Plan
+
+    print("case capture behind persistent steps 96^2", flush=True)
+    prob = periodic_problem_from_seed(135, 2, (96, 96), 0.02, 16, order=8)
+    plan = Plan.from_problem(prob, device="cuda:0")
+    u0 = torch.as_tensor(prob.u0).to("cuda:0", torch.complex128)
+    ref = plan.run(u0).clone()
+    plan.set_state(u0)
+    plan.step(16)
+    side = torch.cuda.Stream()
+    g = torch.cuda.CUDAGraph()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(g, stream=side):
+        out = plan.run(u0)
+    for _ in range(3):
+        out.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert (torch.linalg.vector_norm(out - ref) / torch.linalg.vector_norm(ref)).item() <= 1e-13
+    plan.configure(CFG_PERSISTENT, 0)
+    assert torch.equal(plan.run(u0), out)
+    plan.close()
