@@ -6,4 +6,4 @@ thread_local dim3 blockDim, gridDim;
 thread_local emu::Block* emu::g_block = nullptr;
 thread_local emu::CoopRun* emu::g_coop = nullptr;
 thread_local emu_graph* emu_capture = nullptr;
-int emu_coop_blocks = 1, emu_spin_limit = 1000000, emu_stream_waits = 0, emu_event_waits = 0, emu_launches = 0;
+int emu_coop_blocks = 1, emu_spin_limit = 1000000, emu_stream_waits = 0, emu_event_waits = 0, emu_launches = 0, emu_trig = 0;

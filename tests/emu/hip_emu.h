@@ -86,6 +86,14 @@ extern "C" int emu_coop_blocks;
 // stream, of a stream's waits for an event and of kernel launches
 extern "C" int emu_spin_limit, emu_stream_waits, emu_event_waits, emu_launches;
 #define TDSE_P2_SPIN_LIMIT emu_spin_limit
+// and of the extended-precision sines and cosines of the host's tables
+extern "C" int emu_trig;
+inline long double emu_cosl(long double x) { ++emu_trig; return cosl(x); }
+inline long double emu_sinl(long double x) { ++emu_trig; return sinl(x); }
+inline void emu_sincosl(long double x, long double* s, long double* c) { ++emu_trig; sincosl(x, s, c); }
+#define cosl emu_cosl
+#define sinl emu_sinl
+#define sincosl emu_sincosl
 
 namespace emu {
 // Cooperative fibers: every emulated thread of a block runs on one OS thread

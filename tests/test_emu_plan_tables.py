@@ -1,8 +1,7 @@
-"""Host tables of the one-launch paths: what planning them costs beside a plan
-that does not have them (the split form of the same grid), and the static phase
-factors against the exact phases of a run without a potential."""
+"""Host tables of the one-launch paths: the extended-precision evaluations that
+planning them takes, and the static phase factors against the exact phases of a
+run without a potential."""
 import ctypes as C
-import time
 
 import numpy as np
 import pytest
@@ -10,26 +9,31 @@ import pytest
 from workloads import periodic_problem_from_seed
 
 
-def _plan_ms(lib, prob):
-    from paper_2001_06113_amd.tdse import problem_kwargs, problem_struct
-
-    struct, keep = problem_struct(**problem_kwargs(prob))
-    best = float("inf")
-    for _ in range(40):
-        h = C.c_void_p()
-        t0 = time.perf_counter()
-        assert lib.tdse_plan(C.byref(struct), C.byref(h)) == 0
-        best = min(best, time.perf_counter() - t0)
-        lib.tdse_destroy(h)
-    return 1e3 * best
+def _evaluations(emu, call):
+    n = C.c_int.in_dll(emu, "emu_trig")
+    before = n.value
+    call()
+    return n.value - before
 
 
-@pytest.mark.parametrize("M, factor", [((768,), 1.6), ((2048,), 1.6), ((384, 384), 2.0)])
-def test_planning_time(emu, M, factor):
-    probs = [periodic_problem_from_seed(170, len(M), M, 0.02, 100, precision=p) for p in ("fp64", "fp32split")]
-    one, plain = (_plan_ms(emu, p) for p in probs)
-    print(f"plan {M}: {one:.3f} ms, without the tables {plain:.3f} ms")
-    assert one <= factor * plain
+@pytest.mark.parametrize("M", [(96,), (768,), (2048,), (48, 48), (384, 384), (64, 192)])
+def test_table_evaluations(emu, M):
+    """A sine and a cosine per entry of each different twiddle table, one pair per
+    non-negative k for the static phases; none of those for a batch's
+    instances, and none at all for a new field."""
+    from emu.emu_plan import EmuBatchPlan, EmuPlan
+
+    prob = periodic_problem_from_seed(170, len(M), M, 0.02, 20, order=8, A_kind="stepwise")
+    prob.A_steps = np.zeros((20, len(M)))
+    plans = []
+    twiddles = sum(2 * n for n in set(M if len(M) == 2 else (1,) + M))
+    n = _evaluations(emu, lambda: plans.append(EmuPlan(emu, prob)))
+    one_launch = plans[0].query(28) > 0
+    assert one_launch == (len(M) == 1 or M[0] == M[1])
+    assert n == twiddles + (M[-1] // 2 + 1 if one_launch else 0)
+    assert _evaluations(emu, lambda: plans[0].call("tdse_set_field", prob.A_steps.ctypes.data_as(C.POINTER(C.c_double)))) == 0
+    if min(M) >= 64 and all(m % 3 or m >= 192 for m in M):
+        assert _evaluations(emu, lambda: EmuBatchPlan(emu, [prob])) == twiddles
 
 
 @pytest.mark.parametrize("M, order", [((2048,), 8), ((768,), 4), ((48, 48), 8), ((64, 64), 6)])
