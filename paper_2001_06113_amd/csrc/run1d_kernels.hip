@@ -20,12 +20,10 @@
 // E = exp(-i k^2 dt) exp(i k (phi(t_{m+1}) - phi(t_m))): a static factor (a
 // table built once per plan in extended precision) times an increment computed
 // from its own small argument (1 with A = 0), so no angle error grows with k or
-// with the step count.  A launch that ends before T leaves the propagated
-// entries in memory for the next one, and the newest n-1 entries What_m in the
-// history ring, from which a launch propagates them anew, by the same products
-// in the same order, when the field has been changed in between (pieces of one
-// step with a pulse at N = 2048: 35.3 -> 21.0 us a launch, which was mostly the
-// sines of that).
+// with the step count.  The newest n-1 entries What_m go to the history ring in
+// memory, from which the next launch propagates them anew, by the same
+// products in the same order; the longest lines leave the propagated entries
+// themselves for it (run1d_holds), unless the field is changed in between.
 //
 // A step is latency: two transforms of three to five exchanges on one
 // workgroup.  With the history read from the ring, a factor per history term
@@ -65,11 +63,18 @@ constexpr int run1d_ept(int N) { return N % 3 == 0 ? 3 : 4; }
 constexpr int run1d_threads(int N) { return N / run1d_ept(N); }
 constexpr bool run1d_held(int N) { return N <= 512; }
 
+// Lines whose propagated history stays in memory between launches.  At 2048
+// points a launch of one step took 35.3 us when it propagated the ring anew,
+// mostly the sines of that, and takes 21.0; below, the host's 38 us per launch
+// hide it (15 us at 512), and the stores would cost the loop 2.5 to 3 % (512
+// points 3.00 -> 3.10 us per step).
+constexpr bool run1d_holds(int N) { return N >= 2048; }
+
 // PH: the field A is nonzero, so the phase factors carry increments
 template <int N, bool PH>
 __global__ __launch_bounds__(run1d_threads(N)) void k_run1d(Run1DArgs a) {
   constexpr int EA = 4, TA = N / EA, EB = run1d_ept(N), TB = N / EB, H = MAXH - 1;
-  constexpr bool HELD = run1d_held(N);
+  constexpr bool HELD = run1d_held(N), HOLD = run1d_holds(N);
   constexpr double PI = 3.14159265358979323846264338327950288;
   HIP_DYNAMIC_SHARED(double2, run1d_lds)
   double2* la = run1d_lds;                          // the two exchange lines
@@ -271,7 +276,7 @@ __global__ __launch_bounds__(run1d_threads(N)) void k_run1d(Run1DArgs a) {
   } else {
 #pragma unroll
     for (int q = 0; q < EB; ++q) B[q] = a.B[t + TB * q];
-    if (a.held) {
+    if (HOLD && a.held) {
 #pragma unroll
       for (int j = 2; j <= H; ++j)
 #pragma unroll
@@ -313,11 +318,13 @@ __global__ __launch_bounds__(run1d_threads(N)) void k_run1d(Run1DArgs a) {
   if (a.m1 < a.nsteps) {
 #pragma unroll
     for (int q = 0; q < EB; ++q) a.B[t + TB * q] = B[q];
+    if constexpr (HOLD) {
 #pragma unroll
-    for (int j = 2; j <= H; ++j)
+      for (int j = 2; j <= H; ++j)
 #pragma unroll
-      for (int q = 0; q < EB; ++q)
-        if (j <= nh) a.G[(int64_t)(j - 2) * N + t + TB * q] = G[j - 2][q];
+        for (int q = 0; q < EB; ++q)
+          if (j <= nh) a.G[(int64_t)(j - 2) * N + t + TB * q] = G[j - 2][q];
+    }
   }
 }
 

@@ -350,12 +350,12 @@ hipError_t launch_far_gemm(int M, int N, int K, const double2* A, int64_t sam, i
 //   oD + i - 1                    phi(t_i) - phi(t_{i-1}), i = 1..nsteps
 // (f_r: the eight potential time factors, or the moving well's parameters).
 // stab holds exp(-i k^2 dt), then exp(-i k^2 dt / 2^l), l < L.  G and held as
-// in FSRun1DArgs, for launches past the Adams start.
+// in FSRun1DArgs, for the lines that run1d_kernels.hip keeps them for.
 struct Run1DArgs {
   int M, order, ns, nsteps, L;
   int m0, m1;
   int nV, vkind;
-  int write_u, has_phase, held;
+  int write_u, has_phase;
   double dt, c0;
   double ch[MAXH + 1];
   double rich[4];
@@ -367,9 +367,10 @@ struct Run1DArgs {
   double2* u_out;
   double2* B;
   double2* ring;
-  double2* G;
   const double2* stab;
   const double2* tw;
+  double2* G;
+  int held;
 };
 bool run1d_supported(int N);
 hipError_t launch_run1d(const Run1DArgs& a, hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);

@@ -56,8 +56,8 @@ def test_free_1d_pieces_equal_the_whole_run(emu):
         assert np.array_equal(_state(plan, M), full), (M, order)
 
 
-@pytest.mark.parametrize("domain, order", [("periodic", 8), ("periodic", 4), ("free", 6)])
-def test_field_changed_between_pieces(emu, domain, order):
+@pytest.mark.parametrize("domain, M, order", [("periodic", 32, 8), ("periodic", 2048, 4), ("free", 32, 6)])
+def test_field_changed_between_pieces(emu, domain, M, order):
     """The entries in flight are carried with the new field, as by the general
     passes (a sampled potential takes those; in free space a profiled run)."""
     from emu.emu_plan import EmuPlan
@@ -66,10 +66,10 @@ def test_field_changed_between_pieces(emu, domain, order):
 
     N = order + 9
     if domain == "periodic":
-        prob = periodic_problem_from_seed(150, 1, (32,), 0.05, N, order=order, A_kind="stepwise")
+        prob = periodic_problem_from_seed(150, 1, (M,), 0.05, N, order=order, A_kind="stepwise")
         prob.n_start, prob.f_kind, prob.f_params = order - 1, ["const"], [(0.0, 0.0)]
     else:
-        prob = free_problem_from_seed(151, 1, (32,), 0.02, N, order=order, nu=(256,), eps=1e-8, q=8)
+        prob = free_problem_from_seed(151, 1, (M,), 0.02, N, order=order, nu=(256,), eps=1e-8, q=8)
     rng = np.random.default_rng(7)
     fields = [np.ascontiguousarray(rng.uniform(-1, 1, size=(N, 1))) for _ in range(2)]
 

@@ -69,3 +69,32 @@ def test_a_run_captured_while_steps_are_under_way():
     plan.configure(CFG_PERSISTENT, 0)
     assert torch.equal(plan.run(u0), out)
     plan.close()
+
+
+@pytest.mark.parametrize("M", [64, 384])
+def test_plans_on_streams_of_their_own(M):
+    """Steps of three plans, queued without waiting: their launches take turns."""
+    import torch
+
+    from paper_2001_06113_amd.tdse import Plan
+
+    print(f"case persistent plans on three streams M={M}", flush=True)
+    probs = [periodic_problem_from_seed(140 + i, 2, (M, M), 0.02, 40, order=8) for i in range(3)]
+    plans = [Plan.from_problem(p, device="cuda:0") for p in probs]
+    u0 = [torch.as_tensor(p.u0).to("cuda:0", torch.complex128) for p in probs]
+    ref = [p.run(u).clone() for p, u in zip(plans, u0)]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in plans]
+    out = [None] * 3
+    for k in (20, 1, 19):
+        for i, plan in enumerate(plans):
+            with torch.cuda.stream(streams[i]):
+                if k == 20:
+                    plan.set_state(u0[i])
+                plan.step(k)
+                if k == 19:
+                    out[i] = plan.get_state()
+    torch.cuda.synchronize()
+    for plan, a, b in zip(plans, out, ref):
+        assert torch.equal(a, b)
+        plan.close()
