@@ -43,10 +43,12 @@ def build(sanitize: bool = False) -> str:
              f"-I{os.path.join(HERE, 'stub')}", f"-I{CSRC}", f"-I{os.path.join(ROOT, 'include')}", "-x", "c++"]
     if sanitize:
         flags = ["-fsanitize=address,undefined", "-fno-omit-frame-pointer"] + flags
-    cmd = ["g++", *flags, *SOURCES, "-o", OUT]
+    tmp = f"{OUT}.tmp{os.getpid()}"   # several test processes may build at once
+    cmd = ["g++", *flags, *SOURCES, "-o", tmp]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(" ".join(cmd) + "\n" + r.stderr[-4000:])
+    os.replace(tmp, OUT)
     return OUT
 
 
